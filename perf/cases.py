@@ -134,3 +134,21 @@ def tolerance(case):
     if case["kind"] == "f32":
         return {"rel": 5e-6, "max": 4e-5}
     return {"rel": 2.5e-6, "max": 2e-5}
+
+
+def exact(case, seed):
+    """The product of the same operands in binary64, laid out as run() returns it."""
+    dtype = KINDS[case["kind"]][1]
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    M, N, K = case["M"], case["N"], case["K"]
+
+    def dense(rows, cols, layout):
+        x, ld = _matrix(rows, cols, layout, case["pad"], dtype, case["dist"], gen)
+        major, minor = (rows, cols) if layout == ROW else (cols, rows)
+        x = x.view(major, ld)[:, :minor].to(torch.float64)
+        return x if layout == ROW else x.t()
+
+    A = dense(M, K, case["a"])
+    B = dense(K, N, case["b"])
+    C = torch.matmul(A, B)
+    return C if case["c"] == ROW else C.t().contiguous()
