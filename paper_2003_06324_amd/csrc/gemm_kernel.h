@@ -265,7 +265,7 @@ struct DirectLoader {
 // while the current one is multiplied: guarded_fetch (global -> registers) and
 // staged_store (registers -> LDS).  A granule that lies fully inside the
 // matrix is fetched with one 16-byte load (element-aligned only: the compiler
-// picks the widest access the target allows), a ragged one element by element.
+// picks the widest access the target allows), one at the edge as guarded_fetch says.
 // ---------------------------------------------------------------------------
 template <typename T, int R, int NT>
 struct Staged {
@@ -296,7 +296,41 @@ __device__ __forceinline__ void granule_of(int q, const T *base, int64_t ld, int
     }
 }
 
-// global -> registers: whole granules only (ragged ones are left zero, see staged_store)
+// the upper n elements of 16 bytes moved to their beginning, zeros behind them; n is the same for the wave
+template <typename T>
+__device__ __forceinline__ uint4_t last_elements(const uint4_t &w, int n)
+{
+    const int s = __builtin_amdgcn_readfirstlane(128 - n * 8 * (int)sizeof(T));  // bits to drop at the low end, 16 .. 112
+    const uint64_t lo = ((uint64_t)w[1] << 32) | w[0], hi = ((uint64_t)w[3] << 32) | w[2];
+    uint64_t l, h = 0;
+    if (s >= 64) {
+        l = hi >> (s - 64);
+    } else {
+        l = (lo >> s) | (hi << (64 - s));
+        h = hi >> s;
+    }
+    const uint4_t out = {(uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32)};
+    return out;
+}
+
+// Granules that straddle the edge of the matrix hold the same number of elements, the extent modulo the granule.  With
+// two or more of them the granule is loaded as the last 16 bytes of its row, which hold those elements, and shifted
+// into place: one load, in flight with the others.  Fetched one after the other between the loads and the LDS stores
+// they kept a workgroup waiting for a memory round trip each (binary16 304x151x151 7.10 us, now 5.36; 540x1679x949
+// 10.6, now 9.2); rows shorter than a granule still are.
+template <typename T> __device__ __forceinline__ bool edge_as_granule(int extent)
+{
+    constexpr int EPC = Elem<T>::EPC;
+    return extent >= EPC && extent % EPC > 1;
+}
+// whether a slab has such granules at all
+template <typename T, int R, bool KC> __device__ __forceinline__ bool has_edge(int row0, int rmax, int k0, int kend)
+{
+    constexpr int EPC = Elem<T>::EPC;
+    return KC ? kend % EPC != 0 && k0 + Elem<T>::BK > kend : rmax % EPC != 0 && row0 + R > rmax;
+}
+
+// global -> registers
 template <typename T, int R, int NT, bool KC>
 __device__ __forceinline__ void guarded_fetch(Staged<T, R, NT> &st, const T *base, int64_t ld,
                                               int row0, int rmax, int k0, int kend, int tid)
@@ -314,10 +348,20 @@ __device__ __forceinline__ void guarded_fetch(Staged<T, R, NT> &st, const T *bas
         if (nvalid >= EPC) __builtin_memcpy(&w, p, 16);
         st.v[i] = w;
     }
+    if (has_edge<T, R, KC>(row0, rmax, k0, kend) && edge_as_granule<T>(KC ? kend : rmax)) {
+#pragma unroll
+        for (int i = 0; i < Staged<T, R, NT>::ITERS; ++i) {
+            const int q = tid + i * NT;
+            const T *p;
+            int nvalid, off;
+            granule_of<T, R, KC>(q, base, ld, row0, rmax, k0, kend, p, nvalid, off);
+            if (NGRAN % NT != 0 && q >= NGRAN) nvalid = 0;
+            if (nvalid > 0 && nvalid < EPC) __builtin_memcpy(&st.v[i], p - (EPC - nvalid), 16);
+        }
+    }
 }
 
-// registers -> LDS; the few granules that straddle the matrix edge or the end of K are
-// completed here, element by element, straight from global memory
+// registers -> LDS
 template <typename T, int R, int NT, bool KC>
 __device__ __forceinline__ void staged_store(GEMM_LDS(char) *dst, const Staged<T, R, NT> &st,
                                              const T *base, int64_t ld, int row0, int rmax, int k0,
@@ -325,18 +369,42 @@ __device__ __forceinline__ void staged_store(GEMM_LDS(char) *dst, const Staged<T
 {
     constexpr int EPC = Elem<T>::EPC;
     constexpr int NGRAN = R * GPR;
+    constexpr int ITERS = Staged<T, R, NT>::ITERS;
+    const T *p[ITERS];
+    int nvalid[ITERS], off[ITERS];
 #pragma unroll
-    for (int i = 0; i < Staged<T, R, NT>::ITERS; ++i) {
+    for (int i = 0; i < ITERS; ++i) {
         const int q = tid + i * NT;
-        if (NGRAN % NT != 0 && q >= NGRAN) break;
-        const T *p;
-        int nvalid, off;
-        granule_of<T, R, KC>(q, base, ld, row0, rmax, k0, kend, p, nvalid, off);
-        *(GEMM_LDS(uint4_t) *)(dst + off) = st.v[i];
-        if (nvalid > 0 && nvalid < EPC) {
-            GEMM_LDS(T) *d = (GEMM_LDS(T) *)(dst + off);
+        granule_of<T, R, KC>(q, base, ld, row0, rmax, k0, kend, p[i], nvalid[i], off[i]);
+        if (NGRAN % NT != 0 && q >= NGRAN) continue;
+        *(GEMM_LDS(uint4_t) *)(dst + off[i]) = st.v[i];
+    }
+    if (!has_edge<T, R, KC>(row0, rmax, k0, kend)) return;
+    // once more for the granules at the edge (out of the way of the slabs that have none)
+    auto ragged = [&](int i) { return !(NGRAN % NT != 0 && tid + i * NT >= NGRAN) && nvalid[i] > 0 && nvalid[i] < EPC; };
+    const int extent = KC ? kend : rmax;
+    if (edge_as_granule<T>(extent)) {
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i)
+            if (ragged(i)) *(GEMM_LDS(uint4_t) *)(dst + off[i]) = last_elements<T>(st.v[i], extent % EPC);
+    } else if (extent % EPC == 1) {
+        typedef std::conditional_t<sizeof(T) == 2, uint16_t, uint32_t> bits_t;
+        uint4_t w[ITERS];
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i) w[i] = uint4_t{ragged(i) ? (uint32_t)*(const bits_t *)p[i] : 0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i)
+            if (ragged(i)) *(GEMM_LDS(uint4_t) *)(dst + off[i]) = w[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i) {
+            if (!ragged(i)) continue;
+            GEMM_LDS(T) *d = (GEMM_LDS(T) *)(dst + off[i]);
 #pragma unroll 1
-            for (int x = 0; x < nvalid; ++x) d[x] = p[x];
+            for (int x = 0; x < nvalid[i]; ++x) {
+                asm volatile("" ::: "memory");  // behind the zeros stored above
+                d[x] = p[i][x];
+            }
         }
     }
 }
