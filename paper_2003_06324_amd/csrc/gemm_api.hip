@@ -47,6 +47,9 @@ GEMM_DECLARE_TILE(float, 64, 128, 2, 2)
 GEMM_DECLARE_KSPLIT(_Float16, 64, 64)
 GEMM_DECLARE_KSPLIT(__bf16, 64, 64)
 GEMM_DECLARE_KSPLIT(float, 64, 64)
+GEMM_DECLARE_SMALL(_Float16)
+GEMM_DECLARE_SMALL(__bf16)
+GEMM_DECLARE_SMALL(float)
 }  // namespace gemm_gfx950
 
 namespace {
@@ -175,6 +178,11 @@ const TileConfig kTiles[] = {
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
+// The kernel for small products (gemm_small_kernel.h) as a choice of its own beside the tiles.  To callers it is the
+// smallest tile in one slice, on whose 64x64 pieces four of its blocks lie.
+constexpr int kSmall = kNumTiles, kSmallAs = 2;
+const TileConfig &tile_of(int choice) { return kTiles[choice == kSmall ? kSmallAs : choice]; }
+
 std::mutex g_mutex;
 int g_forced_tile = -1;    // -1: heuristic
 int g_forced_splits = 0;   // 0: heuristic
@@ -272,6 +280,18 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     return cost;
 }
 
+// Products gemm_small_kernel is the fastest for: blocks for one round of CUs, and a K that sixteen waves request in a
+// round or two.  Measured against the tile kernels' pick (M N from 64 64 to 1024 256, microseconds per launch back to back):
+// binary32 K = 136 6.3 -> 3.6, 256 6.9 -> 4.2, 512 7.5 .. 9.6 -> 5.7 .. 6.4, 768 6.8 .. 10.8 -> 7.3 .. 8.7;
+// 16 bits K = 136 4.3 -> 3.5, 512 4.4 .. 6.2 -> 3.5 .. 4.1, 1024 5.8 .. 6.2 -> 4.3 .. 5.8, 2048 6.4 .. 9.0 -> 6.8 .. 10.2;
+// K-contiguous rows on 2-byte boundaries, whose loads are split up, K = 136 5.2 -> 3.6, 512 5.9 -> 8.2.
+// Twice the blocks lose 10 % and more at any K.
+bool serves_small(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_contig, int num_cu)
+{
+    if (cdiv(M, 32) * cdiv(N, 32) > num_cu) return false;
+    return K <= (f32 ? 512 : (path == 2 && k_contig > 0 ? 256 : 1024));
+}
+
 // max_ws_bytes: largest K-slice workspace the caller can provide (0 = no limit); automatic
 // picks that would need more are not considered.
 // ksplit_ok: the operands qualify for the kernels that split K across the waves of a workgroup
@@ -281,6 +301,12 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
     double best = 1e300;
     tile = g_forced_tile >= 0 ? g_forced_tile : 0;
     splits = 1;
+    // (what can be forced, or traced, are the tile kernels)
+    if (g_forced_tile < 0 && g_forced_splits == 0 && !g_forced_safe && !g_force_regload && g_store_mode == 0 && g_trace == nullptr &&
+        serves_small(M, N, K, f32, path, k_contig, num_cu)) {
+        tile = kSmall;
+        return;
+    }
     // a forced slice count beyond the number of slabs means one slab per slice
     const int forced = g_forced_splits > 0 ? (int)(g_forced_splits < KT ? g_forced_splits : KT) : 0;
     for (int t = 0; t < kNumTiles; ++t) {
@@ -512,8 +538,9 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         choose(M, N, K, KT, f32, path, (int)akc + (int)bkc, num_cu, noalloc ? (size_t)GEMM_NOALLOC_SCRATCH_BYTES : 0,
                ksplit_ok, tile, splits);
     }
-    if (kTiles[tile].fallback >= 0 && !ksplit_ok) tile = kTiles[tile].fallback;  // forced, but not served by that kernel
-    const TileConfig &t = kTiles[tile];
+    const bool small = tile == kSmall;
+    if (tile_of(tile).fallback >= 0 && !ksplit_ok) tile = kTiles[tile].fallback;  // forced, but not served by that kernel
+    const TileConfig &t = tile_of(tile);
     const int64_t tiles_m = cdiv(M, t.BM), tiles_n = cdiv(N, t.BN);
     int64_t kt_per_split = cdiv(KT, splits);
     splits = (int)cdiv(KT, kt_per_split);  // no empty slices
@@ -577,9 +604,16 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         const bool rounds = tiles_m * tiles_n > (int64_t)num_cu * t.wg_per_cu;
         a.stream_c = (lines && (rounds || M * N * 4 <= (32LL << 20))) ? 1 : 0;
     }
-    const dim3 grid((unsigned)(8 * cdiv(tiles_m * tiles_n * splits, 8)));
-    const launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
-    const hipError_t launch_rc = fn(akc, bkc, aligned, grid, stream, a);
+    hipError_t launch_rc;
+    if (small) {
+        a.tiles_m = (int)cdiv(M, 32);
+        a.tiles_n = (int)cdiv(N, 32);
+        launch_rc = launch_small<T>(akc, bkc, dim3((unsigned)(a.tiles_m * a.tiles_n)), stream, a);
+    } else {
+        const dim3 grid((unsigned)(8 * cdiv(tiles_m * tiles_n * splits, 8)));
+        const launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
+        launch_rc = fn(akc, bkc, aligned, grid, stream, a);
+    }
     if (launch_rc != hipSuccess) {
         if (getenv("GEMM_VERBOSE"))
             fprintf(stderr, "gemm: launch of %s failed: %s\n", t.name, hipGetErrorString(launch_rc));
@@ -594,8 +628,8 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
                                             vec_c);
         if (rc != hipSuccess) return GEMM_ERR_HIP;
     }
-    snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s", type_name, t.name,
-             akc ? 'N' : 'T', bkc ? 'T' : 'N', aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, a.safe ? " safe" : "",
+    snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s", type_name, t.name,
+             akc ? 'N' : 'T', bkc ? 'T' : 'N', aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, small ? " small" : "", a.safe ? " safe" : "",
              noalloc && splits > 1 ? " static-scratch" : "");
     return GEMM_OK;
 }
@@ -623,6 +657,7 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     std::vector<std::tuple<double, int, int>> cand;
     {
         std::lock_guard<std::mutex> lock(g_mutex);
+        if (serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
         for (int t = 0; t < kNumTiles; ++t) {
             if (kTiles[t].fallback >= 0 && !key.ksplit_ok) continue;
             for (int s = 1; s <= 32 && (s == 1 || s <= KT); s *= 2)
@@ -706,7 +741,7 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     // the product, by the configuration just recorded (unless one is forced)
     rc = gemm_impl<T, TC>(M, N, K, A, layA, lda, B, layB, ldb, C, layC, ldc, stream_);
     const int64_t per = cdiv(KT, best_splits);
-    snprintf(buf, (size_t)buflen, "%s:s%d", kTiles[best_tile].name, (int)cdiv(KT, per));
+    snprintf(buf, (size_t)buflen, "%s:s%d", tile_of(best_tile).name, (int)cdiv(KT, per));
     return rc;
 }
 
@@ -790,7 +825,7 @@ int gemm_tune_save(const char *path)
     for (const auto &e : g_tuned) {
         const ShapeKey &k = e.first;
         fprintf(f, "%d %lld %lld %lld %d %d %d %d %s %d\n", k.f32 ? 4 : 2, (long long)k.M, (long long)k.N, (long long)k.K, k.path,
-                k.k_contig, k.num_cu, k.ksplit_ok, kTiles[e.second.first].name, e.second.second);
+                k.k_contig, k.num_cu, k.ksplit_ok, e.second.first == kSmall ? "small" : kTiles[e.second.first].name, e.second.second);
     }
     return fclose(f) == 0 ? GEMM_OK : GEMM_ERR_INVALID_ARG;
 }
@@ -817,8 +852,10 @@ int gemm_tune_load(const char *path)
         int tile = -1;
         for (int i = 0; i < kNumTiles; ++i)
             if (strcmp(name, kTiles[i].name) == 0) tile = i;
+        // (a line written where the small kernel served more than here runs as the tile that it stands for)
+        if (strcmp(name, "small") == 0) tile = serves_small(M, N, K, esz == 4, path_, kc, cus) ? kSmall : kSmallAs;
         // a tile this build does not have, or one that does not serve the class, makes the file invalid as a whole
-        if (tile < 0 || (kTiles[tile].fallback >= 0 && !whole)) {
+        if (tile < 0 || (tile_of(tile).fallback >= 0 && !whole)) {
             rc = GEMM_ERR_INVALID_ARG;
             break;
         }
@@ -854,7 +891,7 @@ int gemm_query_config_layouts(int elem_bytes, int64_t M, int64_t N, int64_t K, i
     }
     const int64_t per = cdiv(KT, splits);
     splits = (int)cdiv(KT, per);  // no empty slices, as in the launch path
-    snprintf(buf, (size_t)buflen, "%s:s%d", kTiles[tile].name, splits);
+    snprintf(buf, (size_t)buflen, "%s:s%d", tile_of(tile).name, splits);
     return GEMM_OK;
 }
 
@@ -916,6 +953,7 @@ int gemm_set_phase_trace(void *device_buffer, int64_t workgroups)
 {
     std::lock_guard<std::mutex> lock(g_mutex);
     if (device_buffer != nullptr && workgroups <= 0) return GEMM_ERR_INVALID_ARG;
+    ++g_epoch;
     g_trace = (unsigned long long *)device_buffer;
     g_trace_records = device_buffer ? workgroups : 0;
     return GEMM_OK;

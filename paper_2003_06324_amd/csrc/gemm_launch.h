@@ -4,6 +4,7 @@
 #include "gemm_f32_kernel.h"
 #include "gemm_kernel.h"
 #include "gemm_ksplit_kernel.h"
+#include "gemm_small_kernel.h"
 
 #include <tuple>
 #include <type_traits>
@@ -69,6 +70,16 @@ hipError_t launch_ksplit(bool akc, bool bkc, bool aligned, dim3 grid, hipStream_
     return launch_kernel(gemm_ksplit_kernel<T, BM, BN, false, false>, grid, block, s, a);
 }
 
+template <typename T>
+hipError_t launch_small(bool akc, bool bkc, dim3 grid, hipStream_t s, const KernelArgs &a)
+{
+    const dim3 block(SMALL_WAVES * 64);
+    if (akc && bkc) return launch_kernel(gemm_small_kernel<T, true, true>, grid, block, s, a);
+    if (akc && !bkc) return launch_kernel(gemm_small_kernel<T, true, false>, grid, block, s, a);
+    if (!akc && bkc) return launch_kernel(gemm_small_kernel<T, false, true>, grid, block, s, a);
+    return launch_kernel(gemm_small_kernel<T, false, false>, grid, block, s, a);
+}
+
 typedef hipError_t (*launch_fn)(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
 
 #define GEMM_DECLARE_TILE(T, BM, BN, WM, WN) \
@@ -79,5 +90,8 @@ typedef hipError_t (*launch_fn)(bool, bool, bool, dim3, hipStream_t, const Kerne
     extern template hipError_t launch_ksplit<T, BM, BN>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
 #define GEMM_INSTANTIATE_KSPLIT(T, BM, BN) \
     template hipError_t launch_ksplit<T, BM, BN>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
+#define GEMM_DECLARE_SMALL(T) \
+    extern template hipError_t launch_small<T>(bool, bool, dim3, hipStream_t, const KernelArgs &);
+#define GEMM_INSTANTIATE_SMALL(T) template hipError_t launch_small<T>(bool, bool, dim3, hipStream_t, const KernelArgs &);
 
 }  // namespace gemm_gfx950

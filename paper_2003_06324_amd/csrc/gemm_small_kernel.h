@@ -1,0 +1,101 @@
+// Small products: one round of loads straight into matrix-instruction operands.
+//
+// A product of a few hundred rows and columns is over in a few microseconds, and what bounds it is how often a
+// memory round trip is waited for: the pipelines of the tile kernels fill and drain around a handful of slabs on
+// a handful of CUs.  Here a workgroup of sixteen waves computes one 32x32 block of C; the waves share out K, one
+// k-group (what a matrix instruction, or four of binary32, consumes) after the other, so the operands
+// of the whole block are requested at once by sixteen waves, without LDS, ring or barrier.  The sixteen partial
+// blocks meet in LDS and are added in wave order.  Loads need element alignment only, any leading
+// dimension, and are guarded at the edges of K (rows past the edges of M and N re-read the last one).
+#pragma once
+#include "gemm_kernel.h"
+
+namespace gemm_gfx950 {
+
+constexpr int SMALL_WAVES = 16;
+
+// the fragment of one k-group: EPL consecutive k of one row, zero from kend on (full: the group lies below kend)
+template <typename T, bool KC>
+__device__ __forceinline__ typename Frag<T>::type small_fragment(const T *base, int64_t ld, int64_t row, int k, int kend, bool full)
+{
+    constexpr int EPL = Elem<T>::KG / 2;  // elements per lane
+    typedef typename Frag<T>::type frag_t;
+    frag_t f;
+    if constexpr (KC) {
+        typedef frag_t loose_t __attribute__((aligned(sizeof(T))));
+        const T *p = base + row * ld + k;
+        if (full) {
+            f = *(const loose_t *)p;
+        } else {
+#pragma unroll
+            for (int x = 0; x < EPL; ++x) f[x] = k + x < kend ? p[x] : (T)0.0f;
+        }
+    } else {
+        const T *p = base + (int64_t)k * ld + row;
+        if (full) {
+#pragma unroll
+            for (int x = 0; x < EPL; ++x) f[x] = p[(int64_t)x * ld];
+        } else {
+#pragma unroll
+            for (int x = 0; x < EPL; ++x) f[x] = k + x < kend ? p[(int64_t)x * ld] : (T)0.0f;
+        }
+    }
+    return f;
+}
+
+template <typename T, bool AKC, bool BKC>
+__global__ __launch_bounds__(SMALL_WAVES * 64) void gemm_small_kernel(const KernelArgs p)
+{
+    constexpr int KG = Elem<T>::KG, W = SMALL_WAVES, BATCH = 4;
+    constexpr int SW = 33;  // row stride of a partial block in LDS, in words
+    typedef typename Frag<T>::type frag_t;
+    __shared__ float part[W][32 * SW];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile_m = blockIdx.x / p.tiles_n, tile_n = blockIdx.x - tile_m * p.tiles_n;
+    const int m0 = tile_m * 32, n0 = tile_n * 32;
+    const T *A = (const T *)p.A, *B = (const T *)p.B;
+    const int m = m0 + (lane & 31) < p.M ? m0 + (lane & 31) : p.M - 1;
+    const int n = n0 + (lane & 31) < p.N ? n0 + (lane & 31) : p.N - 1;
+    const int groups = (p.K + KG - 1) / KG, kl = (KG / 2) * (lane >> 5);
+
+    float16_t acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    // the wave's k-groups are wave, wave + W, ...; as many as BATCH whole ones are requested together
+    auto batch = [&](auto n_tag, int g, bool full) {
+        constexpr int N = decltype(n_tag)::value;
+        frag_t fa[N], fb[N];
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+            const int k = (g + b * W) * KG + kl;
+            fa[b] = small_fragment<T, AKC>(A, p.lda, m, k, p.K, full);
+            fb[b] = small_fragment<T, BKC>(B, p.ldb, n, k, p.K, full);
+        }
+#pragma unroll
+        for (int b = 0; b < N; ++b) mma(acc, fa[b], fb[b]);
+    };
+    const int whole = p.K / KG;
+    int g = wave;
+    for (; g + (BATCH - 1) * W < whole; g += BATCH * W) batch(std::integral_constant<int, BATCH>(), g, true);
+    static_assert(BATCH == 4, "the rest is one to three");
+    if (g + 2 * W < whole) batch(std::integral_constant<int, 3>(), g, true);
+    else if (g + W < whole) batch(std::integral_constant<int, 2>(), g, true);
+    else if (g < whole) batch(std::integral_constant<int, 1>(), g, true);
+    if (whole < groups && whole % W == wave) batch(std::integral_constant<int, 1>(), whole, false);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[wave][(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * SW + (lane & 31)] = acc[r];
+    __syncthreads();
+    const int row = tid >> 5, col = tid & 31;
+    float s = part[0][row * SW + col];
+#pragma unroll
+    for (int w = 1; w < W; ++w) s += part[w][row * SW + col];
+    if (m0 + row < p.M && n0 + col < p.N) {
+        const int64_t at = (int64_t)(m0 + row) * p.ldc + n0 + col;
+        if (p.out16) ((_Float16 *)p.C)[at] = (_Float16)s;
+        else p.C[at] = s;
+    }
+}
+
+}  // namespace gemm_gfx950

@@ -1,0 +1,45 @@
+"""The kernel for small products: every remainder of the 32x32 blocks and of the k-groups its sixteen waves
+share out, all operand types and layouts, misaligned rows, and the limits of the sizes it is chosen for."""
+import numpy as np
+import pytest
+
+import gemm_inputs as gi
+from gpu_util import check, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 1, 1), (31, 33, 7), (32, 64, 8), (33, 31, 15), (65, 40, 17), (100, 95, 129), (64, 32, 255), (40, 72, 257), (256, 1024, 256),
+          (300, 200, 136), (8, 500, 250)]
+
+
+def _ref(oracle, A, B, dtype):
+    if dtype == "bf16":
+        A, B = gi.bfloat16_bits(A), gi.bfloat16_bits(B)
+    return oracle.gemm(A.shape[0], B.shape[1], A.shape[1], A, 0, B, 0, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_small_products_are_exact_on_whole_numbers(oracle, dtype, shape):
+    M, N, K = shape
+    A, B = gi.make_problem(1300 + M + K, M, N, K, "int", dtype)
+    ref = _ref(oracle, A, B, dtype)
+    for i, (la, lb) in enumerate(((0, 0), (0, 1), (1, 0), (1, 1))):
+        for pads, offs in (((0, 0, 0), (0, 0, 0)), ((1, 3, 2), (1, 0, 3))):
+            C, cfg = run_gpu(dtype, A, B, la, lb, lc=i % 2, pads=pads, offsets=offs, return_config=True)
+            # (2-byte aligned K-contiguous rows are served up to K = 256)
+            assert cfg.endswith(" small") or (K > 256 and "general" in cfg), (dtype, shape, la, lb, pads, cfg)
+            assert np.array_equal(C.astype(np.float64), ref), (dtype, shape, la, lb, pads, cfg)
+        if dtype == "f16":
+            C = run_gpu(dtype, A, B, la, lb, out="f16")
+            assert np.array_equal(C.view(np.uint16), oracle.round_to_half(ref).view(np.uint16))
+
+
+@pytest.mark.parametrize("dtype,limit", [("f16", 1024), ("bf16", 1024), ("f32", 512)])
+def test_the_limits_of_the_choice(oracle, dtype, limit):
+    for (M, N, K), small in (((256, 512, limit), True), ((256, 512, limit + 8), False), ((512, 512, limit), True),
+                             ((513, 512, limit), False)):
+        A, B = gi.make_problem(77 + K, M, N, K, "normal", dtype)
+        C, cfg = run_gpu(dtype, A, B, 0, 1, return_config=True)
+        assert cfg.endswith(" small") == small, (M, N, K, cfg)
+        check(C, _ref(oracle, A, B, dtype), A, B, dtype, cfg)
