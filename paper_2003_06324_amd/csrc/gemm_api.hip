@@ -319,6 +319,11 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
             const int cand = forced > 0 ? forced : s;
             if (cand > 1 && cand > KT) break;
             if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
+            // Sums of more than 4096 terms are cut into slices of at most kSplitMaxK per accumulator on the split kernels:
+            // the small tiles of the binary32 instructions cut long sums to fill the chip, and the error of a sum grows
+            // with the square root of its terms (659x906x61365: 7.9e-7 in 32 slices there, 1.25e-6 in 16 here).
+            if (forced == 0 && f32 && K > 4096 && kTiles[t].BM * kTiles[t].BN > 64 * 64 && cand < 32 && 2 * cand <= KT &&
+                cdiv(K, cand) > kSplitMaxK * f32_wave_groups(kTiles[t].BM, kTiles[t].BN)) continue;
             const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu);
             if (c < best) { best = c; tile = t; splits = cand; }
             if (forced > 0) break;

@@ -34,6 +34,7 @@ typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
 // 512x512xK product, 2-norm, binary32 instructions / split: K = 1 2.5e-8 / 5.2e-8, 16 7.3e-8 / 8.2e-8, 32 1.03e-7 /
 // 1.04e-7, 64 1.44e-7 / 1.35e-7, 512 4.1e-7 / 3.5e-7, 32768 3.2e-6 / 3.0e-6).
 constexpr int kSplitMinK = 64;
+constexpr int kSplitMaxK = 2048;  // terms per accumulator the selection does not exceed in long sums (error 7e-7 there)
 
 // Two operands as three pairs of bfloat16; rest collects the bits the three pieces do not hold
 // (bits 0..15 nonzero: the split was not exact).
