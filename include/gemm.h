@@ -222,8 +222,8 @@ int gemm_tune_clear(void);
  * The recorded pairs as a text file, so that a service tunes once and later processes start with the picks:
  * gemm_tune_save writes every pair gemm_tune has recorded (one line each: bytes per operand element, M, N,
  * K, alignment class, number of K-contiguous operands, CU count, whether the operands are whole slabs and
- * granules, tile name, K slices; '#' starts a comment line); gemm_tune_load adds the pairs of such a file to
- * the table, replacing entries for the same class.  Host only.  GEMM_ERR_INVALID_ARG if the file cannot be
+ * granules, tile name, K slices, and "small" where the kernel for small products runs; '#' starts a comment
+ * line); gemm_tune_load adds the pairs of such a file to the table, replacing entries for the same class.  Host only.  GEMM_ERR_INVALID_ARG if the file cannot be
  * opened or written, or (load) if any line does not parse, names a tile this build does not have or one
  * that cannot serve the line's class, or a K-slice count outside 1 .. 32 (what gemm_tune records): then
  * nothing of the file is taken over.
@@ -273,7 +273,8 @@ const char *gemm_config_name(int i);
 
 /*
  * Description of the configuration the last successful call on this thread
- * used, e.g. "f16 t256x256 NT aligned s1".  The string is thread-local storage
+ * used, e.g. "f16 t256x256 NT aligned s1"; " small" at the end: the kernel for
+ * small products ran, which the selection counts as the smallest tile in one slice.  The string is thread-local storage
  * owned by the library, valid until the thread's next gemm call.
  */
 const char *gemm_last_config(void);

@@ -154,6 +154,8 @@ struct TileConfig {
 // model's pick against the best measured configuration (fit_cost_model.py; tune_sweep.py prints that ratio).  The
 // slab times therefore absorb what the model has no term for (a lone workgroup's slab is bound
 // by load latency, not by its MFMA work) and are not clock-peak figures.
+// The binary32 columns were fitted again, alone, for the kernels on bfloat16 pieces (117 random shapes, 320 of the powers of
+// two; time of the pick over the best measured 1.01 in the mean, 1.12 at most).
 // (64x128 before 128x64: the model often ties the two, and the tie goes to the first; 64x128 measures 4-8 % ahead)
 const TileConfig kTiles[] = {
     {"t256x256", 256, 256, 1, 1.02, 1.02, 3.46, 3.46, 7.2, 11.9, 0.83, 1.2, 0.942, 1.67, 1.25, 1,
@@ -283,13 +285,14 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
 // Products gemm_small_kernel is the fastest for: blocks for one round of CUs, and a K that sixteen waves request in a
 // round or two.  Measured against the tile kernels' pick (M N from 64 64 to 1024 256, microseconds per launch back to back):
 // binary32 K = 136 6.3 -> 3.6, 256 6.9 -> 4.2, 512 7.5 .. 9.6 -> 5.7 .. 6.4, 768 6.8 .. 10.8 -> 7.3 .. 8.7;
-// 16 bits K = 136 4.3 -> 3.5, 512 4.4 .. 6.2 -> 3.5 .. 4.1, 1024 5.8 .. 6.2 -> 4.3 .. 5.8, 2048 6.4 .. 9.0 -> 6.8 .. 10.2;
+// 16 bits K = 136 4.3 -> 3.5, 512 4.4 .. 6.2 -> 3.5 .. 4.1, 768 5.2 .. 7.2 -> 3.9 .. 5.0, 1024 with both operands K-contiguous
+// 5.8 .. 5.9 -> 5.7 .. 5.8, 2048 6.4 .. 9.0 -> 6.8 .. 10.2;
 // K-contiguous rows on 2-byte boundaries, whose loads are split up, K = 136 5.2 -> 3.6, 512 5.9 -> 8.2.
 // Twice the blocks lose 10 % and more at any K.
 bool serves_small(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_contig, int num_cu)
 {
     if (cdiv(M, 32) * cdiv(N, 32) > num_cu) return false;
-    return K <= (f32 ? 512 : (path == 2 && k_contig > 0 ? 256 : 1024));
+    return K <= (f32 ? 512 : (path == 2 && k_contig > 0 ? 256 : 768));
 }
 
 // max_ws_bytes: largest K-slice workspace the caller can provide (0 = no limit); automatic
@@ -321,8 +324,9 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
             if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
             // Sums of more than 4096 terms are cut into slices of at most kSplitMaxK per accumulator on the split kernels:
             // the small tiles of the binary32 instructions cut long sums to fill the chip, and the error of a sum grows
-            // with the square root of its terms (659x906x61365: 7.9e-7 in 32 slices there, 1.25e-6 in 16 here).
-            if (forced == 0 && f32 && K > 4096 && kTiles[t].BM * kTiles[t].BN > 64 * 64 && cand < 32 && 2 * cand <= KT &&
+            // with the square root of its terms (659x906x61365: 7.9e-7 in 32 slices there, 1.25e-6 in 16 here).  Results of
+            // more than 2^21 entries fill the chip in one slice on any tile, and partial sums of that size are not worth it.
+            if (forced == 0 && f32 && K > 4096 && M * N <= (1 << 21) && kTiles[t].BM * kTiles[t].BN > 64 * 64 && cand < 32 && 2 * cand <= KT &&
                 cdiv(K, cand) > kSplitMaxK * f32_wave_groups(kTiles[t].BM, kTiles[t].BN)) continue;
             const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu);
             if (c < best) { best = c; tile = t; splits = cand; }
@@ -819,7 +823,8 @@ int gemm_tune_clear(void)
 }
 
 // One recorded pick per line: "<bytes per operand element> M N K <alignment class> <K-contiguous operands> <CUs>
-// <whole slabs and granules> <tile> <K slices>"; lines starting with '#' are comments.
+// <whole slabs and granules> <tile> <K slices>", and "small" if the small kernel runs as that tile; lines starting
+// with '#' are comments.
 int gemm_tune_save(const char *path)
 {
     if (path == nullptr) return GEMM_ERR_INVALID_ARG;
@@ -829,8 +834,8 @@ int gemm_tune_save(const char *path)
     fprintf(f, "# gemm_tune picks: elem_bytes M N K class k_contig cus whole tile slices\n");
     for (const auto &e : g_tuned) {
         const ShapeKey &k = e.first;
-        fprintf(f, "%d %lld %lld %lld %d %d %d %d %s %d\n", k.f32 ? 4 : 2, (long long)k.M, (long long)k.N, (long long)k.K, k.path,
-                k.k_contig, k.num_cu, k.ksplit_ok, e.second.first == kSmall ? "small" : kTiles[e.second.first].name, e.second.second);
+        fprintf(f, "%d %lld %lld %lld %d %d %d %d %s %d%s\n", k.f32 ? 4 : 2, (long long)k.M, (long long)k.N, (long long)k.K, k.path,
+                k.k_contig, k.num_cu, k.ksplit_ok, tile_of(e.second.first).name, e.second.second, e.second.first == kSmall ? " small" : "");
     }
     return fclose(f) == 0 ? GEMM_OK : GEMM_ERR_INVALID_ARG;
 }
@@ -847,8 +852,9 @@ int gemm_tune_load(const char *path)
         if (line[0] == '#' || line[0] == '\n' || line[0] == 0) continue;
         long long M, N, K;
         int esz, path_, kc, cus, whole, slices;
-        char name[32];
-        if (sscanf(line, "%d %lld %lld %lld %d %d %d %d %31s %d", &esz, &M, &N, &K, &path_, &kc, &cus, &whole, name, &slices) != 10 ||
+        char name[32], kernel[32] = "";
+        if (sscanf(line, "%d %lld %lld %lld %d %d %d %d %31s %d %31s", &esz, &M, &N, &K, &path_, &kc, &cus, &whole, name, &slices,
+                   kernel) < 10 ||
             (esz != 2 && esz != 4) || M <= 0 || N <= 0 || K <= 0 || path_ < 0 || path_ > 3 || kc < 0 || kc > 2 || cus <= 0 ||
             (whole != 0 && whole != 1) || slices < 1 || slices > 32) {   // gemm_tune records 1 .. 32 slices
             rc = GEMM_ERR_INVALID_ARG;
@@ -857,8 +863,8 @@ int gemm_tune_load(const char *path)
         int tile = -1;
         for (int i = 0; i < kNumTiles; ++i)
             if (strcmp(name, kTiles[i].name) == 0) tile = i;
-        // (a line written where the small kernel served more than here runs as the tile that it stands for)
-        if (strcmp(name, "small") == 0) tile = serves_small(M, N, K, esz == 4, path_, kc, cus) ? kSmall : kSmallAs;
+        // the small kernel, where it serves the size
+        if (strcmp(kernel, "small") == 0 && tile == kSmallAs && slices == 1 && serves_small(M, N, K, esz == 4, path_, kc, cus)) tile = kSmall;
         // a tile this build does not have, or one that does not serve the class, makes the file invalid as a whole
         if (tile < 0 || (tile_of(tile).fallback >= 0 && !whole)) {
             rc = GEMM_ERR_INVALID_ARG;

@@ -35,7 +35,7 @@ def test_small_products_are_exact_on_whole_numbers(oracle, dtype, shape):
             assert np.array_equal(C.view(np.uint16), oracle.round_to_half(ref).view(np.uint16))
 
 
-@pytest.mark.parametrize("dtype,limit", [("f16", 1024), ("bf16", 1024), ("f32", 512)])
+@pytest.mark.parametrize("dtype,limit", [("f16", 768), ("bf16", 768), ("f32", 512)])
 def test_the_limits_of_the_choice(oracle, dtype, limit):
     for (M, N, K), small in (((256, 512, limit), True), ((256, 512, limit + 8), False), ((512, 512, limit), True),
                              ((513, 512, limit), False)):
