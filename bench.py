@@ -22,9 +22,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# MI355X dense MFMA peaks: 256 CU x 2.4 GHz x 4096 flop/clk/CU, and for binary32 a sixth of it: six bfloat16 products
-# per product (the binary32 instructions peak at 157.3)
-PEAK_TFLOPS = {"f16": 2516.6, "f32": 419.4}
+PEAK_TFLOPS = {"f16": 2516.6, "f32": 157.3}   # MI355X dense MFMA peaks: 256 CU x 2.4 GHz x 4096 / 256 flop/clk/CU
 
 
 def device_operands(A, B, layout):

@@ -29,12 +29,7 @@
  *   take slower kernels that stage loads through registers.
  *
  * Element types
- *   gemm_f32    : binary32 operands, binary32 accumulation, binary32 C.  Small tiles and
- *                 sums of fewer than 64 terms use the binary32 matrix instructions; the
- *                 larger tiles write each operand as an exact sum of three bfloat16
- *                 numbers and accumulate the products of the pieces (error against the
- *                 exact sum not above that of the binary32 instructions; operands or
- *                 results that this does not hold are computed with those).
+ *   gemm_f32    : binary32 operands, IEEE binary32 multiply-add, binary32 C.
  *   gemm_f16f32 : binary16 operands (passed as their 16-bit patterns), products
  *                 accumulated in binary32, binary32 C.
  *   gemm_f16f16 : the same, with C rounded to binary16 at the store.

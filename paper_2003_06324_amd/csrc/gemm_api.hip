@@ -128,7 +128,7 @@ struct TileConfig {
     int wg_per_cu;              // resident workgroups per CU (LDS-limited)
     double f16_alone, f16_full; // microseconds per 64-k slab: one workgroup on a CU / CU fully occupied
     double f32_alone, f32_full; // same per 32-k f32 slab
-    double fixed, fixed32;      // microseconds a round of tiles spends outside its K loop (first operands, stores): 16-bit, binary32
+    double fixed;               // microseconds a round of tiles spends outside its K loop (first operands, stores)
     double hbm_eff;             // share of the model's HBM rate this tile's access pattern reaches
     double f16_a4, f32_a4;      // slab time on 4-/8-byte aligned operands (direct loads whose row pieces straddle
                                 // cache lines) over the aligned slab time
@@ -154,28 +154,26 @@ struct TileConfig {
 // model's pick against the best measured configuration (fit_cost_model.py; tune_sweep.py prints that ratio).  The
 // slab times therefore absorb what the model has no term for (a lone workgroup's slab is bound
 // by load latency, not by its MFMA work) and are not clock-peak figures.
-// The binary32 columns were fitted again, alone, for the kernels on bfloat16 pieces (117 random shapes, 320 of the powers of
-// two; time of the pick over the best measured 1.01 in the mean, 1.12 at most).
 // (64x128 before 128x64: the model often ties the two, and the tie goes to the first; 64x128 measures 4-8 % ahead)
 const TileConfig kTiles[] = {
-    {"t256x256", 256, 256, 1, 1.02, 1.02, 3.46, 3.46, 7.2, 11.9, 0.83, 1.2, 0.942, 1.67, 1.25, 1,
+    {"t256x256", 256, 256, 1, 1.02, 1.02, 6.98, 6.98, 7.2, 0.83, 1.2, 1.05, 1.67, 1.25, 1,
      GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15},
-    {"t128x128", 128, 128, 2, 0.457, 0.868, 1.08, 2.52, 1.92, 8.69, 1.39, 1.23, 0.949, 1.57, 1.3, 3,
+    {"t128x128", 128, 128, 2, 0.457, 0.868, 1.99, 3.64, 1.92, 1.39, 1.23, 0.817, 1.57, 1.3, 3,
      GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15},
-    {"t64x64", 64, 64, 4, 0.265, 0.855, 0.498, 1.94, 1.27, 2.93, 0.78, 1.07, 0.849, 1.65, 1.35, 4,
+    {"t64x64", 64, 64, 4, 0.265, 0.855, 0.495, 1.86, 1.27, 0.78, 1.07, 0.992, 1.65, 1.35, 4,
      GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15},
-    {"t256x256w8", 256, 256, 1, 1.05, 1.05, 3.46, 3.46, 6.02, 11.9, 0.812, 1.2, 0.942, 1.35, 1.15, 1,
+    {"t256x256w8", 256, 256, 1, 1.05, 1.05, 7.6, 7.6, 6.02, 0.812, 1.2, 0.915, 1.35, 1.15, 1,
      GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15},
-    {"t256x128", 256, 128, 1, 0.71, 0.71, 2.34, 2.34, 3.82, 8.86, 0.637, 1.2, 1.01, 1.47, 1.3, 1,
+    {"t256x128", 256, 128, 1, 0.71, 0.71, 3.52, 3.52, 3.82, 0.637, 1.2, 1.09, 1.47, 1.3, 1,
      GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15},
-    {"t128x256", 128, 256, 1, 0.661, 0.661, 2.35, 2.35, 4.17, 8.13, 1.78, 1.25, 0.979, 2.03, 1.3, 1,
+    {"t128x256", 128, 256, 1, 0.661, 0.661, 4.19, 4.19, 4.17, 1.78, 1.25, 0.864, 2.03, 1.3, 1,
      GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15},
-    {"t64x128", 64, 128, 2, 0.349, 0.512, 1.01, 1.44, 1.67, 4.1, 1.11, 1.31, 0.965, 1.87, 1.3, 3,
+    {"t64x128", 64, 128, 2, 0.349, 0.512, 1.12, 1.86, 1.67, 1.11, 1.31, 0.884, 1.87, 1.3, 3,
      GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15},
-    {"t128x64", 128, 64, 2, 0.371, 0.617, 0.998, 1.62, 1.33, 4.07, 1.06, 1.31, 0.822, 1.84, 1.3, 3,
+    {"t128x64", 128, 64, 2, 0.371, 0.617, 1.14, 1.81, 1.33, 1.06, 1.31, 0.919, 1.84, 1.3, 3,
      GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15},
     // K split across the four waves of the workgroup (Section 5.3, small sizes); fitted on 16-byte aligned operands only
-    {"k64x64", 64, 64, 4, 0.311, 0.854, 0.541, 2.06, 2.02, 3.54, 0.781, 1.07, 0.849, 1.65, 1.0, 1,
+    {"k64x64", 64, 64, 4, 0.311, 0.854, 0.598, 2.02, 2.02, 0.781, 1.07, 0.992, 1.65, 1.0, 1,
      launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
@@ -253,7 +251,7 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     const double foot_factor = foot <= kFootLo ? kFootFactor
                                : (foot >= kFootHi ? 1.0 : exp(log(kFootFactor) * (log(kFootHi) - log(foot)) / (log(kFootHi) - log(kFootLo))));
     // slabs' worth of extra time for the guarded last slab of a ragged K
-    double tail = f32 ? (path == 3 ? 0.681 : 0.0) : (path == 3 ? 2.8 : 2.32);
+    double tail = f32 ? (path == 3 ? 3.23 : 1.27) : (path == 3 ? 2.8 : 2.32);
     if (path == 3) slab *= f32 ? t.f32_a4 : t.f16_a4 * kLayA4[k_contig];
     if (path == 1 || path == 2) slab *= f32 ? 1.05 : (path == 2 ? t.f16_a2 * kLayA2[k_contig] : t.general);
     slab *= foot_factor;
@@ -266,7 +264,7 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
         if (!f32) tail = 4.58;
     }
     slab *= scale[GEMM_COST_SLAB];
-    double t_mfma = rounds * ((double)per * slab + (f32 ? t.fixed32 : t.fixed));
+    double t_mfma = rounds * ((double)per * slab + t.fixed);
     if (K % (f32 ? 32 : 64) != 0) t_mfma += tail * slab;
     const double unique = ((double)M * K + (double)K * N) * esz + (double)M * N * 4.0;
     const double resident = (double)W < slots ? (double)W : slots;
@@ -316,18 +314,10 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
         if (g_forced_tile >= 0 && t != g_forced_tile) continue;
         if (g_forced_tile < 0 && kTiles[t].fallback >= 0 && !ksplit_ok) continue;
         if (g_forced_tile < 0 && !(((f32 ? kTiles[t].auto32 : kTiles[t].auto16) >> path) & 1)) continue;
-        // (the larger binary32 tiles multiply short sums in a general, unpipelined way: see kSplitMinK)
-        if (g_forced_tile < 0 && f32 && K < kSplitMinK && kTiles[t].BM * kTiles[t].BN > 64 * 64) continue;
         for (int s = 1; s <= 32; s *= 2) {
             const int cand = forced > 0 ? forced : s;
             if (cand > 1 && cand > KT) break;
             if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
-            // Sums of more than 4096 terms are cut into slices of at most kSplitMaxK per accumulator on the split kernels:
-            // the small tiles of the binary32 instructions cut long sums to fill the chip, and the error of a sum grows
-            // with the square root of its terms (659x906x61365: 7.9e-7 in 32 slices there, 1.25e-6 in 16 here).  Results of
-            // more than 2^21 entries fill the chip in one slice on any tile, and partial sums of that size are not worth it.
-            if (forced == 0 && f32 && K > 4096 && M * N <= (1 << 21) && kTiles[t].BM * kTiles[t].BN > 64 * 64 && cand < 32 && 2 * cand <= KT &&
-                cdiv(K, cand) > kSplitMaxK * f32_wave_groups(kTiles[t].BM, kTiles[t].BN)) continue;
             const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu);
             if (c < best) { best = c; tile = t; splits = cand; }
             if (forced > 0) break;

@@ -1,13 +1,11 @@
 // Host-side launcher shared by the per-tile instantiation files: maps the
 // run-time (layout, alignment) choice onto the kernel template's booleans.
 #pragma once
-#include "gemm_f32_kernel.h"
 #include "gemm_kernel.h"
 #include "gemm_ksplit_kernel.h"
 #include "gemm_small_kernel.h"
 
 #include <tuple>
-#include <type_traits>
 #include <utility>
 
 namespace gemm_gfx950 {
@@ -34,17 +32,8 @@ template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC>
 static hipError_t launch_aligned(bool aligned, dim3 grid, hipStream_t s, const KernelArgs &a)
 {
     const dim3 block(WM * WN * 64);
-    if constexpr (std::is_same<T, float>::value && BM * BN > 64 * 64) {
-        // binary32 on the bfloat16 matrix instructions, one kernel for every alignment.  The 64x64 tiles stay with the
-        // binary32 instructions: they would split as many elements as they multiply (256^3 6.9 us there, 8.7 split)
-        constexpr int WNF = BM * BN == 256 * 256 ? 4 : WN;  // 256x256: eight waves, 577 us against 615 with four (4096^3)
-        return launch_kernel(gemm_f32_kernel<BM, BN, WM, WNF, AKC, BKC>, grid,
-                             dim3(WM * WNF * f32_wave_groups(BM, BN) * 64), s, a);
-    } else if (aligned) {
-        return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, true>, grid, block, s, a);
-    } else {
-        return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, false>, grid, block, s, a);
-    }
+    if (aligned) return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, true>, grid, block, s, a);
+    return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, false>, grid, block, s, a);
 }
 
 // akc: A is K-contiguous (row-major); bkc: B is K-contiguous (column-major)

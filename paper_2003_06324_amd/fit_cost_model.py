@@ -39,13 +39,12 @@ K_CONTIG = {"NN": 1, "NT": 2, "TN": 0, "TT": 1}     # how many of A, B have K as
 GLOBALS = dict(fixed=2.7, lat=0.85, hbm_cap=4.8e6, l2=22e6, red_fixed=1.5, red_rate=3.8e6, red_slice=0.087,
                foot_factor=0.29, foot_lo=2.2e5, foot_hi=1.5e7)
 GLOBAL_NAMES = list(GLOBALS)
-# starting points: (alone, full, fixed) per 64-k binary16 slab, the same per 32-k binary32 slab
+# starting points: (alone, full, fixed) per 64-k binary16 slab, (alone, full) per 32-k binary32 slab
 START16 = {"t256x256": (1.1, 1.1, 5.0), "t128x128": (0.5, 0.85, 1.5), "t64x64": (0.28, 0.72, 1.2), "t256x256w8": (1.15, 1.15, 3.4),
            "t256x128": (0.8, 0.8, 3.0), "t128x256": (0.73, 0.73, 3.1), "t64x128": (0.36, 0.59, 1.4), "t128x64": (0.37, 0.6, 1.3),
            "k64x64": (0.29, 0.71, 2.3)}
-START32 = {"t256x256": (3.5, 3.5, 12.0), "t128x128": (1.1, 2.5, 8.7), "t64x64": (0.5, 1.9, 2.9), "t256x256w8": (3.5, 3.5, 12.0),
-           "t256x128": (2.3, 2.3, 8.9), "t128x256": (2.35, 2.35, 8.1), "t64x128": (1.0, 1.45, 4.1), "t128x64": (1.0, 1.6, 4.1),
-           "k64x64": (0.54, 2.1, 3.5)}
+START32 = {"t256x256": (7.5, 7.5), "t128x128": (1.9, 3.3), "t64x64": (0.48, 1.7), "t256x256w8": (7.0, 7.0), "t256x128": (3.6, 3.6),
+           "t128x256": (3.4, 3.4), "t64x128": (0.89, 1.7), "t128x64": (0.97, 1.65), "k64x64": (0.55, 1.8)}
 PERTURBED = [tuple(f if i == j else 1.0 for i in range(4)) for j in range(4) for f in (0.88, 1.12)]
 
 
@@ -235,14 +234,13 @@ def main():
     T16, G, tail16 = unpack16(fit_stage(x0, make16, select("f16", 0, rand), select("f16", 0, paper), select("f16", 0, tuned), iters,
                                         5.0, "f16 aligned"))
 
-    # binary32, aligned: slab times, fixed part and tail (HBM efficiency and globals as fitted above)
+    # binary32, aligned: slab times and tail only (fixed part, HBM efficiency and globals as fitted above)
     def unpack32(x):
         T = {}
         for i, t in enumerate(NAMES):
-            a, f, fx = np.exp(x[3 * i:3 * i + 3])
-            T[t] = (a, max(a, f) if TILES[t][2] > 1 else a, fx, T16[t][3])
-        T["t256x256w8"] = T["t256x256"][:3] + (T16["t256x256w8"][3],)   # one kernel for both
-        return T, math.exp(x[27])
+            a, f = np.exp(x[2 * i:2 * i + 2])
+            T[t] = (a, max(a, f) if TILES[t][2] > 1 else a, T16[t][2], T16[t][3])
+        return T, math.exp(x[18])
 
     def make32(x):
         T, tail = unpack32(x)
@@ -272,12 +270,12 @@ def main():
                                              "%s path %d" % (dt, path)))
 
     print("\nglobal terms:", {k: float("%.3g" % v) for k, v in G.items()}, "ragged-K tail f16 %.3g f32 %.3g" % (tail16, tail32))
-    print("tile: f16_alone, f16_full, f32_alone, f32_full, fixed, fixed32, hbm_eff, f16_a4, f32_a4, f16_a2")
+    print("tile: f16_alone, f16_full, f32_alone, f32_full, fixed, hbm_eff, f16_a4, f32_a4, f16_a2")
     for t in NAMES:
         a4 = classes["f16", 3][0].get(t, classes["f16", 3][0]["t64x64"])
         b4 = classes["f32", 3][0].get(t, classes["f32", 3][0]["t64x64"])
         a2 = classes["f16", 2][0].get(t, classes["f16", 2][0]["t64x64"])
-        print("  %-11s" % t + ", ".join("%.3g" % v for v in (T16[t][0], T16[t][1], T32[t][0], T32[t][1], T16[t][2], T32[t][2], T16[t][3], a4, b4, a2)))
+        print("  %-11s" % t + ", ".join("%.3g" % v for v in (T16[t][0], T16[t][1], T32[t][0], T32[t][1], T16[t][2], T16[t][3], a4, b4, a2)))
     for (dt, path), (_, lay, tail) in classes.items():
         print("%s path %d: factor by K-contiguous operands (0, 1, 2) %s, ragged-K tail %.3g" % (
             dt, path, ["%.3g" % v for v in lay], tail))

@@ -229,6 +229,19 @@ def test_forced_slice_count_beyond_the_slab_count_still_costs_every_tile():
         g.force_config(None)
 
 
+def test_binary32_products_that_fill_the_chip_take_one_slice():
+    """These need no K-slice workspace (so a first call can be captured), keep the larger tiles' pipelined kernels for
+    short sums, and a sum is not longer per accumulator than the selection for the binary32 instructions has it."""
+    import paper_2003_06324_amd as g
+    g.force_config(None)
+    q = g.query_config
+    for M, N, K in ((1024, 1024, 2048), (1024, 1024, 3072), (1280, 1280, 1280), (3072, 2560, 2560), (2816, 2816, 4096)):
+        assert q(4, M, N, K, 16, g.ROW_MAJOR, g.COL_MAJOR).split(":")[1] == "s1", (M, N, K)
+    for M, N, K in ((8192, 8192, 32), (20000, 20000, 32), (4096, 4096, 63)):
+        assert q(4, M, N, K, 16, g.ROW_MAJOR, g.COL_MAJOR).split(":")[0] == "t128x128", (M, N, K)
+    assert q(4, 3933, 3365, 3756, 16, g.ROW_MAJOR, g.COL_MAJOR) == "t128x64:s4"
+
+
 def test_force_config_suffixes():
     import paper_2003_06324_amd as g
     try:

@@ -9,7 +9,7 @@ from gpu_util import all_tiles, run_gpu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,tiles", [("f16", all_tiles()), ("bf16", ("t64x64", "t256x256w8")), ("f32", ("t64x64",))])
+@pytest.mark.parametrize("dtype,tiles", [("f16", all_tiles()), ("bf16", ("t64x64", "t256x256w8")), ("f32", all_tiles())])
 @pytest.mark.parametrize("left", range(1, 9))
 def test_every_number_of_elements_at_the_edge(oracle, dtype, tiles, left):
     # extents left, granule + left and a few slabs + left; rows 2-, 4- and 16-byte aligned
