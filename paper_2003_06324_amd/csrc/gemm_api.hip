@@ -293,6 +293,13 @@ bool serves_small(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_con
     return K <= (f32 ? 512 : (path == 2 && k_contig > 0 ? 256 : 768));
 }
 
+// What can be forced, or traced, are the tile kernels: with any such setting the small kernel stays out, whether the
+// rule above, a recorded pick or gemm_tune would run it (g_mutex held).
+bool small_allowed()
+{
+    return g_forced_tile < 0 && g_forced_splits == 0 && !g_forced_safe && !g_force_regload && g_store_mode == 0 && g_trace == nullptr;
+}
+
 // max_ws_bytes: largest K-slice workspace the caller can provide (0 = no limit); automatic
 // picks that would need more are not considered.
 // ksplit_ok: the operands qualify for the kernels that split K across the waves of a workgroup
@@ -302,9 +309,7 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
     double best = 1e300;
     tile = g_forced_tile >= 0 ? g_forced_tile : 0;
     splits = 1;
-    // (what can be forced, or traced, are the tile kernels)
-    if (g_forced_tile < 0 && g_forced_splits == 0 && !g_forced_safe && !g_force_regload && g_store_mode == 0 && g_trace == nullptr &&
-        serves_small(M, N, K, f32, path, k_contig, num_cu)) {
+    if (small_allowed() && serves_small(M, N, K, f32, path, k_contig, num_cu)) {
         tile = kSmall;
         return;
     }
@@ -365,7 +370,7 @@ void choose(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int path, int
                        (uint64_t)K * 0x165667B19E3779F9ull ^ (uint64_t)(k_contig * 16 + path * 4 + f32 * 2 + ksplit_ok);
     if (g_forced_tile < 0 && g_forced_splits == 0 && !g_tuned.empty()) {
         const auto it = g_tuned.find(ShapeKey{M, N, K, (int)f32, path, k_contig, num_cu, (int)ksplit_ok});
-        if (it != g_tuned.end() && (max_ws_bytes == 0 || it->second.second == 1 ||
+        if (it != g_tuned.end() && (it->second.first != kSmall || small_allowed()) && (max_ws_bytes == 0 || it->second.second == 1 ||
                                     ws_bytes(it->second.second, M, N) <= max_ws_bytes)) {
             tile = it->second.first;
             splits = it->second.second;
@@ -656,7 +661,7 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     std::vector<std::tuple<double, int, int>> cand;
     {
         std::lock_guard<std::mutex> lock(g_mutex);
-        if (serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
+        if (small_allowed() && serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
         for (int t = 0; t < kNumTiles; ++t) {
             if (kTiles[t].fallback >= 0 && !key.ksplit_ok) continue;
             for (int s = 1; s <= 32 && (s == 1 || s <= KT); s *= 2)

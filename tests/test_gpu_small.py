@@ -43,3 +43,32 @@ def test_the_limits_of_the_choice(oracle, dtype, limit):
         C, cfg = run_gpu(dtype, A, B, 0, 1, return_config=True)
         assert cfg.endswith(" small") == small, (M, N, K, cfg)
         check(C, _ref(oracle, A, B, dtype), A, B, dtype, cfg)
+
+
+def test_a_recorded_pick_of_the_kernel_gives_way_to_the_tile_kernels(oracle, tmp_path):
+    """What asks for a tile kernel -- the synchronised variant, register-staged loads, a way to store C, the phase
+    trace -- gets one, also where a recorded pick names the kernel for small products."""
+    import torch
+    import paper_2003_06324_amd as g
+    M, N, K = 96, 64, 128
+    A, B = gi.make_problem(1500, M, N, K, "int", "f32")
+    ref = oracle.gemm(M, N, K, A, 0, B, 0, "f32")
+    g.force_config(None)
+    g.tune_clear()
+    picks = tmp_path / "picks.txt"
+    picks.write_text("4 96 64 128 0 2 256 1 t64x64 1 small\n4 96 64 128 1 2 256 0 t64x64 1 small\n")
+    trace = torch.zeros(8 * 64, dtype=torch.int64, device="cuda")
+    try:
+        g.tune_load(picks)
+        assert run_gpu("f32", A, B, 0, 1, return_config=True)[1].endswith(" small")
+        for how in ("auto:safe", "auto:regload", "auto:direct", "auto:staged"):
+            C, cfg = run_gpu("f32", A, B, 0, 1, force=how, return_config=True)
+            assert " small" not in cfg and np.array_equal(C.astype(np.float64), ref), (how, cfg)
+        g.set_phase_trace(trace, 64)
+        C, cfg = run_gpu("f32", A, B, 0, 1, return_config=True)
+        g.set_phase_trace(None)
+        assert " small" not in cfg and np.array_equal(C.astype(np.float64), ref), cfg
+        assert int(trace[0]) != 0 and int(trace[5]) >= int(trace[0])
+    finally:
+        g.set_phase_trace(None)
+        g.tune_clear()
