@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import gemm_inputs as gi
-from gpu_util import run_gpu
+from gpu_util import all_tiles, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -37,6 +37,23 @@ def test_subnormals_are_not_flushed(oracle, case):
     for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
         C = run_gpu(dtype, A, B, la, lb)
         assert np.array_equal(C.astype(np.float64), ref), (case, la, lb)
+
+
+@pytest.mark.parametrize("tile", all_tiles())
+def test_subnormals_are_not_flushed_by_the_tile_kernels(oracle, tile):
+    # (unforced, a product of this size runs the kernel for small products)
+    for dtype, a, b, npdt in (("f16", 2.0 ** -24, 1024.0, np.float16), ("f16", 3 * 2.0 ** -24, 5 * 2.0 ** -24, np.float16),
+                              ("f32", 2.0 ** -130, 4.0, np.float32), ("f32", 2.0 ** -106, 1.0, np.float32),
+                              ("f32", 2.0 ** -70, 2.0 ** -70, np.float32), ("bf16", 2.0 ** -130, 2.0 ** 20, np.float32)):
+        rng = np.random.default_rng(3)
+        A = (rng.integers(1, 4, size=(70, 96)) * a).astype(npdt)
+        B = (rng.integers(-3, 4, size=(96, 66)) * b).astype(npdt)
+        ref = oracle_c(oracle, A, B, dtype)
+        assert np.any(ref != 0) and np.array_equal(ref.astype(np.float32).astype(np.float64), ref)
+        for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+            C, cfg = run_gpu(dtype, A, B, la, lb, force=tile, return_config=True)
+            assert " small" not in cfg
+            assert np.array_equal(C.astype(np.float64), ref), (dtype, a, b, cfg)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "f32", "bf16"])
