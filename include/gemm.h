@@ -220,7 +220,8 @@ int gemm_tune_clear(void);
  * granules, tile name, K slices, and "small" where the kernel for small products runs; '#' starts a comment
  * line); gemm_tune_load adds the pairs of such a file to the table, replacing entries for the same class.  Host only.  GEMM_ERR_INVALID_ARG if the file cannot be
  * opened or written, or (load) if any line does not parse, names a tile this build does not have or one
- * that cannot serve the line's class, or a K-slice count outside 1 .. 32 (what gemm_tune records): then
+ * that cannot serve the line's class (the kernel for small products included), a K-slice count outside 1 .. 32
+ * (what gemm_tune records), or has another word than "small" or a '#' comment behind it: then
  * nothing of the file is taken over.
  */
 int gemm_tune_save(const char *path);

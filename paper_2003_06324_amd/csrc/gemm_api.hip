@@ -847,9 +847,9 @@ int gemm_tune_load(const char *path)
         if (line[0] == '#' || line[0] == '\n' || line[0] == 0) continue;
         long long M, N, K;
         int esz, path_, kc, cus, whole, slices;
-        char name[32], kernel[32] = "";
-        if (sscanf(line, "%d %lld %lld %lld %d %d %d %d %31s %d %31s", &esz, &M, &N, &K, &path_, &kc, &cus, &whole, name, &slices,
-                   kernel) < 10 ||
+        int end = 0;
+        char name[32], kernel[8] = "", more[2] = "";
+        if (sscanf(line, "%d %lld %lld %lld %d %d %d %d %31s %d%n", &esz, &M, &N, &K, &path_, &kc, &cus, &whole, name, &slices, &end) != 10 ||
             (esz != 2 && esz != 4) || M <= 0 || N <= 0 || K <= 0 || path_ < 0 || path_ > 3 || kc < 0 || kc > 2 || cus <= 0 ||
             (whole != 0 && whole != 1) || slices < 1 || slices > 32) {   // gemm_tune records 1 .. 32 slices
             rc = GEMM_ERR_INVALID_ARG;
@@ -858,8 +858,13 @@ int gemm_tune_load(const char *path)
         int tile = -1;
         for (int i = 0; i < kNumTiles; ++i)
             if (strcmp(name, kTiles[i].name) == 0) tile = i;
-        // the small kernel, where it serves the size
-        if (strcmp(kernel, "small") == 0 && tile == kSmallAs && slices == 1 && serves_small(M, N, K, esz == 4, path_, kc, cus)) tile = kSmall;
+        // behind the slices: nothing, a comment, or the word for the small kernel, which then has to serve the class
+        const int words = sscanf(line + end, "%7s %1s", kernel, more);
+        if (words > 0 && kernel[0] != '#') {
+            const bool ok = strcmp(kernel, "small") == 0 && (words == 1 || more[0] == '#') && tile == kSmallAs && slices == 1 &&
+                            serves_small(M, N, K, esz == 4, path_, kc, cus);
+            tile = ok ? kSmall : -1;
+        }
         // a tile this build does not have, or one that does not serve the class, makes the file invalid as a whole
         if (tile < 0 || (tile_of(tile).fallback >= 0 && !whole)) {
             rc = GEMM_ERR_INVALID_ARG;

@@ -169,6 +169,33 @@ def test_recorded_picks_load_from_a_file_and_precede_the_cost_model(tmp_path):
         g.tune_clear()
 
 
+def test_the_word_behind_a_recorded_pick(tmp_path):
+    """Behind the slice count a line may say "small" where the kernel for small products serves the class; any other
+    word, or that one on another tile, slice count or size, is refused with the whole file."""
+    import paper_2003_06324_amd as g
+    g.force_config(None)
+    g.tune_clear()
+    f, out = tmp_path / "picks.txt", tmp_path / "saved.txt"
+    good = "2 512 512 512 0 2 256 1 t128x64 2\n"
+    try:
+        for text in ("4 64 64 64 0 2 256 1 t64x64 1 smal\n", "4 64 64 64 0 2 256 1 t64x64 1 small2\n", "4 64 64 64 0 2 256 1 t64x64 1 x\n",
+                     "4 64 64 64 0 2 256 1 t64x64 1x\n", "4 64 64 64 0 2 256 1 t64x64 1 small small\n",
+                     "4 64 64 64 0 2 256 1 t128x128 1 small\n", "4 64 64 64 0 2 256 1 t64x64 2 small\n",
+                     "4 64 64 1024 0 2 256 1 t64x64 1 small\n", "2 2048 2048 64 0 2 256 1 t64x64 1 small\n",
+                     "2 64 64 512 2 2 256 0 t64x64 1 small\n"):
+            f.write_text(good + text)
+            assert g.tune_load(f, check=False) == -1, text
+            g.tune_save(out)
+            assert [ln for ln in out.read_text().split("\n") if ln and not ln.startswith("#")] == [], text
+        lines = ["2 512 512 512 0 2 256 1 t128x64 2", "4 64 64 64 0 2 256 1 t64x64 1 small", "4 64 64 96 0 2 256 1 t64x64 1"]
+        f.write_text(lines[0] + "  # measured twice\n" + lines[1] + " \n" + lines[2] + "\n")
+        g.tune_load(f)
+        g.tune_save(out)
+        assert sorted(ln for ln in out.read_text().split("\n") if ln and not ln.startswith("#")) == sorted(lines)
+    finally:
+        g.tune_clear()
+
+
 def test_shipped_table_of_measured_picks_loads():
     """tuned_mi355x.txt (gemm_tune over the paper's size ranges, Section 5.3) parses, names only configurations this
     build has, covers every size triple, layout class and operand type, and answers queries once loaded."""
