@@ -190,7 +190,8 @@ int gemm_cost_model_scale(int term, double factor);
  * call performs it).  kind names the entry point (GEMM_KIND_*), the other arguments are that entry
  * point's: the call computes C = A * B like it, then runs the product again with each candidate
  * (tile, K slices) pair -- the max_candidates cheapest by the cost model, or every pair the library
- * has if max_candidates is 0 (9 tiles x up to 6 slice counts; 10-50 ms for a mid-size shape, 1.3 s at 8192^3) --
+ * has if max_candidates is 0 (9 tiles x up to 6 slice counts, and before them, where the selection uses it, the kernel
+ * for small products, written as "t64x64:s1"; 10-50 ms for a mid-size shape, 1.3 s at 8192^3) --
  * timing each with events on hip_stream (two untimed and six timed launches per pair behind 40 untimed ones, all
  * enqueued back to back; then the four fastest and the cost model's own pick again, twice in turn with 24 timed
  * launches each, the better take of each kept), records the fastest in a process-wide table, computes C
@@ -235,7 +236,10 @@ int gemm_tune_load(const char *path);
  * straddle cache lines, 2 the register-staged kernels on operands whose 16-byte loads the
  * memory pipeline has to split, 0 ("no") the register-staged kernels for another reason (a
  * leading dimension too long for 32-bit tile offsets, a forced ":regload").  Writes "<tile>:s<splits>"
- * into buf (NUL-terminated, truncated to buflen).
+ * into buf (NUL-terminated, truncated to buflen).  Products of at most one 32x32 block of C per CU and a short K
+ * (512 for binary32, 768 for 16-bit operands, 256 for K-contiguous 16-bit rows on 2-byte boundaries) run a kernel
+ * of their own in one slice, which has no name: it answers "t64x64:s1", gemm_last_config says "small", and it
+ * runs only while nothing is forced or traced (forcing "t64x64:s1" runs the tile kernel of that name).
  * This is the host side of the per-size tuning of Section 5.3, exposed so that it can be
  * tested without a GPU.
  */
@@ -270,7 +274,7 @@ const char *gemm_config_name(int i);
 /*
  * Description of the configuration the last successful call on this thread
  * used, e.g. "f16 t256x256 NT aligned s1"; " small" at the end: the kernel for
- * small products ran, which the selection counts as the smallest tile in one slice.  The string is thread-local storage
+ * small products ran (see gemm_query_config).  The string is thread-local storage
  * owned by the library, valid until the thread's next gemm call.
  */
 const char *gemm_last_config(void);

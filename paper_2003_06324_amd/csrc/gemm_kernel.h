@@ -316,8 +316,9 @@ __device__ __forceinline__ uint4_t last_elements(const uint4_t &w, int n)
 // Granules that straddle the edge of the matrix hold the same number of elements, the extent modulo the granule.  With
 // two or more of them the granule is loaded as the last 16 bytes of its row, which hold those elements, and shifted
 // into place: one load, in flight with the others.  Fetched one after the other between the loads and the LDS stores
-// they kept a workgroup waiting for a memory round trip each (binary16 304x151x151 7.10 us, now 5.36; 540x1679x949
-// 10.6, now 9.2); rows shorter than a granule still are.
+// they kept a workgroup waiting for a memory round trip each (binary16 1023x1251x615 13.6 us, now 11.1; 3945x2199x183
+// 21.1, now 17.8; 71 products of odd sizes, microseconds before over now, 1.05 in the geometric mean, 0.97 at worst, where the
+// extent leaves one element); rows shorter than a granule still are.
 template <typename T> __device__ __forceinline__ bool edge_as_granule(int extent)
 {
     constexpr int EPC = Elem<T>::EPC;
