@@ -64,8 +64,15 @@ def main():
         torch.cuda.synchronize()
         return [e0.elapsed_time(e1) / iters * 1e3 for e0, e1 in pairs]
 
+    def config_to_force(ran):
+        """"<tile>:s<slices>" of a gemm_last_config text; None for the kernel for small products, which runs unforced only."""
+        f = ran.split()
+        return None if f[-1] == "small" else f[1] + ":" + f[4]
+
     g.force_config(None)
     g.tune_clear()
+    aside = out + ".part"
+    recorded = []
     ratios = {"f16": [], "f32": []}
     changed = 0
     if listed is None:
@@ -87,10 +94,16 @@ def main():
                 la, lb = gi.LAYOUTS[lay]
                 fn = lambda: call(M, N, K, A, la, 0, B, lb, 0, C, gi.ROW_MAJOR, 0, stream)
                 fn()
-                model = g.last_config().split()
-                model = model[1] + ":" + model[4]
-                pick = g.tune(kind, M, N, K, A, la, 0, B, lb, 0, C, gi.ROW_MAJOR, 0, stream)
-                # both picks forced alternately in one pass, the better take of each
+                model = config_to_force(g.last_config())
+                g.tune(kind, M, N, K, A, la, 0, B, lb, 0, C, gi.ROW_MAJOR, 0, stream)
+                fn()
+                pick = config_to_force(g.last_config())
+                # the pick is put aside, so that "unforced" is the model's choice while both are timed
+                g.tune_save(aside)
+                with open(aside) as f:
+                    recorded += [line for line in f if not line.startswith("#")]
+                g.tune_clear()
+                # both picks alternately in one pass, the better take of each
                 takes = timed(fn, [model, pick, model, pick], iters)
                 t_model, t_tuned = min(takes[0::2]), min(takes[1::2])
                 if pick == model:
@@ -99,7 +112,12 @@ def main():
                     changed += 1
                 ratios[dt].append(t_model / t_tuned)
                 print("%s %dx%dx%d %s%s: model %s %.1f us | tuned %s %.1f us | model/tuned %.2f" % (
-                    dt, M, N, K, lay, " +%dB" % off if off else "", model, t_model, pick, t_tuned, t_model / t_tuned), flush=True)
+                    dt, M, N, K, lay, " +%dB" % off if off else "", model or "small", t_model, pick or "small", t_tuned,
+                    t_model / t_tuned), flush=True)
+    with open(aside, "w") as f:
+        f.writelines(recorded)
+    g.tune_load(aside)
+    os.remove(aside)
     g.tune_save(out)
     for dt, r in ratios.items():
         if not r:
