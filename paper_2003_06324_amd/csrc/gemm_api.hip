@@ -47,6 +47,14 @@ GEMM_DECLARE_TILE(float, 64, 128, 2, 2)
 GEMM_DECLARE_KSPLIT(_Float16, 64, 64)
 GEMM_DECLARE_KSPLIT(__bf16, 64, 64)
 GEMM_DECLARE_KSPLIT(float, 64, 64)
+GEMM_DECLARE_STAGE(_Float16, 64, 64, 6)
+GEMM_DECLARE_STAGE(_Float16, 64, 128, 5)
+GEMM_DECLARE_STAGE(_Float16, 128, 64, 5)
+GEMM_DECLARE_STAGE(_Float16, 128, 128, 4)
+GEMM_DECLARE_STAGE(__bf16, 64, 64, 6)
+GEMM_DECLARE_STAGE(__bf16, 64, 128, 5)
+GEMM_DECLARE_STAGE(__bf16, 128, 64, 5)
+GEMM_DECLARE_STAGE(__bf16, 128, 128, 4)
 GEMM_DECLARE_SMALL(_Float16)
 GEMM_DECLARE_SMALL(__bf16)
 GEMM_DECLARE_SMALL(float)
@@ -142,10 +150,14 @@ struct TileConfig {
                                 // 2-byte aligned operands, bit 3: direct loads on 4-/8-byte aligned operands) for
                                 // which the automatic selection considers this configuration, for 16-bit and for
                                 // binary32 operands; 0: only when forced
+    launch_fn stage16, stage_bf16;  // gemm_stage_kernel (null: none), see runs_stage
+    double stage_slab, stage_a4;    // its slab time (microseconds per 64 k, one workgroup on a CU), on 4-/8-byte aligned operands over that
+    int stage_from;                 // slabs from which it is ahead on whole ones
 };
 
 #define GEMM_TILE_LAUNCHERS(BM, BN, WM, WN) \
     launch_tile<_Float16, BM, BN, WM, WN>, launch_tile<float, BM, BN, WM, WN>, launch_tile<__bf16, BM, BN, WM, WN>
+#define GEMM_STAGE_LAUNCHERS(BM, BN, NST) launch_stage<_Float16, BM, BN, NST>, launch_stage<__bf16, BM, BN, NST>
 // The constants of this table and of estimate_cost are fitted, not derived: every configuration
 // at 1..32 K slices was timed on MI355X with random operands (so at the ~1.5 GHz the part
 // throttles to under sustained MFMA load) on the benchmark shapes and on 425 random shapes
@@ -157,24 +169,24 @@ struct TileConfig {
 // (64x128 before 128x64: the model often ties the two, and the tie goes to the first; 64x128 measures 4-8 % ahead)
 const TileConfig kTiles[] = {
     {"t256x256", 256, 256, 1, 1.02, 1.02, 6.98, 6.98, 7.2, 0.83, 1.2, 1.05, 1.67, 1.25, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t128x128", 128, 128, 2, 0.457, 0.868, 1.99, 3.64, 1.92, 1.39, 1.23, 0.817, 1.57, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.40, 1.40, 24},
     {"t64x64", 64, 64, 4, 0.265, 0.855, 0.495, 1.86, 1.27, 0.78, 1.07, 0.992, 1.65, 1.35, 4,
-     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.187, 1.48, 16},
     {"t256x256w8", 256, 256, 1, 1.05, 1.05, 7.6, 7.6, 6.02, 0.812, 1.2, 0.915, 1.35, 1.15, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t256x128", 256, 128, 1, 0.71, 0.71, 3.52, 3.52, 3.82, 0.637, 1.2, 1.09, 1.47, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t128x256", 128, 256, 1, 0.661, 0.661, 4.19, 4.19, 4.17, 1.78, 1.25, 0.864, 2.03, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t64x128", 64, 128, 2, 0.349, 0.512, 1.12, 1.86, 1.67, 1.11, 1.31, 0.884, 1.87, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.255, 1.60, 16},
     {"t128x64", 128, 64, 2, 0.371, 0.617, 1.14, 1.81, 1.33, 1.06, 1.31, 0.919, 1.84, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15},
+     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.28, 1.6, 16},
     // K split across the four waves of the workgroup (Section 5.3, small sizes); fitted on 16-byte aligned operands only
     {"k64x64", 64, 64, 4, 0.311, 0.854, 0.598, 2.02, 2.02, 0.781, 1.07, 0.992, 1.65, 1.0, 1,
-     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1},
+     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, 0.0, 0.0, 0},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -216,6 +228,17 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int64_t ws_pitch(int64_t N) { return cdiv(N, 32) * 32; }
 size_t ws_bytes(int64_t splits, int64_t M, int64_t N) { return (size_t)splits * (size_t)M * (size_t)ws_pitch(N) * sizeof(float); }
 
+// Whether a launch on direct loads (16-bit operands, load path 0 or 3) runs gemm_stage_kernel: at most one workgroup per CU,
+// and enough slabs to pay for its longer start, 0.5 us, or a last slab that gemm_tile_kernel leaves to its guarded loop
+// (ragged: K no multiple of the slab, or granules straddling the M/N edge of an operand).  Microseconds per launch back to
+// back, 96 and 240 workgroups of each tile, gemm_tile_kernel -> gemm_stage_kernel: K = 4096 26.2 -> 15.4 and 26.3 -> 16.2
+// (64x64), 26.9 -> 19.5 and 27.9 -> 22.5 (64x128), 31.2 -> 27.0 and 36.2 -> 35.0 (128x128); K = 1024 8.4 -> 6.6, 9.3 -> 8.1,
+// 10.9 -> 10.3; K = 512 4.4 -> 5.0, 5.3 -> 6.0, 7.2 -> 7.6; with a ragged K 72 .. 1544 1.03 .. 1.5 times as fast on all tiles.
+bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, bool ragged, int num_cu)
+{
+    return t.stage16 != nullptr && workgroups <= num_cu && (ragged || slabs >= t.stage_from);
+}
+
 // Estimated run time in microseconds of (tile, splits) on this shape.  Three floors: the
 // MFMA work as scheduled on 256 CUs (rounds of resident workgroups, slab time depending on
 // how many workgroups share a CU), HBM traffic for the unique bytes (limited by how many
@@ -255,6 +278,11 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     if (path == 3) slab *= f32 ? t.f32_a4 : t.f16_a4 * kLayA4[k_contig];
     if (path == 1 || path == 2) slab *= f32 ? 1.05 : (path == 2 ? t.f16_a2 * kLayA2[k_contig] : t.general);
     slab *= foot_factor;
+    // (its slab time hardly depends on where the operands come from; a ragged last slab is one more)
+    if (!f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K % 64 != 0, NUM_CU)) {
+        slab = t.stage_slab * (path == 3 ? t.stage_a4 : 1.0);
+        tail = 0.0;
+    }
     if (path == 1 || path == 2) {
         // the register-staged path keeps `depth` slabs in flight per workgroup: a slab cannot take
         // less than that share of a global-load round trip
@@ -617,7 +645,8 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         launch_rc = launch_small<T>(akc, bkc, dim3((unsigned)(a.tiles_m * a.tiles_n)), stream, a);
     } else {
         const dim3 grid((unsigned)(8 * cdiv(tiles_m * tiles_n * splits, 8)));
-        const launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
+        launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
+        if (!f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, ragged || K % BK != 0, num_cu)) fn = bf16 ? t.stage_bf16 : t.stage16;
         launch_rc = fn(akc, bkc, aligned, grid, stream, a);
     }
     if (launch_rc != hipSuccess) {

@@ -522,6 +522,245 @@ __device__ __forceinline__ void mma(float16_t &acc, const float4_t &a, const flo
 }
 
 // ---------------------------------------------------------------------------
+// Work item of this workgroup.  Workgroups are dealt round-robin to the 8 XCDs (each with its own L2): every XCD
+// gets one contiguous run of work items, K-slice by K-slice (the tiles of one slice share that
+// slice's A and B panels; the same tile in another slice shares nothing), and within a
+// slice tiles are ordered in bands of GM tile rows so that tiles running together share panels.
+// ---------------------------------------------------------------------------
+struct WorkItem { int slice, tile_m, tile_n; };
+__device__ __forceinline__ bool work_item(const KernelArgs &p, WorkItem &w)
+{
+    const int ntiles = p.tiles_m * p.tiles_n;
+    const int nwork = ntiles * p.splits;
+    const int per_xcd = (nwork + 7) >> 3;
+    const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (work >= nwork) return false;
+    w.slice = work / ntiles;
+    const int lin = work - w.slice * ntiles;
+    constexpr int GM = 8;
+    const int band = lin / (GM * p.tiles_n);
+    const int first_m = band * GM;
+    const int band_rows = (p.tiles_m - first_m) < GM ? (p.tiles_m - first_m) : GM;
+    const int in_band = lin - band * GM * p.tiles_n;
+    w.tile_m = first_m + in_band % band_rows;
+    w.tile_n = in_band / band_rows;
+    return true;
+}
+
+// ---------------------------------------------------------------------------
+// Stores the accumulators of a workgroup's tile; lds: the operand buffers, LDS_BYTES long, drained of loads by now.
+// ---------------------------------------------------------------------------
+template <int BM, int BN, int WM, int WN, int LDS_BYTES>
+__device__ __forceinline__ void store_tile(const KernelArgs &p, const float16_t (&acc)[BM / WM / 32][BN / WN / 32],
+                                           GEMM_LDS(char) *lds, int m0, int n0, int slice, int wave, int lane)
+{
+    constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
+    const int wm = wave / WN, wn = wave % WN;
+    // marks 4 and 5 of the profiling trace: all stores of this thread issued / complete
+    auto trace_stores = [&]() {
+        if (p.trace != nullptr) {
+            trace_mark(p, 4);
+            __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+            trace_mark(p, 5);
+        }
+    };
+    // epilogue: accumulator register r of lane l holds
+    //   row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its 32x32 block
+    float *C = p.C + (int64_t)slice * p.split_stride;
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass of hipcc does not know the buffer builtins
+    // Tiles that lie fully inside C, with rows of C on 16-byte boundaries (host flag): the store
+    // goes through LDS (the paper's epilogue via shared memory, Section 3.2 "Epilog" and
+    // Listing 5, with the operand buffers reused once they have drained), so that each lane
+    // writes 16 contiguous bytes of a row and a store instruction covers whole 128-byte lines:
+    // a quarter of the store instructions for binary32 C, an eighth for binary16 C.  Each wave
+    // stages its own sub-tile, one band of 32 rows at a time, in a private piece of LDS, as
+    // binary32 [32][TN + 8]: the 8 words of padding put the two rows a write instruction covers
+    // (four apart) into different halves of the 64 banks.  LDS operations of one wave execute in
+    // order, so the bands need no barrier between them.
+    if (p.stage_c && m0 + BM <= p.M && n0 + BN <= p.N) {
+        constexpr int SW = TN + 8;                 // staging row stride in words
+        constexpr int STAGE = 32 * SW * 4;         // bytes per wave
+        static_assert(NW * STAGE <= LDS_BYTES, "staging area does not fit the operand buffers");
+        __syncthreads();  // every wave has read its last operands, every direct load has landed
+        trace_mark(p, 3);
+        GEMM_LDS(float) *stage = (GEMM_LDS(float) *)(lds + wave * STAGE);
+        const int lrow = 4 * (lane >> 5), lcol = lane & 31;
+        const int esz = p.out16 ? 2 : 4;
+        const int ldcb = (int)p.ldc * esz;
+        char *cbase = p.out16 ? (char *)((_Float16 *)p.C + (int64_t)m0 * p.ldc + n0)
+                              : (char *)(C + (int64_t)m0 * p.ldc + n0);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)cbase, 0, 0x7fffffff, 0x00020000);
+        auto band = [&](auto out16_tag, auto policy) {
+            constexpr bool O16 = decltype(out16_tag)::value;
+            constexpr int POLICY = decltype(policy)::value;
+            constexpr int WPL = O16 ? 8 : 4;          // staged words per lane and store (16 bytes of C)
+            constexpr int LPR = TN / WPL;             // lanes per row
+            constexpr int RPI = 64 / LPR;             // rows per store instruction
+            static_assert(64 % LPR == 0 && 32 % RPI == 0, "wave tile width not supported by the staged store");
+            const int srow = lane / LPR, spiece = lane % LPR;
+            const int voff = (wm * TM + srow) * ldcb + (wn * TN) * (O16 ? 2 : 4) + spiece * 16;
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        stage[(8 * (r >> 2) + (r & 3) + lrow) * SW + j * 32 + lcol] = acc[i][j][r];
+#pragma unroll
+                for (int it = 0; it < 32 / RPI; ++it) {
+                    const GEMM_LDS(float) *src = stage + (it * RPI + srow) * SW + spiece * WPL;
+                    const int soff = (i * 32 + it * RPI) * ldcb;
+                    if constexpr (O16) {
+                        const float4_t lo = *(const GEMM_LDS(float4_t) *)src;
+                        const float4_t hi = *(const GEMM_LDS(float4_t) *)(src + 4);
+                        half8_t h;
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            h[x] = (_Float16)lo[x];
+                            h[4 + x] = (_Float16)hi[x];
+                        }
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, h), rsrc, voff, soff, POLICY);
+                    } else {
+                        const float4_t v = *(const GEMM_LDS(float4_t) *)src;
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), rsrc, voff, soff, POLICY);
+                    }
+                }
+            }
+        };
+        if (p.out16) band(std::true_type(), std::integral_constant<int, 0>());
+        else if (p.stream_c) band(std::false_type(), std::integral_constant<int, 2>());
+        else band(std::false_type(), std::integral_constant<int, 0>());
+        trace_stores();
+        return;
+    }
+#endif
+    trace_mark(p, 3);
+    if (p.out16) {
+        // binary16 result (never combined with K-slices: those reduce from binary32 partials)
+        _Float16 *Ch = (_Float16 *)p.C;
+#if defined(__HIP_DEVICE_COMPILE__)
+        if (p.ldc < (int64_t(1) << 20)) {
+            // same range-checked descriptor as the binary32 edge-tile stores below
+            const int ldc2 = (int)p.ldc * 2;
+            const int rows_valid = p.M - m0 < BM ? p.M - m0 : BM;
+            const __amdgpu_buffer_rsrc_t rsrc =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(Ch + (int64_t)m0 * p.ldc + n0), 0, rows_valid * ldc2, 0x00020000);
+            const int voff = (wm * TM + 4 * (lane >> 5)) * ldc2 + (wn * TN + (lane & 31)) * 2;
+            int voffj[FN];
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                voffj[j] = n0 + wn * TN + j * 32 + (lane & 31) < p.N ? voff + j * 64 : (int)0x80000000;
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int roff = (i * 32 + 8 * (r >> 2) + (r & 3)) * ldc2;
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        const _Float16 h = (_Float16)acc[i][j][r];
+                        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, h), rsrc, voffj[j] + roff, 0, 0);
+                    }
+                }
+            trace_stores();
+            return;
+        }
+#endif
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const int col = n0 + wn * TN + j * 32 + (lane & 31);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = m0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                    if (row < p.M && col < p.N) Ch[(int64_t)row * p.ldc + col] = (_Float16)acc[i][j][r];
+                }
+            }
+        }
+        trace_stores();
+        return;
+    }
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass of hipcc does not know the buffer builtins
+    // Tiles that lie fully inside C (and whose byte offsets fit 32 bits) store through a
+    // buffer descriptor based at the tile origin: the per-lane part of the address is one
+    // 32-bit register, the row (i, r) a scalar offset and the column block j an immediate,
+    // so a store costs an accumulator read, a scalar multiply shared by FN stores, and the
+    // store itself - no per-store 64-bit address arithmetic, compares or exec masking.
+    if (m0 + BM <= p.M && n0 + BN <= p.N && p.ldc < (int64_t(1) << 20)) {
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(C + (int64_t)m0 * p.ldc + n0), 0, 0x7fffffff, 0x00020000);
+        const int ldc4 = (int)p.ldc * 4;
+        const int voff = (wm * TM + 4 * (lane >> 5)) * ldc4 + (wn * TN + (lane & 31)) * 4;
+        // C is written once and never read here.  When every 128-byte piece a store instruction
+        // writes is a whole cache line (host flag) the stores carry the non-temporal hint, which
+        // keeps the result from displacing A and B panels in the L2 (8192^3: 1-6 % faster);
+        // on partial lines the hint costs 10 %, and K-slice partials are re-read at once.
+        auto store_all = [&](auto policy) {
+            constexpr int POLICY = decltype(policy)::value;  // cache-policy operand: bit 1 = nt
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int soff = (i * 32 + 8 * (r >> 2) + (r & 3)) * ldc4;
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        // through a scalar temporary: a bit cast applied directly to a vector
+                        // element expression reads element 0 with this compiler
+                        const float v = acc[i][j][r];
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc, voff + j * 128, soff, POLICY);
+                    }
+                }
+        };
+        if (p.stream_c) store_all(std::integral_constant<int, 2>());
+        else store_all(std::integral_constant<int, 0>());
+        trace_stores();
+        return;
+    }
+    // Edge tiles, same descriptor trick: the descriptor's range ends with the last valid row
+    // (out-of-range buffer stores are discarded by the hardware) and lanes whose column is
+    // past N get an offset that is out of range by itself.  The row offset goes into the
+    // vector offset here, because the range check does not look at the scalar offset.
+    if (p.ldc < (int64_t(1) << 20)) {
+        const int ldc4 = (int)p.ldc * 4;
+        const int rows_valid = p.M - m0 < BM ? p.M - m0 : BM;
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(C + (int64_t)m0 * p.ldc + n0), 0, rows_valid * ldc4, 0x00020000);
+        const int voff = (wm * TM + 4 * (lane >> 5)) * ldc4 + (wn * TN + (lane & 31)) * 4;
+        int voffj[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+            voffj[j] = n0 + wn * TN + j * 32 + (lane & 31) < p.N ? voff + j * 128 : (int)0x80000000;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int roff = (i * 32 + 8 * (r >> 2) + (r & 3)) * ldc4;
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const float v = acc[i][j][r];
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc, voffj[j] + roff, 0, 0);
+                }
+            }
+        trace_stores();
+        return;
+    }
+#endif
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const int col = n0 + wn * TN + j * 32 + (lane & 31);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = m0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                if (row < p.M && col < p.N) C[(int64_t)row * p.ldc + col] = acc[i][j][r];
+            }
+        }
+    }
+    trace_stores();
+}
+
+// ---------------------------------------------------------------------------
 // The kernel.  grid.x = 8 * ceil(tiles * K-slices / 8) workgroups.
 // ---------------------------------------------------------------------------
 template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool ALIGNED>
@@ -547,27 +786,12 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
 
-    // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2): give every XCD
-    // one contiguous run of work items, K-slice by K-slice (the tiles of one slice share that
-    // slice's A and B panels; the same tile in another slice shares nothing), and within a
-    // slice order tiles in bands of GM tile rows so that tiles running together share panels.
-    const int ntiles = p.tiles_m * p.tiles_n;
-    const int nwork = ntiles * p.splits;
-    const int per_xcd = (nwork + 7) >> 3;
-    const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (work >= nwork) return;
+    WorkItem item;
+    if (!work_item(p, item)) return;
     trace_mark(p, 0);
     trace_place(p);
-    const int slice = work / ntiles;
-    const int lin = work - slice * ntiles;
-    constexpr int GM = 8;
-    const int band = lin / (GM * p.tiles_n);
-    const int first_m = band * GM;
-    const int band_rows = (p.tiles_m - first_m) < GM ? (p.tiles_m - first_m) : GM;
-    const int in_band = lin - band * GM * p.tiles_n;
-    const int tile_m = first_m + in_band % band_rows;
-    const int tile_n = in_band / band_rows;
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    const int slice = item.slice;
+    const int m0 = item.tile_m * BM, n0 = item.tile_n * BN;
 
     // K range of this slice
     const int KT = (p.K + BK - 1) / BK;
@@ -984,208 +1208,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     }
 
     trace_mark(p, 2);
-    // marks 4 and 5 of the profiling trace: all stores of this thread issued / complete
-    auto trace_stores = [&]() {
-        if (p.trace != nullptr) {
-            trace_mark(p, 4);
-            __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-            trace_mark(p, 5);
-        }
-    };
-    // epilogue: accumulator register r of lane l holds
-    //   row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its 32x32 block
-    float *C = p.C + (int64_t)slice * p.split_stride;
-#if defined(__HIP_DEVICE_COMPILE__)  // the host pass of hipcc does not know the buffer builtins
-    // Tiles that lie fully inside C, with rows of C on 16-byte boundaries (host flag): the store
-    // goes through LDS (the paper's epilogue via shared memory, Section 3.2 "Epilog" and
-    // Listing 5, with the operand buffers reused once they have drained), so that each lane
-    // writes 16 contiguous bytes of a row and a store instruction covers whole 128-byte lines:
-    // a quarter of the store instructions for binary32 C, an eighth for binary16 C.  Each wave
-    // stages its own sub-tile, one band of 32 rows at a time, in a private piece of LDS, as
-    // binary32 [32][TN + 8]: the 8 words of padding put the two rows a write instruction covers
-    // (four apart) into different halves of the 64 banks.  LDS operations of one wave execute in
-    // order, so the bands need no barrier between them.
-    if (p.stage_c && m0 + BM <= p.M && n0 + BN <= p.N) {
-        constexpr int SW = TN + 8;                 // staging row stride in words
-        constexpr int STAGE = 32 * SW * 4;         // bytes per wave
-        static_assert(NW * STAGE <= NBUF * SLOT, "staging area does not fit the operand buffers");
-        __syncthreads();  // every wave has read its last operands, every direct load has landed
-        trace_mark(p, 3);
-        GEMM_LDS(float) *stage = (GEMM_LDS(float) *)(lds + wave * STAGE);
-        const int lrow = 4 * (lane >> 5), lcol = lane & 31;
-        const int esz = p.out16 ? 2 : 4;
-        const int ldcb = (int)p.ldc * esz;
-        char *cbase = p.out16 ? (char *)((_Float16 *)p.C + (int64_t)m0 * p.ldc + n0)
-                              : (char *)(C + (int64_t)m0 * p.ldc + n0);
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)cbase, 0, 0x7fffffff, 0x00020000);
-        auto band = [&](auto out16_tag, auto policy) {
-            constexpr bool O16 = decltype(out16_tag)::value;
-            constexpr int POLICY = decltype(policy)::value;
-            constexpr int WPL = O16 ? 8 : 4;          // staged words per lane and store (16 bytes of C)
-            constexpr int LPR = TN / WPL;             // lanes per row
-            constexpr int RPI = 64 / LPR;             // rows per store instruction
-            static_assert(64 % LPR == 0 && 32 % RPI == 0, "wave tile width not supported by the staged store");
-            const int srow = lane / LPR, spiece = lane % LPR;
-            const int voff = (wm * TM + srow) * ldcb + (wn * TN) * (O16 ? 2 : 4) + spiece * 16;
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        stage[(8 * (r >> 2) + (r & 3) + lrow) * SW + j * 32 + lcol] = acc[i][j][r];
-#pragma unroll
-                for (int it = 0; it < 32 / RPI; ++it) {
-                    const GEMM_LDS(float) *src = stage + (it * RPI + srow) * SW + spiece * WPL;
-                    const int soff = (i * 32 + it * RPI) * ldcb;
-                    if constexpr (O16) {
-                        const float4_t lo = *(const GEMM_LDS(float4_t) *)src;
-                        const float4_t hi = *(const GEMM_LDS(float4_t) *)(src + 4);
-                        half8_t h;
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            h[x] = (_Float16)lo[x];
-                            h[4 + x] = (_Float16)hi[x];
-                        }
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, h), rsrc, voff, soff, POLICY);
-                    } else {
-                        const float4_t v = *(const GEMM_LDS(float4_t) *)src;
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), rsrc, voff, soff, POLICY);
-                    }
-                }
-            }
-        };
-        if (p.out16) band(std::true_type(), std::integral_constant<int, 0>());
-        else if (p.stream_c) band(std::false_type(), std::integral_constant<int, 2>());
-        else band(std::false_type(), std::integral_constant<int, 0>());
-        trace_stores();
-        return;
-    }
-#endif
-    trace_mark(p, 3);
-    if (p.out16) {
-        // binary16 result (never combined with K-slices: those reduce from binary32 partials)
-        _Float16 *Ch = (_Float16 *)p.C;
-#if defined(__HIP_DEVICE_COMPILE__)
-        if (p.ldc < (int64_t(1) << 20)) {
-            // same range-checked descriptor as the binary32 edge-tile stores below
-            const int ldc2 = (int)p.ldc * 2;
-            const int rows_valid = p.M - m0 < BM ? p.M - m0 : BM;
-            const __amdgpu_buffer_rsrc_t rsrc =
-                __builtin_amdgcn_make_buffer_rsrc((void *)(Ch + (int64_t)m0 * p.ldc + n0), 0, rows_valid * ldc2, 0x00020000);
-            const int voff = (wm * TM + 4 * (lane >> 5)) * ldc2 + (wn * TN + (lane & 31)) * 2;
-            int voffj[FN];
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-                voffj[j] = n0 + wn * TN + j * 32 + (lane & 31) < p.N ? voff + j * 64 : (int)0x80000000;
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int roff = (i * 32 + 8 * (r >> 2) + (r & 3)) * ldc2;
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) {
-                        const _Float16 h = (_Float16)acc[i][j][r];
-                        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, h), rsrc, voffj[j] + roff, 0, 0);
-                    }
-                }
-            trace_stores();
-            return;
-        }
-#endif
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int col = n0 + wn * TN + j * 32 + (lane & 31);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = m0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    if (row < p.M && col < p.N) Ch[(int64_t)row * p.ldc + col] = (_Float16)acc[i][j][r];
-                }
-            }
-        }
-        trace_stores();
-        return;
-    }
-#if defined(__HIP_DEVICE_COMPILE__)  // the host pass of hipcc does not know the buffer builtins
-    // Tiles that lie fully inside C (and whose byte offsets fit 32 bits) store through a
-    // buffer descriptor based at the tile origin: the per-lane part of the address is one
-    // 32-bit register, the row (i, r) a scalar offset and the column block j an immediate,
-    // so a store costs an accumulator read, a scalar multiply shared by FN stores, and the
-    // store itself - no per-store 64-bit address arithmetic, compares or exec masking.
-    if (m0 + BM <= p.M && n0 + BN <= p.N && p.ldc < (int64_t(1) << 20)) {
-        const __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(C + (int64_t)m0 * p.ldc + n0), 0, 0x7fffffff, 0x00020000);
-        const int ldc4 = (int)p.ldc * 4;
-        const int voff = (wm * TM + 4 * (lane >> 5)) * ldc4 + (wn * TN + (lane & 31)) * 4;
-        // C is written once and never read here.  When every 128-byte piece a store instruction
-        // writes is a whole cache line (host flag) the stores carry the non-temporal hint, which
-        // keeps the result from displacing A and B panels in the L2 (8192^3: 1-6 % faster);
-        // on partial lines the hint costs 10 %, and K-slice partials are re-read at once.
-        auto store_all = [&](auto policy) {
-            constexpr int POLICY = decltype(policy)::value;  // cache-policy operand: bit 1 = nt
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int soff = (i * 32 + 8 * (r >> 2) + (r & 3)) * ldc4;
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) {
-                        // through a scalar temporary: a bit cast applied directly to a vector
-                        // element expression reads element 0 with this compiler
-                        const float v = acc[i][j][r];
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc, voff + j * 128, soff, POLICY);
-                    }
-                }
-        };
-        if (p.stream_c) store_all(std::integral_constant<int, 2>());
-        else store_all(std::integral_constant<int, 0>());
-        trace_stores();
-        return;
-    }
-    // Edge tiles, same descriptor trick: the descriptor's range ends with the last valid row
-    // (out-of-range buffer stores are discarded by the hardware) and lanes whose column is
-    // past N get an offset that is out of range by itself.  The row offset goes into the
-    // vector offset here, because the range check does not look at the scalar offset.
-    if (p.ldc < (int64_t(1) << 20)) {
-        const int ldc4 = (int)p.ldc * 4;
-        const int rows_valid = p.M - m0 < BM ? p.M - m0 : BM;
-        const __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(C + (int64_t)m0 * p.ldc + n0), 0, rows_valid * ldc4, 0x00020000);
-        const int voff = (wm * TM + 4 * (lane >> 5)) * ldc4 + (wn * TN + (lane & 31)) * 4;
-        int voffj[FN];
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-            voffj[j] = n0 + wn * TN + j * 32 + (lane & 31) < p.N ? voff + j * 128 : (int)0x80000000;
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int roff = (i * 32 + 8 * (r >> 2) + (r & 3)) * ldc4;
-#pragma unroll
-                for (int j = 0; j < FN; ++j) {
-                    const float v = acc[i][j][r];
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc, voffj[j] + roff, 0, 0);
-                }
-            }
-        trace_stores();
-        return;
-    }
-#endif
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            const int col = n0 + wn * TN + j * 32 + (lane & 31);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = m0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (row < p.M && col < p.N) C[(int64_t)row * p.ldc + col] = acc[i][j][r];
-            }
-        }
-    }
-    trace_stores();
+    store_tile<BM, BN, WM, WN, NBUF * SLOT>(p, acc, lds, m0, n0, slice, wave, lane);
 }
 
 }  // namespace gemm_gfx950

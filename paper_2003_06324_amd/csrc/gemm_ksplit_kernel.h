@@ -66,22 +66,10 @@ __global__ __launch_bounds__(256) void gemm_ksplit_kernel(const KernelArgs p)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // same work-item order as gemm_tile_kernel: one contiguous run per XCD, K-slice by K-slice
-    const int ntiles = p.tiles_m * p.tiles_n;
-    const int nwork = ntiles * p.splits;
-    const int per_xcd = (nwork + 7) >> 3;
-    const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (work >= nwork) return;
-    const int slice = work / ntiles;
-    const int lin = work - slice * ntiles;
-    constexpr int GM = 8;
-    const int band = lin / (GM * p.tiles_n);
-    const int first_m = band * GM;
-    const int band_rows = (p.tiles_m - first_m) < GM ? (p.tiles_m - first_m) : GM;
-    const int in_band = lin - band * GM * p.tiles_n;
-    const int tile_m = first_m + in_band % band_rows;
-    const int tile_n = in_band / band_rows;
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    WorkItem item;
+    if (!work_item(p, item)) return;
+    const int slice = item.slice;
+    const int m0 = item.tile_m * BM, n0 = item.tile_n * BN;
 
     const int KT = p.K / BK;  // K is a multiple of the slab here
     const int kt0 = slice * p.kt_per_split;

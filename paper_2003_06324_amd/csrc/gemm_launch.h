@@ -4,6 +4,7 @@
 #include "gemm_kernel.h"
 #include "gemm_ksplit_kernel.h"
 #include "gemm_small_kernel.h"
+#include "gemm_stage_kernel.h"
 
 #include <tuple>
 #include <utility>
@@ -69,6 +70,18 @@ hipError_t launch_small(bool akc, bool bkc, dim3 grid, hipStream_t s, const Kern
     return launch_kernel(gemm_small_kernel<T, false, false>, grid, block, s, a);
 }
 
+// operands the direct loads serve (`aligned` as above)
+template <typename T, int BM, int BN, int NST>
+hipError_t launch_stage(bool akc, bool bkc, bool aligned, dim3 grid, hipStream_t s, const KernelArgs &a)
+{
+    (void)aligned;
+    const dim3 block(256);
+    if (akc && bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, true>, grid, block, s, a);
+    if (akc && !bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, false>, grid, block, s, a);
+    if (!akc && bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, false, true>, grid, block, s, a);
+    return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, false, false>, grid, block, s, a);
+}
+
 typedef hipError_t (*launch_fn)(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
 
 #define GEMM_DECLARE_TILE(T, BM, BN, WM, WN) \
@@ -79,6 +92,10 @@ typedef hipError_t (*launch_fn)(bool, bool, bool, dim3, hipStream_t, const Kerne
     extern template hipError_t launch_ksplit<T, BM, BN>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
 #define GEMM_INSTANTIATE_KSPLIT(T, BM, BN) \
     template hipError_t launch_ksplit<T, BM, BN>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
+#define GEMM_DECLARE_STAGE(T, BM, BN, NST) \
+    extern template hipError_t launch_stage<T, BM, BN, NST>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
+#define GEMM_INSTANTIATE_STAGE(T, BM, BN, NST) \
+    template hipError_t launch_stage<T, BM, BN, NST>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
 #define GEMM_DECLARE_SMALL(T) \
     extern template hipError_t launch_small<T>(bool, bool, dim3, hipStream_t, const KernelArgs &);
 #define GEMM_INSTANTIATE_SMALL(T) template hipError_t launch_small<T>(bool, bool, dim3, hipStream_t, const KernelArgs &);
