@@ -192,6 +192,30 @@ struct DirectLoader {
         step = (KC ? (int64_t)BK : (int64_t)BK * ld) * (int64_t)sizeof(T);
     }
 
+    // end of an operand of `rmax` rows (tile direction) and `kmax` k.  The range check drops a dword that is not wholly
+    // inside: an odd number of 16-bit elements is rounded up, which admits the two bytes behind the last element, in the
+    // same aligned dword (the direct loads' operands are 4-byte aligned).
+    static __device__ __forceinline__ uint64_t end_of(const T *origin, int64_t ld, int rmax, int kmax)
+    {
+        const T *e = origin + (KC ? (int64_t)(rmax - 1) * ld + kmax : (int64_t)(kmax - 1) * ld + rmax);
+        return ((uint64_t)(uintptr_t)e + 3) & ~(uint64_t)3;
+    }
+    // Before the loads of the operand's last slab, of which `krem` k lie inside: the descriptor's range ends with the
+    // operand, so that k-rows past K, and what a granule reaches past the operand's end, read as zeros; lanes whose whole
+    // granule of a K-contiguous row lies past K load from outside the range.
+    __device__ __forceinline__ void last_slab(uint64_t end, int krem, int wave, int lane)
+    {
+        const uint64_t left = end - (((uint64_t)(uint32_t)rsrc[1] << 32) | (uint32_t)rsrc[0]);
+        rsrc[2] = __builtin_amdgcn_readfirstlane((left >> 31) != 0 ? 0x7fffffff : (int)(uint32_t)left);
+        if (!KC) return;
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            const int r = ROWS_PER_LOAD * (wave + i * NW) + lane / GPR;
+            const int g = (lane % GPR) ^ swz_kc(r);
+            if (g * EPC >= krem) off[i] = 0x80000000u;
+        }
+    }
+
     // issue this wave's loads number [i0, i1) of the current slab into the slot at dst
     __device__ __forceinline__ void issue(GEMM_LDS(char) *dst, int wave, int i0 = 0, int i1 = PER_WAVE)
     {
@@ -805,12 +829,6 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     const bool safe = p.safe != 0;
 
     float16_t acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     // Keeps the accumulators in the accumulation registers at this point (an empty asm with an
     // "a" constraint): without it the register allocator parks part of them in ordinary
     // vector registers across the guarded loop and spills the staging registers instead.
@@ -820,7 +838,16 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
 #pragma unroll
             for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
     };
-    pin_acc();
+    auto zero_acc = [&]() {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        pin_acc();
+    };
+    if (!ALIGNED) zero_acc();  // (else while the first loads are on their way)
 
     // One k-group of work in a fixed instruction order (the compiler may not move anything
     // across the fences): the m-th MFMA block (row m / FN of the wave's blocks) is followed by the m-th operand fetch of
@@ -866,8 +893,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     typedef std::integral_constant<int, 0> L0;
 
     int k_done = kt0 * BK;  // first k not yet accumulated
-    // Registers of the guarded loop at the end.  When a fast path is followed by leftover k
-    // (a ragged tail), it fetches the first leftover slab into them before its own last slab
+    // Registers of the guarded loop at the end (register-staged path).  When the full slabs are followed by leftover k
+    // (a ragged tail), they fetch the first leftover slab into them before its own last slab
     // is multiplied, so that the loads are not waited for in the open.
     Staged<T, BM, NT> sa_;
     Staged<T, BN, NT> sb_;
@@ -879,8 +906,9 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             staged_ready = true;
         }
     };
-    if (ALIGNED) {
-        // Full slabs: direct global->LDS loads into a ring of NSLOT = 5 operand slots.  One
+    if constexpr (ALIGNED) {
+        constexpr int EPC_ = Elem<T>::EPC;
+        // Slabs: direct global->LDS loads into a ring of NSLOT = 5 operand slots.  One
         // operand, called X below, goes first: slabs are fetched in the order X(0) Y(0) X(1)
         // Y(1) ..., slab number h going to slot h % 5, so tile t has X in slot 2t % 5 and Y
         // in the next one, and one slot is always spare.  Per tile t (four k-groups, operand
@@ -897,16 +925,17 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
         // the number of outstanding loads constant for the counted waits.
         // A granule of an M/N-contiguous operand that straddles the matrix edge is read whole (its
         // tail, padding or the start of the next k-row, only feeds tile rows that are never
-        // stored); on the operand's last k-row that tail could lie past the operand, so a tile
-        // with such granules leaves the slab holding that row to the guarded loop below.
-        constexpr int EPC_ = Elem<T>::EPC;
-        const bool edge_a = !AKC && p.M % EPC_ != 0 && m0 + BM > p.M;
-        const bool edge_b = !BKC && p.N % EPC_ != 0 && n0 + BN > p.N;
-        const bool narrow = (edge_a && p.lda < 2 * EPC_) || (edge_b && p.ldb < 2 * EPC_);
-        int n = (kend - k_done) / BK;
-        if ((edge_a || edge_b) && k_done + n * BK == p.K) --n;
-        if (narrow) n = 0;
-        if (n > 0) {
+        // stored).  Towards the operand's end the loads are range-checked against it (last_slab), so that
+        // the last slab may be ragged and the last k-row's granules may straddle its end: a slab left to
+        // guarded loads of its own would be fetched, staged and multiplied in the open, 2.3 .. 2.8 slab
+        // times.  The range is exact from two slabs before the end on, because with a leading dimension
+        // below the granule it covers up to four k-rows.
+        const int n = kt1 - kt0;
+        const bool ends = kt1 == KT;                                // this slice holds the operand's last slab
+        const int krem = ends ? p.K - (kt1 - 1) * BK : BK;          // k of the slice's last slab
+        // whether its loads have to be checked
+        const bool checked = ends && (krem < BK || (!AKC && p.M % EPC_ != 0 && m0 + BM > p.M) || (!BKC && p.N % EPC_ != 0 && n0 + BN > p.N));
+        {
             DirectLoader<T, BM, NW, AKC> la;
             DirectLoader<T, BN, NW, BKC> lb;
             la.init(A, p.lda, m0, p.M, k_done, wave, lane);
@@ -931,7 +960,18 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             auto y_issue = [&](GEMM_LDS(char) *dst, int q) { if constexpr (BF) la.issue1(dst, wave, q); else lb.issue1(dst, wave, q); };
             auto x_advance = [&](bool more) { if constexpr (BF) lb.advance(more); else la.advance(more); };
             auto y_advance = [&](bool more) { if constexpr (BF) la.advance(more); else lb.advance(more); };
+            // a loader points at tile h now
+            auto a_at = [&](int h) {
+                if (__builtin_expect(checked && h >= n - 2 && h < n, 0)) la.last_slab(la.end_of(A, p.lda, p.M, p.K), h == n - 1 ? krem : BK, wave, lane);
+            };
+            auto b_at = [&](int h) {
+                if (__builtin_expect(checked && h >= n - 2 && h < n, 0)) lb.last_slab(lb.end_of(B, p.ldb, p.N, p.K), h == n - 1 ? krem : BK, wave, lane);
+            };
+            auto x_at = [&](int h) { if constexpr (BF) b_at(h); else a_at(h); };
+            auto y_at = [&](int h) { if constexpr (BF) a_at(h); else b_at(h); };
             // X(0) Y(0) X(1) Y(1); the loaders then point at tile 2 (or the last tile)
+            a_at(0);
+            b_at(0);
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
 #pragma unroll
@@ -939,9 +979,15 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
                     if (h % 2 == 0) x_issue(lds + h * SLOT, q);
                     else y_issue(lds + h * SLOT, q);
                 }
-                if (h % 2 == 0) x_advance(h / 2 + 1 < n);
-                else y_advance(h / 2 + 1 < n);
+                if (h % 2 == 0) {
+                    x_advance(h / 2 + 1 < n);
+                    x_at(h / 2 + 1);
+                } else {
+                    y_advance(h / 2 + 1 < n);
+                    y_at(h / 2 + 1);
+                }
             }
+            zero_acc();
             if (safe) {
                 full_sync();
             } else {
@@ -962,10 +1008,11 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             // The k-groups of one steady-state tile; cX.. are the slots of this and the next tile.
             auto tile_kgroups = [&](const GEMM_LDS(char) * cA, const GEMM_LDS(char) * cB, const GEMM_LDS(char) * nA,
                                     const GEMM_LDS(char) * nB, auto load_x_lo, auto load_x_hi, auto load_y,
-                                    const bool more) {
+                                    const bool more, auto near_end, const int h) {  // the loaders move to tile h, if there is one (more)
                 kgroup(fa[0], fb[0], fa[1], fb[1], cA, cB, 1, true, load_x_lo, std::integral_constant<int, NVX / 2>());
                 kgroup(fa[1], fb[1], fa[0], fb[0], cA, cB, 2, true, load_x_hi, std::integral_constant<int, NVX - NVX / 2>());
                 x_advance(more);
+                if constexpr (decltype(near_end)::value) x_at(h);
                 kgroup(fa[0], fb[0], fa[1], fb[1], cA, cB, 3, true, no_load, L0());
                 // tile t+1 landed (all but the youngest NVX loads), own reads of tile t done
                 if (safe) {
@@ -976,6 +1023,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
                 }
                 kgroup(fa[1], fb[1], fa[0], fb[0], nA, nB, 0, true, load_y, std::integral_constant<int, NVY>());
                 y_advance(more);
+                if constexpr (decltype(near_end)::value) y_at(h);
                 if (safe) full_sync();
             };
             // One steady-state tile whose slot pair starts at slot SA (compile time).
@@ -994,7 +1042,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
                     if constexpr (BF) la.template issue_at<O0>(wave_lds, q); else lb.template issue_at<O0>(wave_lds, q);
                 };
                 tile_kgroups(lds + (PA ? O1 : O0), lds + (PB ? O1 : O0), lds + (PA ? O3 : O2), lds + (PB ? O3 : O2),
-                             load_x_lo, load_x_hi, load_y, more);
+                             load_x_lo, load_x_hi, load_y, more, std::false_type(), 0);
             };
             static_assert(NSLOT == 5, "the slot sequence below is 0 2 4 1 3");
             // Constant addresses for five slots cost address registers (one base per 64 KiB of
@@ -1003,8 +1051,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             constexpr bool CONST_SLOTS = NW <= 4;
             const int nbody = n - 1;  // tiles 0 .. n-2 run a tile body, tile n-1 has nothing to load
             int t = 0;
-            // whole groups whose loaders all still advance (tile t + 4 fetches tile t + 6 < n)
-            for (; CONST_SLOTS && t + NSLOT + 2 < n; t += NSLOT) {
+            // whole groups whose loaders stay more than two tiles before the end (tile t + 4 moves them to tile t + 7)
+            for (; CONST_SLOTS && t + NSLOT + 4 < n; t += NSLOT) {
                 tile_body(std::integral_constant<int, 0>(), true);
                 tile_body(std::integral_constant<int, 2>(), true);
                 tile_body(std::integral_constant<int, 4>(), true);
@@ -1018,27 +1066,54 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
                 x = x >= NSLOT ? x - NSLOT : x;
                 return lds + x * SLOT;
             };
-            for (; t < nbody; ++t) {
+            auto tile_rest = [&](auto near_end) {
                 GEMM_LDS(char) *s0 = slot(0), *spare = slot(4);
                 auto load_x_lo = [&](int q) { x_issue(spare, q); };
                 auto load_x_hi = [&](int q) { x_issue(spare, NVX / 2 + q); };
                 auto load_y = [&](int q) { y_issue(s0, q); };
-                tile_kgroups(slot(PA), slot(PB), slot(2 + PA), slot(2 + PB), load_x_lo, load_x_hi, load_y, t + 3 < n);
+                tile_kgroups(slot(PA), slot(PB), slot(2 + PA), slot(2 + PB), load_x_lo, load_x_hi, load_y, t + 3 < n, near_end, t + 3);
                 sa = sa + 2 >= NSLOT ? sa + 2 - NSLOT : sa + 2;
+            };
+            // (a loop of its own for the tiles that move the loaders to a slab to be checked: the test alone costs 2 % of
+            // a product whose slabs are whole)
+            const int nplain = checked ? n - 5 : nbody;
+            for (; t < nplain; ++t) tile_rest(std::false_type());
+            for (; t < nbody; ++t) tile_rest(std::true_type());
+            // the last tile, up to the k-group that holds the last k; the elements past K in the granule that
+            // straddles it (of a K-contiguous operand) are masked in registers
+            const bool part = krem % EPC_ != 0;
+            uint4_t mask = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+            if (part && (lane >> 5) == krem % Elem<T>::KG / EPC_) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int in = krem % EPC_ * (int)sizeof(T) - 4 * w;  // bytes of this word inside K
+                    mask[w] = in >= 4 ? 0xffffffffu : (in == 2 ? 0x0000ffffu : 0u);
+                }
             }
-            prefetch_leftover(k_done + n * BK);
-            {
-                const GEMM_LDS(char) *cA = slot(PA), *cB = slot(PB);
-                kgroup(fa[0], fb[0], fa[1], fb[1], cA, cB, 1, true, no_load, L0());
-                kgroup(fa[1], fb[1], fa[0], fb[0], cA, cB, 2, true, no_load, L0());
-                kgroup(fa[0], fb[0], fa[1], fb[1], cA, cB, 3, true, no_load, L0());
-                kgroup(fa[1], fb[1], fa[0], fb[0], cA, cB, 0, false, no_load, L0());
-            }
-            k_done += n * BK;
+            const GEMM_LDS(char) *cA = slot(PA), *cB = slot(PB);
+            auto last_group = [&](frag_t(&ca)[FM], frag_t(&cb)[FN], frag_t(&na)[FM], frag_t(&nb)[FN], auto kg_tag) {
+                constexpr int kg = decltype(kg_tag)::value;
+                if (part && kg == krem / Elem<T>::KG) {
+                    if (AKC) {
+#pragma unroll
+                        for (int i = 0; i < FM; ++i) ca[i] = __builtin_bit_cast(frag_t, __builtin_bit_cast(uint4_t, ca[i]) & mask);
+                    }
+                    if (BKC) {
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) cb[j] = __builtin_bit_cast(frag_t, __builtin_bit_cast(uint4_t, cb[j]) & mask);
+                    }
+                }
+                if (kg * Elem<T>::KG < krem) kgroup(ca, cb, na, nb, cA, cB, (kg + 1) % KGS, kg + 1 < KGS, no_load, L0());
+                pin_acc();
+            };
+            last_group(fa[0], fb[0], fa[1], fb[1], std::integral_constant<int, 0>());
+            last_group(fa[1], fb[1], fa[0], fb[0], std::integral_constant<int, 1>());
+            last_group(fa[0], fb[0], fa[1], fb[1], std::integral_constant<int, 2>());
+            last_group(fa[1], fb[1], fa[0], fb[0], std::integral_constant<int, 3>());
             __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));  // drain the redundant refills
         }
     }
-    if (!ALIGNED) {
+    if constexpr (!ALIGNED) {
         // Operands the direct loads do not serve (2-byte aligned, or forced): full slabs go through registers into two LDS
         // buffers (the same image as the direct loads make).  Per slab s: k-groups 0,1 multiply;
         // k-group 2 also writes slab s+1 (in registers since an earlier slab) to the other
@@ -1165,10 +1240,10 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             // the redundant last refill is still in flight: it targets registers only
         }
     }
-    // Remaining slabs (a ragged K tail; everything for the tiles excluded above): guarded
-    // loads through registers into one LDS buffer; the loads of slab s+1 are issued before
-    // slab s is multiplied and written to LDS after it.
-    if (k_done < kend) {
+    // Remaining slabs of operands the direct loads do not serve (a ragged K tail; everything for the
+    // tiles excluded above): guarded loads through registers into one LDS buffer; the loads of slab
+    // s+1 are issued before slab s is multiplied and written to LDS after it.
+    if (!ALIGNED && k_done < kend) {
         __syncthreads();  // LDS is free (direct-load pipeline drained, all reads done)
         if (!staged_ready) {
             guarded_fetch<T, BM, NT, AKC>(sa_, A, p.lda, m0, p.M, k_done, kend, tid);
