@@ -3,12 +3,15 @@ import concurrent.futures
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgemm_mi355x.so")
+BINDING_SRC = os.path.join(CSRC, "binding.cpp")
+BINDING = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC,
@@ -35,8 +38,19 @@ def _compile(src, force):
     return obj
 
 
+def build_binding(force=False):
+    """Compile the Python extension that calls the library (host code only). Returns its path."""
+    if force or _stale(BINDING, [BINDING_SRC]):
+        tmp = BINDING + ".tmp%d" % os.getpid()
+        subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+                        "-I" + sysconfig.get_paths()["include"], BINDING_SRC, "-o", tmp], check=True)
+        os.replace(tmp, BINDING)
+    return BINDING
+
+
 def build(force=False, jobs=None):
-    """Compile every .hip file and link the shared library. Returns its path."""
+    """Compile every .hip file and link the shared library, and the Python extension. Returns the library's path."""
+    build_binding(force)
     os.makedirs(OBJDIR, exist_ok=True)
     srcs = sources()
     jobs = jobs or min(8, len(srcs), os.cpu_count() or 1)

@@ -219,7 +219,16 @@ struct DeviceState {
 };
 std::map<int, DeviceState> g_dev;
 
-thread_local char t_last_config[128] = "none";
+// What the calling thread's last call ran.  Kept as it is and put into words by gemm_last_config: the text took longer
+// (0.3 us) than the rest of the library's own part of a call.
+struct LastCall {
+    const char *type = nullptr, *special = nullptr, *tile = nullptr;  // special: "empty", "zero-fill", or null
+    bool akc = false, bkc = false, small = false, safe = false, fixed_scratch = false;
+    const char *path = nullptr;
+    int splits = 0;
+};
+thread_local LastCall t_last;
+thread_local char t_last_config[128];
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -504,7 +513,9 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     if (M > kMax || N > kMax || K > kMax) return GEMM_ERR_UNSUPPORTED;
     hipStream_t stream = (hipStream_t)stream_;
     if (M == 0 || N == 0) {
-        snprintf(t_last_config, sizeof t_last_config, "%s empty", type_name);
+        t_last = LastCall();
+        t_last.type = type_name;
+        t_last.special = "empty";
         return GEMM_OK;
     }
 
@@ -525,7 +536,9 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         const int blocks = (int)(cdiv(total, 256) < 65536 ? cdiv(total, 256) : 65536);
         if (launch_kernel(fill_zero_kernel<TC>, dim3(blocks), dim3(256), stream, C, ldc, (int)M, (int)N) != hipSuccess)
             return GEMM_ERR_HIP;
-        snprintf(t_last_config, sizeof t_last_config, "%s zero-fill", type_name);
+        t_last = LastCall();
+        t_last.type = type_name;
+        t_last.special = "zero-fill";
         return GEMM_OK;
     }
 
@@ -663,9 +676,8 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
                                             vec_c);
         if (rc != hipSuccess) return GEMM_ERR_HIP;
     }
-    snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s", type_name, t.name,
-             akc ? 'N' : 'T', bkc ? 'T' : 'N', aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, small ? " small" : "", a.safe ? " safe" : "",
-             noalloc && splits > 1 ? " static-scratch" : "");
+    t_last = LastCall{type_name, nullptr, t.name, akc, bkc, small, a.safe != 0, noalloc && splits > 1,
+                      aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits};
     return GEMM_OK;
 }
 
@@ -1018,7 +1030,17 @@ int gemm_num_configs(void) { return kNumTiles; }
 
 const char *gemm_config_name(int i) { return (i >= 0 && i < kNumTiles) ? kTiles[i].name : nullptr; }
 
-const char *gemm_last_config(void) { return t_last_config; }
+const char *gemm_last_config(void)
+{
+    const LastCall &l = t_last;
+    if (l.type == nullptr) return "none";
+    if (l.special != nullptr)
+        snprintf(t_last_config, sizeof t_last_config, "%s %s", l.type, l.special);
+    else
+        snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s", l.type, l.tile, l.akc ? 'N' : 'T', l.bkc ? 'T' : 'N', l.path,
+                 l.splits, l.small ? " small" : "", l.safe ? " safe" : "", l.fixed_scratch ? " static-scratch" : "");
+    return t_last_config;
+}
 
 const char *gemm_status_string(int status)
 {

@@ -1,4 +1,5 @@
-"""ctypes binding of include/gemm.h.  Argument marshalling only.
+"""Python binding of include/gemm.h.  Argument marshalling only: ctypes, and for the product calls a C extension
+(csrc/binding.cpp) that hands plain arguments over without it.
 
 The functions take raw device addresses (ints), or any object exposing
 ``data_ptr()`` (a torch tensor) -- torch is used by callers purely to own
@@ -14,8 +15,16 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libgemm_mi355x.so")
 _lib = None
 
+try:
+    from . import _binding   # built with the library (build.py)
+except ImportError:
+    _binding = None          # the ctypes functions below serve every call
+
 EXPORTS = ("gemm_f32", "gemm_f16f32", "gemm_f16f16", "gemm_bf16f32", "gemm_f16f32_noalloc", "gemm_cost_model_scale", "gemm_set_phase_trace", "gemm_force_config", "gemm_query_config", "gemm_query_config_layouts", "gemm_tune", "gemm_tune_clear", "gemm_tune_save", "gemm_tune_load", "gemm_num_configs", "gemm_config_name",
            "gemm_last_config", "gemm_status_string", "gemm_shutdown")
+
+
+PRODUCTS = ("gemm_f32", "gemm_f16f32", "gemm_f16f16", "gemm_bf16f32", "gemm_f16f32_noalloc")
 
 
 class GemmError(RuntimeError):
@@ -80,6 +89,8 @@ def load_library():
     lib.gemm_shutdown.argtypes = []
     lib.gemm_shutdown.restype = i32
     _lib = lib
+    if _binding is not None:
+        _binding.bind(_check, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in PRODUCTS))
     return lib
 
 
@@ -135,6 +146,11 @@ def gemm_f16f32_noalloc(M, N, K, A, layoutA, lda, B, layoutB, ldb, C, layoutC, l
                                             _ptr(C), layoutC, ldc, stream or None)
     return _check(rc) if check else rc
 
+
+if _binding is not None:
+    for _i, _name in enumerate(PRODUCTS):
+        _binding.general(_i, globals()[_name])   # before the library is loaded, and for arguments that are not plain
+    from ._binding import gemm_bf16f32, gemm_f16f16, gemm_f16f32, gemm_f16f32_noalloc, gemm_f32  # noqa: F811
 
 NOALLOC_SCRATCH_BYTES = 64 << 20
 COST_SLAB, COST_HBM, COST_L2, COST_FIXED = 0, 1, 2, 3
