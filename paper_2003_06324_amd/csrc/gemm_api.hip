@@ -112,6 +112,47 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *ws, int
     }
 }
 
+// Sums the partial tiles of a launch whose last tiles were sliced (KernelArgs::whole_tiles) in slice order into C: the
+// same pass over packed tiles, [slice][tile][BM][BN].  grid.y: tile; the pieces of a tile (four columns) are shared out in x.
+template <typename TC>
+__global__ __launch_bounds__(256) void tail_reduce_kernel(const float *ws, int splits, int whole_tiles, int tiles_m, int tiles_n,
+                                                          Divisor by_band, Divisor by_last_rows, int BM, int BN, TC *C, int64_t ldc, int M, int N, int vec_c)
+{
+    typedef float vec_t __attribute__((ext_vector_type(4)));
+    typedef TC out_t __attribute__((ext_vector_type(4)));
+    int tile_m, tile_n;
+    tile_at(tiles_m, tiles_n, by_band, by_last_rows, whole_tiles + blockIdx.y, tile_m, tile_n);
+    const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;  // element of the tile; the grid holds exactly BM * BN / 4 threads a tile
+    const int row = tile_m * BM + idx / BN, col = tile_n * BN + idx % BN;
+    if (row >= M || col >= N) return;
+    const int64_t stride = (int64_t)(tiles_m * tiles_n - whole_tiles) * BM * BN;
+    const float *src = ws + (int64_t)blockIdx.y * BM * BN + idx;
+    vec_t s = 0.0f;
+    int z = 0;
+    for (; z + 4 <= splits; z += 4) {
+        const vec_t v0 = *(const vec_t *)(src + (z + 0) * stride);
+        const vec_t v1 = *(const vec_t *)(src + (z + 1) * stride);
+        const vec_t v2 = *(const vec_t *)(src + (z + 2) * stride);
+        const vec_t v3 = *(const vec_t *)(src + (z + 3) * stride);
+        s += v0;
+        s += v1;
+        s += v2;
+        s += v3;
+    }
+    for (; z < splits; ++z) s += *(const vec_t *)(src + z * stride);
+    TC *dst = C + (int64_t)row * ldc + col;
+    if (vec_c && col + 4 <= N) {
+        out_t o;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) o[x] = (TC)s[x];
+        *(out_t *)dst = o;
+    } else {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            if (col + x < N) dst[x] = (TC)s[x];
+    }
+}
+
 template <typename TC>
 __global__ __launch_bounds__(256) void fill_zero_kernel(TC *C, int64_t ldc, int M, int N)
 {
@@ -171,9 +212,9 @@ const TileConfig kTiles[] = {
     {"t256x256", 256, 256, 1, 1.02, 1.02, 6.98, 6.98, 7.2, 0.83, 1.2, 1.05, 1.67, 1.25, 1,
      GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t128x128", 128, 128, 2, 0.457, 0.868, 1.99, 3.64, 1.92, 1.39, 1.23, 0.817, 1.57, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.40, 1.40, 24},
+     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.41, 1.40, 24},
     {"t64x64", 64, 64, 4, 0.265, 0.855, 0.495, 1.86, 1.27, 0.78, 1.07, 0.992, 1.65, 1.35, 4,
-     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.187, 1.48, 16},
+     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.21, 1.48, 16},
     {"t256x256w8", 256, 256, 1, 1.05, 1.05, 7.6, 7.6, 6.02, 0.812, 1.2, 0.915, 1.35, 1.15, 1,
      GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t256x128", 256, 128, 1, 0.71, 0.71, 3.52, 3.52, 3.82, 0.637, 1.2, 1.09, 1.47, 1.3, 1,
@@ -181,9 +222,9 @@ const TileConfig kTiles[] = {
     {"t128x256", 128, 256, 1, 0.661, 0.661, 4.19, 4.19, 4.17, 1.78, 1.25, 0.864, 2.03, 1.3, 1,
      GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t64x128", 64, 128, 2, 0.349, 0.512, 1.12, 1.86, 1.67, 1.11, 1.31, 0.884, 1.87, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.255, 1.60, 16},
+     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.275, 1.50, 16},
     {"t128x64", 128, 64, 2, 0.371, 0.617, 1.14, 1.81, 1.33, 1.06, 1.31, 0.919, 1.84, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.28, 1.6, 16},
+     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.30, 1.6, 16},
     // K split across the four waves of the workgroup (Section 5.3, small sizes); fitted on 16-byte aligned operands only
     {"k64x64", 64, 64, 4, 0.311, 0.854, 0.598, 2.02, 2.02, 0.781, 1.07, 0.992, 1.65, 1.0, 1,
      launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, 0.0, 0.0, 0},
@@ -225,7 +266,7 @@ struct LastCall {
     const char *type = nullptr, *special = nullptr, *tile = nullptr;  // special: "empty", "zero-fill", or null
     bool akc = false, bkc = false, small = false, safe = false, fixed_scratch = false;
     const char *path = nullptr;
-    int splits = 0;
+    int splits = 0, tail = 0;  // tail: K-slices of the last tiles
 };
 thread_local LastCall t_last;
 thread_local char t_last_config[128];
@@ -238,14 +279,44 @@ int64_t ws_pitch(int64_t N) { return cdiv(N, 32) * 32; }
 size_t ws_bytes(int64_t splits, int64_t M, int64_t N) { return (size_t)splits * (size_t)M * (size_t)ws_pitch(N) * sizeof(float); }
 
 // Whether a launch on direct loads (16-bit operands, load path 0 or 3) runs gemm_stage_kernel: at most one workgroup per CU,
-// and enough slabs to pay for its longer start, 0.5 us, or a last slab that gemm_tile_kernel leaves to its guarded loop
-// (ragged: K no multiple of the slab, or granules straddling the M/N edge of an operand).  Microseconds per launch back to
+// and enough slabs to pay for its longer start, 0.5 us, or a ragged last slab (which gemm_tile_kernel left to guarded loads
+// when this was measured).  Microseconds per launch back to
 // back, 96 and 240 workgroups of each tile, gemm_tile_kernel -> gemm_stage_kernel: K = 4096 26.2 -> 15.4 and 26.3 -> 16.2
 // (64x64), 26.9 -> 19.5 and 27.9 -> 22.5 (64x128), 31.2 -> 27.0 and 36.2 -> 35.0 (128x128); K = 1024 8.4 -> 6.6, 9.3 -> 8.1,
 // 10.9 -> 10.3; K = 512 4.4 -> 5.0, 5.3 -> 6.0, 7.2 -> 7.6; with a ragged K 72 .. 1544 1.03 .. 1.5 times as fast on all tiles.
-bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, bool ragged, int num_cu)
+// Operands of more than 64 MiB stream from HBM, where loads further ahead gain nothing sure: 8192x128x8192 37.2 -> 34.3 on one
+// box and 40.9 -> 41.0 on another, 128x8192x8192 36.0 -> 34.3 and 36.5 -> 42.7, 776x504x26968 (69 MB) 38.8 -> 39.8;
+// 6848x256x3648 (52 MB) 26.3 -> 21.1.
+bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, bool ragged, int64_t operand_bytes, int num_cu)
 {
-    return t.stage16 != nullptr && workgroups <= num_cu && (ragged || slabs >= t.stage_from);
+    return t.stage16 != nullptr && workgroups <= num_cu && (ragged || slabs >= t.stage_from) && operand_bytes <= (64LL << 20);
+}
+
+size_t tail_bytes(const TileConfig &t, int64_t sliced, int splits) { return (size_t)sliced * (size_t)splits * (size_t)(t.BM * t.BN) * sizeof(float); }
+
+// microseconds that cutting the `sliced` last tiles into s slices saves, by the model's slab time: a fifth of the time the
+// round gets shorter is kept back for what a part-filled chip gains in clock
+double tail_gain(const TileConfig &t, int64_t sliced, int64_t KT, int s, bool f32)
+{
+    const double saved = (double)(KT - cdiv(KT, s)) * (f32 ? t.f32_alone : t.f16_alone);
+    return 0.8 * saved - (5.0 + (double)tail_bytes(t, sliced, s) * (1.0 + 1.0 / s) / 3.8e6);
+}
+
+// K-slices for the tiles of a last round that fills at most half of the chip (1: none).  One workgroup per CU: a round
+// takes as long with 15 tiles as with 256, so the tiles past the last full round are cut into as many slices as there are
+// CUs for them, and a second pass sums their partial tiles (tail_reduce_kernel).  Taken where the part of the round it saves
+// is worth more than the partial tiles (written, read once more, the launch of the pass).
+int tail_slices(const TileConfig &t, int64_t tiles, int64_t KT, bool f32, int num_cu, size_t max_ws_bytes)
+{
+    const int64_t sliced = tiles % num_cu;
+    if (t.wg_per_cu != 1 || tiles < num_cu || sliced == 0 || 2 * sliced > num_cu) return 1;
+    int64_t s = num_cu / sliced < 16 ? num_cu / sliced : 16;
+    if (s > KT / 4) s = KT / 4;  // at least four slabs each
+    if (s < 2) return 1;
+    s = cdiv(KT, cdiv(KT, s));   // no empty slices
+    const size_t bytes = tail_bytes(t, sliced, (int)s);
+    if (max_ws_bytes > 0 && bytes > max_ws_bytes) return 1;
+    return tail_gain(t, sliced, KT, (int)s, f32) > 0.0 ? (int)s : 1;
 }
 
 // Estimated run time in microseconds of (tile, splits) on this shape.  Three floors: the
@@ -259,7 +330,7 @@ bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, bool rag
 // k_contig: how many of A and B have K as their contiguous dimension (0..2); the misaligned
 // classes depend on it (a K-contiguous row is what straddles lines or gets its loads split)
 double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64_t KT, int splits, bool f32,
-                     int path, int k_contig, int NUM_CU)
+                     int path, int k_contig, int NUM_CU, size_t max_ws_bytes)
 {
     static const double kLayA4[3] = {0.867, 1.0, 0.986};  // 16-bit, path 3, by k_contig
     static const double kLayA2[3] = {1.14, 1.0, 1.19};   // 16-bit, path 2
@@ -288,8 +359,9 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     if (path == 1 || path == 2) slab *= f32 ? 1.05 : (path == 2 ? t.f16_a2 * kLayA2[k_contig] : t.general);
     slab *= foot_factor;
     // (its slab time hardly depends on where the operands come from; a ragged last slab is one more)
-    if (!f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K % 64 != 0, NUM_CU)) {
-        slab = t.stage_slab * (path == 3 ? t.stage_a4 : 1.0);
+    const bool stage = !f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K % 64 != 0, (M + N) * K * 2, NUM_CU);
+    if (stage) {
+        slab = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : 1.0);
         tail = 0.0;
     }
     if (path == 1 || path == 2) {
@@ -302,13 +374,20 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     }
     slab *= scale[GEMM_COST_SLAB];
     double t_mfma = rounds * ((double)per * slab + t.fixed);
+    if (splits == 1) {
+        const int ts = tail_slices(t, tiles, KT, f32, NUM_CU, max_ws_bytes);
+        if (ts > 1) t_mfma -= tail_gain(t, tiles % NUM_CU, KT, ts, f32);
+    }
     if (K % (f32 ? 32 : 64) != 0) t_mfma += tail * slab;
     const double unique = ((double)M * K + (double)K * N) * esz + (double)M * N * 4.0;
     const double resident = (double)W < slots ? (double)W : slots;
     double hbm_rate = resident * 1.5 * (t.BM + t.BN) * 128.0 / 0.848;  // bytes/us the workgroups keep in flight
     if (hbm_rate > 4.79e+06) hbm_rate = 4.79e+06;
     hbm_rate *= t.hbm_eff;
-    const double t_hbm = unique / (hbm_rate * scale[GEMM_COST_HBM]);
+    double t_hbm = unique / (hbm_rate * scale[GEMM_COST_HBM]);
+    // the stage kernel's own rate on what exceeds the caches' share: 6848x256x3648 (59 MB) 18.4 us, 256x960x19648 in eight slices
+    // (49 MB) 15.5, 128x6720x1536 (25 MB) 5.5
+    if (stage) t_hbm = std::max(t_hbm, (unique - 16e6) / (2.2e6 * scale[GEMM_COST_HBM]));
     const double t_l2 = (double)W * (double)per * (t.BM + t.BN) * 128.0 / (2.18e+07 * scale[GEMM_COST_L2]);
     double cost = 2.68 * scale[GEMM_COST_FIXED] + (t_mfma > t_hbm ? (t_mfma > t_l2 ? t_mfma : t_l2) : (t_hbm > t_l2 ? t_hbm : t_l2));
     if (S > 1)
@@ -362,7 +441,7 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
             const int cand = forced > 0 ? forced : s;
             if (cand > 1 && cand > KT) break;
             if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
-            const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu);
+            const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu, max_ws_bytes);
             if (c < best) { best = c; tile = t; splits = cand; }
             if (forced > 0) break;
         }
@@ -476,6 +555,30 @@ int get_workspace(DeviceState &d, hipStream_t stream, size_t bytes, void **out)
     }
     *out = w.ptr;
     return GEMM_OK;
+}
+
+// The same for the partial tiles of a last round, which a launch can do without: nothing is allocated while the stream is
+// being captured (nor may a capture elsewhere in the process mind), and failing is no error.
+bool get_tail_workspace(DeviceState &d, hipStream_t stream, size_t bytes, void **out)
+{
+    const auto it = d.ws.find(stream);
+    if (it == d.ws.end() || it->second.bytes < bytes) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+        if (hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return false;
+        }
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        const int rc = get_workspace(d, stream, bytes, out);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        return rc == GEMM_OK;
+    }
+    *out = it->second.ptr;
+    return true;
 }
 
 // device address of this GPU's copy of `scratch` (g_mutex held); looked up once per device
@@ -605,6 +708,8 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     a.tiles_n = (int)tiles_n;
     a.kt_per_split = (int)kt_per_split;
     a.splits = splits;
+    a.whole_tiles = 0;
+    a.tail_ws = nullptr;
     a.ld32 = ld32 ? 1 : 0;
     a.out16 = 0;
     a.stream_c = 0;
@@ -650,16 +755,28 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         const bool lines = !out16 && ldc % 32 == 0 && (uintptr_t)C % 128 == 0;
         const bool rounds = tiles_m * tiles_n > (int64_t)num_cu * t.wg_per_cu;
         a.stream_c = (lines && (rounds || M * N * 4 <= (32LL << 20))) ? 1 : 0;
+        // the tiles past the last full round of the chip cut into K-slices, unless one slice was asked for by name
+        const int64_t tiles = tiles_m * tiles_n;
+        const int tail = small || g_forced_splits != 0 ? 1 : tail_slices(t, tiles, KT, f32, num_cu, noalloc ? (size_t)GEMM_NOALLOC_SCRATCH_BYTES : 0);
+        if (tail > 1 && (noalloc ? static_scratch(*dev, &ws) == GEMM_OK : get_tail_workspace(*dev, stream, tail_bytes(t, tiles % num_cu, tail), &ws))) {
+            a.splits = tail;
+            a.kt_per_split = (int)cdiv(KT, tail);
+            a.whole_tiles = (int)(tiles - tiles % num_cu);
+            a.tail_ws = (float *)ws;
+        }
     }
+    a.by_band = divisor(GM * tiles_n);
+    a.by_last_rows = divisor(tiles_m % GM > 0 ? tiles_m % GM : 1);
+    a.by_sliced = divisor(tiles_m * tiles_n - a.whole_tiles);
     hipError_t launch_rc;
     if (small) {
         a.tiles_m = (int)cdiv(M, 32);
         a.tiles_n = (int)cdiv(N, 32);
         launch_rc = launch_small<T>(akc, bkc, dim3((unsigned)(a.tiles_m * a.tiles_n)), stream, a);
     } else {
-        const dim3 grid((unsigned)(8 * cdiv(tiles_m * tiles_n * splits, 8)));
+        const dim3 grid((unsigned)work_grid((int)(tiles_m * tiles_n), a.whole_tiles, a.splits));
         launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
-        if (!f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, ragged || K % BK != 0, num_cu)) fn = bf16 ? t.stage_bf16 : t.stage16;
+        if (!f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, ragged || K % BK != 0, (M + N) * K * (int64_t)sizeof(T), num_cu)) fn = bf16 ? t.stage_bf16 : t.stage16;
         launch_rc = fn(akc, bkc, aligned, grid, stream, a);
     }
     if (launch_rc != hipSuccess) {
@@ -675,9 +792,15 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
                                             (int64_t)(M * ws_pitch(N)), splits, (int)ws_pitch(N), C, ldc, (int)M, (int)N,
                                             vec_c);
         if (rc != hipSuccess) return GEMM_ERR_HIP;
+    } else if (a.whole_tiles > 0) {
+        const dim3 grid((unsigned)(t.BM * t.BN / 1024), (unsigned)(tiles_m * tiles_n - a.whole_tiles));
+        const int vec_c = ((uintptr_t)C % (4 * sizeof(TC)) == 0 && ldc % 4 == 0) ? 1 : 0;
+        const hipError_t rc = launch_kernel(tail_reduce_kernel<TC>, grid, dim3(256), stream, (const float *)ws, a.splits, a.whole_tiles,
+                                            (int)tiles_m, (int)tiles_n, a.by_band, a.by_last_rows, t.BM, t.BN, C, ldc, (int)M, (int)N, vec_c);
+        if (rc != hipSuccess) return GEMM_ERR_HIP;
     }
-    t_last = LastCall{type_name, nullptr, t.name, akc, bkc, small, a.safe != 0, noalloc && splits > 1,
-                      aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits};
+    t_last = LastCall{type_name, nullptr, t.name, akc, bkc, small, a.safe != 0, noalloc && a.splits > 1,
+                      aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, a.whole_tiles > 0 ? a.splits : 0};
     return GEMM_OK;
 }
 
@@ -709,7 +832,7 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
             if (kTiles[t].fallback >= 0 && !key.ksplit_ok) continue;
             for (int s = 1; s <= 32 && (s == 1 || s <= KT); s *= 2)
                 cand.emplace_back(estimate_cost(kTiles[t], key.M, key.N, key.K, KT, s, key.f32 != 0, key.path, key.k_contig,
-                                                key.num_cu), t, s);
+                                                key.num_cu, 0), t, s);
         }
     }
     std::sort(cand.begin(), cand.end());
@@ -1034,11 +1157,13 @@ const char *gemm_last_config(void)
 {
     const LastCall &l = t_last;
     if (l.type == nullptr) return "none";
+    char tail[16] = "";
+    if (l.tail > 1) snprintf(tail, sizeof tail, " tail%d", l.tail);
     if (l.special != nullptr)
         snprintf(t_last_config, sizeof t_last_config, "%s %s", l.type, l.special);
     else
-        snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s", l.type, l.tile, l.akc ? 'N' : 'T', l.bkc ? 'T' : 'N', l.path,
-                 l.splits, l.small ? " small" : "", l.safe ? " safe" : "", l.fixed_scratch ? " static-scratch" : "");
+        snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s%s", l.type, l.tile, l.akc ? 'N' : 'T', l.bkc ? 'T' : 'N', l.path,
+                 l.splits, l.small ? " small" : "", l.safe ? " safe" : "", tail, l.fixed_scratch ? " static-scratch" : "");
     return t_last_config;
 }
 

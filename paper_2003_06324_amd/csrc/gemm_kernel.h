@@ -56,6 +56,20 @@ constexpr int GPR = 2 * KGS;      // granules per row of a K-contiguous image
 constexpr int RBK = 16 * GPR;     // bytes per row of a K-contiguous image
 constexpr int NSLOT = 5;          // operand slots in the LDS ring of the direct-load pipeline
 
+// Division by a number the host knows: n / d = (n * mul) >> shift, exact for 0 <= n < 2^28 (mul = ceil(2^shift / d) with
+// shift = 28 + ceil(log2 d), so mul is off by less than one part in 2^28 n).  A division the compiler writes out takes a
+// workgroup some 150 cycles before its first load.
+struct Divisor { uint32_t mul, shift; };
+inline Divisor divisor(int64_t d)
+{
+    uint32_t l = 0;
+    while ((1LL << l) < d) ++l;
+    return Divisor{(uint32_t)(((1ULL << (28 + l)) + (uint64_t)d - 1) / (uint64_t)d), 28 + l};
+}
+__host__ __device__ __forceinline__ int divide(int n, const Divisor &d) { return (int)(((uint64_t)(uint32_t)n * d.mul) >> d.shift); }
+
+constexpr int GM = 8;  // tile rows of a band, see work_item
+
 struct KernelArgs {
     const void *A;       // M x K
     const void *B;       // K x N
@@ -64,8 +78,11 @@ struct KernelArgs {
     int64_t split_stride;  // elements between consecutive K-slices of the workspace
     int M, N, K;
     int tiles_m, tiles_n;
+    Divisor by_band, by_last_rows, by_sliced;  // GM * tiles_n, tiles_m % GM, tiles that are cut into K-slices
     int kt_per_split;    // slabs per K-slice
-    int splits;          // number of K-slices; the grid holds tiles_m * tiles_n * splits work items
+    int splits;          // number of K-slices
+    int whole_tiles;     // this many tiles run all of K; the others are cut into the K-slices.  Zero without slices
+    float *tail_ws;      // if whole_tiles: the partial tiles of the others, [slice][tile - whole_tiles][BM][BN]
     int ld32;            // 256 * ld * sizeof(element) < 2^31 for A and B: tile-local byte offsets fit 32 bits
     int out16;           // C holds binary16: the accumulators are rounded (to nearest even) at the store
     int stream_c;        // binary32 C, no K-slices, rows of C start on 128-byte lines: stores may be non-temporal
@@ -546,28 +563,57 @@ __device__ __forceinline__ void mma(float16_t &acc, const float4_t &a, const flo
 }
 
 // ---------------------------------------------------------------------------
-// Work item of this workgroup.  Workgroups are dealt round-robin to the 8 XCDs (each with its own L2): every XCD
-// gets one contiguous run of work items, K-slice by K-slice (the tiles of one slice share that
-// slice's A and B panels; the same tile in another slice shares nothing), and within a
-// slice tiles are ordered in bands of GM tile rows so that tiles running together share panels.
+// Work item of this workgroup: first the tiles that run all of K, then the K-slices of the others.  Workgroups are dealt
+// round-robin to the 8 XCDs (each with its own L2): of either kind every XCD
+// gets one contiguous run, the slices K-slice by K-slice (the tiles of one slice share that
+// slice's A and B panels; the same tile in another slice shares nothing), and
+// tiles are ordered in bands of GM tile rows so that tiles running together share panels.
 // ---------------------------------------------------------------------------
-struct WorkItem { int slice, tile_m, tile_n; };
-__device__ __forceinline__ bool work_item(const KernelArgs &p, WorkItem &w)
+struct WorkItem {
+    int tile, tile_m, tile_n;
+    int slice;       // K-slice
+    int kt0, kt1;    // its slabs
+};
+__device__ __forceinline__ void tile_at(int tiles_m, int tiles_n, const Divisor &by_band, const Divisor &by_last_rows, int tile,
+                                        int &tile_m, int &tile_n)
 {
-    const int ntiles = p.tiles_m * p.tiles_n;
-    const int nwork = ntiles * p.splits;
-    const int per_xcd = (nwork + 7) >> 3;
-    const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (work >= nwork) return false;
-    w.slice = work / ntiles;
-    const int lin = work - w.slice * ntiles;
-    constexpr int GM = 8;
-    const int band = lin / (GM * p.tiles_n);
-    const int first_m = band * GM;
-    const int band_rows = (p.tiles_m - first_m) < GM ? (p.tiles_m - first_m) : GM;
-    const int in_band = lin - band * GM * p.tiles_n;
-    w.tile_m = first_m + in_band % band_rows;
-    w.tile_n = in_band / band_rows;
+    const int band = divide(tile, by_band);
+    const int in_band = tile - band * GM * tiles_n;
+    if (__builtin_expect(tiles_m - band * GM < GM, 0)) {
+        tile_n = divide(in_band, by_last_rows);
+        tile_m = band * GM + in_band - tile_n * (tiles_m - band * GM);
+    } else {
+        tile_n = in_band / GM;
+        tile_m = band * GM + in_band % GM;
+    }
+}
+// workgroups of a launch
+inline int work_grid(int tiles, int whole_tiles, int splits) { return 8 * ((whole_tiles + 7) / 8 + ((tiles - whole_tiles) * splits + 7) / 8); }
+__device__ __forceinline__ bool work_item(const KernelArgs &p, int KT, WorkItem &w)
+{
+    // Every argument the start of a kernel needs is asked for at once: left to the branches that use them, the loads
+    // miss the scalar cache one after the other (0.3 us of a launch).
+    asm volatile("" : : "s"(p.A), "s"(p.B), "s"(p.lda), "s"(p.ldb), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.tiles_m), "s"(p.tiles_n));
+    asm volatile("" : : "s"(p.by_band.mul), "s"(p.by_band.shift), "s"(p.by_last_rows.mul), "s"(p.by_last_rows.shift), "s"(p.by_sliced.mul),
+                 "s"(p.by_sliced.shift), "s"(p.kt_per_split), "s"(p.splits), "s"(p.whole_tiles), "s"(p.safe), "s"(p.trace));
+    const int sliced = p.tiles_m * p.tiles_n - p.whole_tiles;
+    const int whole_per_xcd = (p.whole_tiles + 7) >> 3, per_xcd = (sliced * p.splits + 7) >> 3;
+    const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
+    w.slice = 0;
+    w.kt0 = 0;
+    w.kt1 = KT;
+    if (__builtin_expect(i < whole_per_xcd, 0)) {  // (long launches only)
+        w.tile = xcd * whole_per_xcd + i;
+        if (w.tile >= p.whole_tiles) return false;
+    } else {
+        const int work = xcd * per_xcd + i - whole_per_xcd;
+        if (work >= sliced * p.splits) return false;
+        w.slice = p.splits == 1 ? 0 : divide(work, p.by_sliced);
+        w.tile = p.whole_tiles + work - w.slice * sliced;
+        w.kt0 = w.slice * p.kt_per_split;
+        w.kt1 = w.kt0 + p.kt_per_split < KT ? w.kt0 + p.kt_per_split : KT;
+    }
+    tile_at(p.tiles_m, p.tiles_n, p.by_band, p.by_last_rows, w.tile, w.tile_m, w.tile_n);
     return true;
 }
 
@@ -575,9 +621,21 @@ __device__ __forceinline__ bool work_item(const KernelArgs &p, WorkItem &w)
 // Stores the accumulators of a workgroup's tile; lds: the operand buffers, LDS_BYTES long, drained of loads by now.
 // ---------------------------------------------------------------------------
 template <int BM, int BN, int WM, int WN, int LDS_BYTES>
-__device__ __forceinline__ void store_tile(const KernelArgs &p, const float16_t (&acc)[BM / WM / 32][BN / WN / 32],
-                                           GEMM_LDS(char) *lds, int m0, int n0, int slice, int wave, int lane)
+__device__ __forceinline__ void store_tile(const KernelArgs &args, const WorkItem &item, const float16_t (&acc)[BM / WM / 32][BN / WN / 32],
+                                           GEMM_LDS(char) *lds, int m0, int n0, int wave, int lane)
 {
+    KernelArgs p = args;
+    const int slice = item.slice;
+    if (__builtin_expect(args.whole_tiles > 0 && item.tile >= args.whole_tiles, 0)) {
+        // a slice of one of the last tiles: a partial tile of its own, packed (bases of it are multiples of 1 KiB)
+        const int64_t piece = (int64_t)slice * (args.tiles_m * args.tiles_n - args.whole_tiles) + item.tile - args.whole_tiles;
+        p.C = args.tail_ws + piece * (BM * BN) - ((int64_t)m0 * BN + n0);
+        p.ldc = BN;
+        p.split_stride = 0;
+        p.out16 = 0;
+        p.stream_c = 0;
+        p.stage_c = 1;
+    }
     constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
     const int wm = wave / WN, wn = wave % WN;
     // marks 4 and 5 of the profiling trace: all stores of this thread issued / complete
@@ -785,7 +843,7 @@ __device__ __forceinline__ void store_tile(const KernelArgs &p, const float16_t 
 }
 
 // ---------------------------------------------------------------------------
-// The kernel.  grid.x = 8 * ceil(tiles * K-slices / 8) workgroups.
+// The kernel.  grid.x = work_grid() workgroups.
 // ---------------------------------------------------------------------------
 template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool ALIGNED>
 __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs p)
@@ -810,18 +868,15 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
 
+    const int KT = (p.K + BK - 1) / BK;
     WorkItem item;
-    if (!work_item(p, item)) return;
+    if (!work_item(p, KT, item)) return;
     trace_mark(p, 0);
     trace_place(p);
-    const int slice = item.slice;
     const int m0 = item.tile_m * BM, n0 = item.tile_n * BN;
 
     // K range of this slice
-    const int KT = (p.K + BK - 1) / BK;
-    const int kt0 = slice * p.kt_per_split;
-    int kt1 = kt0 + p.kt_per_split;
-    kt1 = kt1 < KT ? kt1 : KT;
+    const int kt0 = item.kt0, kt1 = item.kt1;
     const int kend = (kt1 * BK) < p.K ? (kt1 * BK) : p.K;
 
     const T *A = (const T *)p.A;
@@ -1051,8 +1106,10 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             constexpr bool CONST_SLOTS = NW <= 4;
             const int nbody = n - 1;  // tiles 0 .. n-2 run a tile body, tile n-1 has nothing to load
             int t = 0;
-            // whole groups whose loaders stay more than two tiles before the end (tile t + 4 moves them to tile t + 7)
-            for (; CONST_SLOTS && t + NSLOT + 4 < n; t += NSLOT) {
+            // whole groups whose loaders all still advance (tile t + 4 fetches tile t + 6 < n) and, if the last slab is
+            // checked, stay more than two tiles before the end (tile t + 4 moves them to tile t + 7)
+            const int ngroup = checked ? n - 2 : n;
+            for (; CONST_SLOTS && t + NSLOT + 2 < ngroup; t += NSLOT) {
                 tile_body(std::integral_constant<int, 0>(), true);
                 tile_body(std::integral_constant<int, 2>(), true);
                 tile_body(std::integral_constant<int, 4>(), true);
@@ -1083,7 +1140,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             // straddles it (of a K-contiguous operand) are masked in registers
             const bool part = krem % EPC_ != 0;
             uint4_t mask = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-            if (part && (lane >> 5) == krem % Elem<T>::KG / EPC_) {
+            if (__builtin_expect(part, 0) && (lane >> 5) == krem % Elem<T>::KG / EPC_) {
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
                     const int in = krem % EPC_ * (int)sizeof(T) - 4 * w;  // bytes of this word inside K
@@ -1093,7 +1150,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             const GEMM_LDS(char) *cA = slot(PA), *cB = slot(PB);
             auto last_group = [&](frag_t(&ca)[FM], frag_t(&cb)[FN], frag_t(&na)[FM], frag_t(&nb)[FN], auto kg_tag) {
                 constexpr int kg = decltype(kg_tag)::value;
-                if (part && kg == krem / Elem<T>::KG) {
+                if (__builtin_expect(part, 0) && kg == krem / Elem<T>::KG) {
                     if (AKC) {
 #pragma unroll
                         for (int i = 0; i < FM; ++i) ca[i] = __builtin_bit_cast(frag_t, __builtin_bit_cast(uint4_t, ca[i]) & mask);
@@ -1103,7 +1160,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
                         for (int j = 0; j < FN; ++j) cb[j] = __builtin_bit_cast(frag_t, __builtin_bit_cast(uint4_t, cb[j]) & mask);
                     }
                 }
-                if (kg * Elem<T>::KG < krem) kgroup(ca, cb, na, nb, cA, cB, (kg + 1) % KGS, kg + 1 < KGS, no_load, L0());
+                if (__builtin_expect(kg * Elem<T>::KG < krem, 1)) kgroup(ca, cb, na, nb, cA, cB, (kg + 1) % KGS, kg + 1 < KGS, no_load, L0());
                 pin_acc();
             };
             last_group(fa[0], fb[0], fa[1], fb[1], std::integral_constant<int, 0>());
@@ -1283,7 +1340,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     }
 
     trace_mark(p, 2);
-    store_tile<BM, BN, WM, WN, NBUF * SLOT>(p, acc, lds, m0, n0, slice, wave, lane);
+    store_tile<BM, BN, WM, WN, NBUF * SLOT>(p, item, acc, lds, m0, n0, wave, lane);
 }
 
 }  // namespace gemm_gfx950

@@ -66,16 +66,13 @@ __global__ __launch_bounds__(256) void gemm_ksplit_kernel(const KernelArgs p)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
+    const int KT = p.K / BK;  // K is a multiple of the slab here
     WorkItem item;
-    if (!work_item(p, item)) return;
+    if (!work_item(p, KT, item)) return;
     const int slice = item.slice;
     const int m0 = item.tile_m * BM, n0 = item.tile_n * BN;
 
-    const int KT = p.K / BK;  // K is a multiple of the slab here
-    const int kt0 = slice * p.kt_per_split;
-    int kt1 = kt0 + p.kt_per_split;
-    kt1 = kt1 < KT ? kt1 : KT;
-    const int n = kt1 - kt0;  // slabs of this slice, at least one
+    const int kt0 = item.kt0, n = item.kt1 - kt0;  // slabs of this slice, at least one
 
     const T *A = (const T *)p.A;
     const T *B = (const T *)p.B;

@@ -183,16 +183,15 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
+    const int KT = (p.K + BK - 1) / BK;
     WorkItem item;
-    if (!work_item(p, item)) return;
+    if (!work_item(p, KT, item)) return;
     trace_mark(p, 0);
     trace_place(p);
     const int m0 = item.tile_m * BM, n0 = item.tile_n * BN;
 
     // slabs of this slice; only the operand's last one can be ragged
-    const int KT = (p.K + BK - 1) / BK;
-    const int kt0 = item.slice * p.kt_per_split;
-    const int n = (kt0 + p.kt_per_split < KT ? kt0 + p.kt_per_split : KT) - kt0;
+    const int kt0 = item.kt0, n = item.kt1 - kt0;
     const int krem = p.K - (kt0 + n - 1) * BK < BK ? p.K - (kt0 + n - 1) * BK : BK;  // k of the last slab
     const bool safe = p.safe != 0;
 
@@ -332,7 +331,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
         for (int b = 0; b < NB; ++b) multiply1(kg * NB + b);
     }
     trace_mark(p, 2);
-    store_tile<BM, BN, WM, WN, NST * STAGE>(p, acc, lds, m0, n0, item.slice, wave, lane);
+    store_tile<BM, BN, WM, WN, NST * STAGE>(p, item, acc, lds, m0, n0, wave, lane);
 }
 
 }  // namespace gemm_gfx950
