@@ -58,6 +58,7 @@ GEMM_DECLARE_STAGE(__bf16, 128, 128, 4)
 GEMM_DECLARE_SMALL(_Float16)
 GEMM_DECLARE_SMALL(__bf16)
 GEMM_DECLARE_SMALL(float)
+extern template hipError_t launch_small16<float>(bool, bool, dim3, hipStream_t, const KernelArgs &);
 }  // namespace gemm_gfx950
 
 namespace {
@@ -222,9 +223,9 @@ const TileConfig kTiles[] = {
     {"t128x256", 128, 256, 1, 0.661, 0.661, 4.19, 4.19, 4.17, 1.78, 1.25, 0.864, 2.03, 1.3, 1,
      GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
     {"t64x128", 64, 128, 2, 0.349, 0.512, 1.12, 1.86, 1.67, 1.11, 1.31, 0.884, 1.87, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.275, 1.50, 16},
+     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.29, 1.45, 16},
     {"t128x64", 128, 64, 2, 0.371, 0.617, 1.14, 1.81, 1.33, 1.06, 1.31, 0.919, 1.84, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.30, 1.6, 16},
+     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.31, 1.5, 16},
     // K split across the four waves of the workgroup (Section 5.3, small sizes); fitted on 16-byte aligned operands only
     {"k64x64", 64, 64, 4, 0.311, 0.854, 0.598, 2.02, 2.02, 0.781, 1.07, 0.992, 1.65, 1.0, 1,
      launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, 0.0, 0.0, 0},
@@ -284,12 +285,12 @@ size_t ws_bytes(int64_t splits, int64_t M, int64_t N) { return (size_t)splits * 
 // back, 96 and 240 workgroups of each tile, gemm_tile_kernel -> gemm_stage_kernel: K = 4096 26.2 -> 15.4 and 26.3 -> 16.2
 // (64x64), 26.9 -> 19.5 and 27.9 -> 22.5 (64x128), 31.2 -> 27.0 and 36.2 -> 35.0 (128x128); K = 1024 8.4 -> 6.6, 9.3 -> 8.1,
 // 10.9 -> 10.3; K = 512 4.4 -> 5.0, 5.3 -> 6.0, 7.2 -> 7.6; with a ragged K 72 .. 1544 1.03 .. 1.5 times as fast on all tiles.
-// Operands of more than 64 MiB stream from HBM, where loads further ahead gain nothing sure: 8192x128x8192 37.2 -> 34.3 on one
-// box and 40.9 -> 41.0 on another, 128x8192x8192 36.0 -> 34.3 and 36.5 -> 42.7, 776x504x26968 (69 MB) 38.8 -> 39.8;
-// 6848x256x3648 (52 MB) 26.3 -> 21.1.
+// Operands of more than 28 MiB are streamed rather than held by the caches, and there loads further ahead gain nothing sure:
+// 128x8192x8192 36.0 -> 34.3 on one card and 36.5 -> 42.7 on another, 776x504x26968 38.8 -> 39.8, 4272x96x3400 (30 MB) 15.4 -> 18.9,
+// though 6848x256x3648 (52 MB) 26.3 -> 21.1; below, 384x448x15680 (26 MB) 17.3 -> 15.7, 128x6720x1536 (21 MB) 12.0 -> 8.2.
 bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, bool ragged, int64_t operand_bytes, int num_cu)
 {
-    return t.stage16 != nullptr && workgroups <= num_cu && (ragged || slabs >= t.stage_from) && operand_bytes <= (64LL << 20);
+    return t.stage16 != nullptr && workgroups <= num_cu && (ragged || slabs >= t.stage_from) && operand_bytes <= (28LL << 20);
 }
 
 size_t tail_bytes(const TileConfig &t, int64_t sliced, int splits) { return (size_t)sliced * (size_t)splits * (size_t)(t.BM * t.BN) * sizeof(float); }
@@ -384,10 +385,7 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     double hbm_rate = resident * 1.5 * (t.BM + t.BN) * 128.0 / 0.848;  // bytes/us the workgroups keep in flight
     if (hbm_rate > 4.79e+06) hbm_rate = 4.79e+06;
     hbm_rate *= t.hbm_eff;
-    double t_hbm = unique / (hbm_rate * scale[GEMM_COST_HBM]);
-    // the stage kernel's own rate on what exceeds the caches' share: 6848x256x3648 (59 MB) 18.4 us, 256x960x19648 in eight slices
-    // (49 MB) 15.5, 128x6720x1536 (25 MB) 5.5
-    if (stage) t_hbm = std::max(t_hbm, (unique - 16e6) / (2.2e6 * scale[GEMM_COST_HBM]));
+    const double t_hbm = unique / (hbm_rate * scale[GEMM_COST_HBM]);
     const double t_l2 = (double)W * (double)per * (t.BM + t.BN) * 128.0 / (2.18e+07 * scale[GEMM_COST_L2]);
     double cost = 2.68 * scale[GEMM_COST_FIXED] + (t_mfma > t_hbm ? (t_mfma > t_l2 ? t_mfma : t_l2) : (t_hbm > t_l2 ? t_hbm : t_l2));
     if (S > 1)
@@ -770,9 +768,15 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     a.by_sliced = divisor(tiles_m * tiles_n - a.whole_tiles);
     hipError_t launch_rc;
     if (small) {
-        a.tiles_m = (int)cdiv(M, 32);
-        a.tiles_n = (int)cdiv(N, 32);
-        launch_rc = launch_small<T>(akc, bkc, dim3((unsigned)(a.tiles_m * a.tiles_n)), stream, a);
+        // binary32 in 16x16 blocks where those fit one round too and the sum is long enough to pay for four times the
+        // workgroups (microseconds per launch, 32x32 -> 16x16 blocks: 256x256 NN K = 64 2.8 -> 3.6, 136 3.2 -> 3.3, 256 3.9 -> 3.5,
+        // 512 5.9 -> 4.4; TN 256 4.4 -> 3.3; 512x512, two rounds and more, 4.1 -> 5.3)
+        const bool blocks16 = f32 && K >= 192 && cdiv(M, 16) * cdiv(N, 16) <= num_cu;
+        const int edge = blocks16 ? 16 : 32;
+        a.tiles_m = (int)cdiv(M, edge);
+        a.tiles_n = (int)cdiv(N, edge);
+        const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
+        launch_rc = blocks16 ? launch_small16<float>(akc, bkc, grid, stream, a) : launch_small<T>(akc, bkc, grid, stream, a);
     } else {
         const dim3 grid((unsigned)work_grid((int)(tiles_m * tiles_n), a.whole_tiles, a.splits));
         launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);

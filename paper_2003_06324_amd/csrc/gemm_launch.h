@@ -70,6 +70,17 @@ hipError_t launch_small(bool akc, bool bkc, dim3 grid, hipStream_t s, const Kern
     return launch_kernel(gemm_small_kernel<T, false, false>, grid, block, s, a);
 }
 
+// binary32, 16x16 blocks; a function template so that only its instantiation file compiles the kernel
+template <typename T>
+hipError_t launch_small16(bool akc, bool bkc, dim3 grid, hipStream_t s, const KernelArgs &a)
+{
+    const dim3 block(SMALL_WAVES * 64);
+    if (akc && bkc) return launch_kernel(gemm_small16_kernel<true, true>, grid, block, s, a);
+    if (akc && !bkc) return launch_kernel(gemm_small16_kernel<true, false>, grid, block, s, a);
+    if (!akc && bkc) return launch_kernel(gemm_small16_kernel<false, true>, grid, block, s, a);
+    return launch_kernel(gemm_small16_kernel<false, false>, grid, block, s, a);
+}
+
 // operands the direct loads serve (`aligned` as above)
 template <typename T, int BM, int BN, int NST>
 hipError_t launch_stage(bool akc, bool bkc, bool aligned, dim3 grid, hipStream_t s, const KernelArgs &a)

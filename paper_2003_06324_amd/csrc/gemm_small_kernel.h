@@ -98,4 +98,72 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void gemm_small_kernel(const Kern
     }
 }
 
+// The same for binary32 products of so few elements that 16x16 blocks still fit one round of CUs: four times the
+// workgroups, and a wave's sum is a quarter of the matrix-instruction time (two 16x16x4 per 8 k, 32 cycles each, where
+// four 32x32x2 take 64 each), which a product this small waits for in the open.  The waves share out K as above, in
+// groups of 8 k, so that no wave's sum is longer than there (groups of 16 raise the error of K = 333 and 400 by 3 .. 5 %).
+template <bool AKC, bool BKC>
+__global__ __launch_bounds__(SMALL_WAVES * 64) void gemm_small16_kernel(const KernelArgs p)
+{
+    constexpr int KG = Elem<float>::KG, W = SMALL_WAVES, BATCH = 4;  // two k per lane and group
+    constexpr int SW = 17;                                           // row stride of a partial block in LDS, in words
+    typedef float float2_t __attribute__((ext_vector_type(2)));
+    __shared__ float part[W][16 * SW];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile_m = blockIdx.x / p.tiles_n, tile_n = blockIdx.x - tile_m * p.tiles_n;
+    const int m0 = tile_m * 16, n0 = tile_n * 16;
+    const float *A = (const float *)p.A, *B = (const float *)p.B;
+    const int m = m0 + (lane & 15) < p.M ? m0 + (lane & 15) : p.M - 1;
+    const int n = n0 + (lane & 15) < p.N ? n0 + (lane & 15) : p.N - 1;
+    const int groups = (p.K + KG - 1) / KG, whole = p.K / KG, kl = 2 * (lane >> 4);
+
+    float4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto fragment = [&](auto kc_tag, const float *base, int64_t ld, int64_t row, int k, bool full) {
+        constexpr bool KC = decltype(kc_tag)::value;
+        typedef float2_t loose_t __attribute__((aligned(4)));
+        const float *q = KC ? base + row * ld + k : base + (int64_t)k * ld + row;
+        float2_t f;
+        if (KC && full) {
+            f = *(const loose_t *)q;
+        } else {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) f[x] = full || k + x < p.K ? q[KC ? (int64_t)x : (int64_t)x * ld] : 0.0f;
+        }
+        return f;
+    };
+    // the wave's k-groups are wave, wave + W, ...; as many as BATCH whole ones are requested together
+    auto batch = [&](auto n_tag, int g, bool full) {
+        constexpr int N = decltype(n_tag)::value;
+        float2_t fa[N], fb[N];
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+            const int k = (g + b * W) * KG + kl;
+            fa[b] = fragment(std::integral_constant<bool, AKC>(), A, p.lda, m, k, full);
+            fb[b] = fragment(std::integral_constant<bool, BKC>(), B, p.ldb, n, k, full);
+        }
+#pragma unroll
+        for (int b = 0; b < N; ++b)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[b][t], fb[b][t], acc, 0, 0, 0);
+    };
+    int g = wave;
+    for (; g + (BATCH - 1) * W < whole; g += BATCH * W) batch(std::integral_constant<int, BATCH>(), g, true);
+    static_assert(BATCH == 4, "the rest is one to three");
+    if (g + 2 * W < whole) batch(std::integral_constant<int, 3>(), g, true);
+    else if (g + W < whole) batch(std::integral_constant<int, 2>(), g, true);
+    else if (g < whole) batch(std::integral_constant<int, 1>(), g, true);
+    if (whole < groups && whole % W == wave) batch(std::integral_constant<int, 1>(), whole, false);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave][(4 * (lane >> 4) + r) * SW + (lane & 15)] = acc[r];
+    __syncthreads();
+    if (tid >= 256) return;
+    const int row = tid >> 4, col = tid & 15;
+    float s = part[0][row * SW + col];
+#pragma unroll
+    for (int w = 1; w < W; ++w) s += part[w][row * SW + col];
+    if (m0 + row < p.M && n0 + col < p.N) p.C[(int64_t)(m0 + row) * p.ldc + n0 + col] = s;
+}
+
 }  // namespace gemm_gfx950
