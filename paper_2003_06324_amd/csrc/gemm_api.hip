@@ -288,9 +288,12 @@ size_t ws_bytes(int64_t splits, int64_t M, int64_t N) { return (size_t)splits * 
 // Operands of more than 28 MiB are streamed rather than held by the caches, and there loads further ahead gain nothing sure:
 // 128x8192x8192 36.0 -> 34.3 on one card and 36.5 -> 42.7 on another, 776x504x26968 38.8 -> 39.8, 4272x96x3400 (30 MB) 15.4 -> 18.9,
 // though 6848x256x3648 (52 MB) 26.3 -> 21.1; below, 384x448x15680 (26 MB) 17.3 -> 15.7, 128x6720x1536 (21 MB) 12.0 -> 8.2.
+// Below 2.5 MiB they stay in the L2s from call to call, and the ring's one slab ahead is enough: 256x512x1024 5.8 -> 6.3,
+// 512x512x1024 5.9 -> 6.3, but 768x512x1024 8.4 -> 6.6.
 bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, bool ragged, int64_t operand_bytes, int num_cu)
 {
-    return t.stage16 != nullptr && workgroups <= num_cu && (ragged || slabs >= t.stage_from) && operand_bytes <= (28LL << 20);
+    return t.stage16 != nullptr && workgroups <= num_cu && operand_bytes <= (28LL << 20) &&
+           (ragged || (slabs >= t.stage_from && operand_bytes >= (5LL << 19)));
 }
 
 size_t tail_bytes(const TileConfig &t, int64_t sliced, int splits) { return (size_t)sliced * (size_t)splits * (size_t)(t.BM * t.BN) * sizeof(float); }

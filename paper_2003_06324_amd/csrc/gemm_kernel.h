@@ -27,8 +27,8 @@
 // swizzle is applied by choosing which global granule a lane fetches; the
 // global address of a granule needs 4-byte alignment only); for operands that
 // are only 2-byte aligned by the same granules fetched through registers and
-// written to the same positions; and for ragged K tails by guarded loads
-// through registers.  The tile of C leaves through LDS as well when its rows
+// written to the same positions, and then for ragged K tails by guarded loads
+// through registers (the direct loads are range-checked instead).  The tile of C leaves through LDS as well when its rows
 // allow 16-byte stores (see the epilogue).
 #pragma once
 #include <hip/hip_runtime.h>
