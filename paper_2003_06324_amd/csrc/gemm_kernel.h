@@ -141,13 +141,13 @@ __device__ __forceinline__ void full_sync()
 // Granule swizzle of a K-contiguous image.  A b128 fragment read has 16 consecutive lanes
 // on 16 consecutive rows at one logical granule; 16/GPR rows share a 256-byte bank period,
 // so the row index above that picks the granule position.
-__device__ __forceinline__ int swz_kc(int r) { return (r / (16 / GPR)) & (GPR - 1); }
+__host__ __device__ __forceinline__ int swz_kc(int r) { return (r / (16 / GPR)) & (GPR - 1); }
 
 // Granule swizzle of an M/N-contiguous image as a function of the k-row; CPR = granules
 // per k-row.  f16 (transposing b64 reads, 32 lanes cover 4 k-rows x 64 bytes): the four
 // rows go to four different 64-byte quarters of the bank space.  f32 (b32 reads, lanes
 // 0-31 on row k, lanes 32-63 on row k+4): the two rows go to different 128-byte halves.
-template <typename T, int CPR> __device__ __forceinline__ int swz_mc(int k)
+template <typename T, int CPR> __host__ __device__ __forceinline__ int swz_mc(int k)
 {
     if (sizeof(T) == 2) return CPR >= 16 ? ((k & 3) << 2) : (((k >> 1) & 1) << 2);
     return ((k >> 2) & 1) << 3;
@@ -176,6 +176,23 @@ struct DirectLoader {
     uint32_t off[PER_WAVE];
     int64_t step;  // bytes to advance per slab
 
+    // byte offset from the slab's base of the granule a lane fetches with its wave's load i (see init)
+    static __host__ __device__ __forceinline__ int64_t granule(int64_t ld, int row0, int rmax, int i, int wave, int lane)
+    {
+        const int j = wave + i * NW;
+        if (KC) {
+            const int r = ROWS_PER_LOAD * j + lane / GPR;
+            const int g = (lane % GPR) ^ swz_kc(r);
+            const int row = row0 + r < rmax ? r : rmax - 1 - row0;  // rows past the edge re-read the last one
+            return ((int64_t)row * ld + g * EPC) * (int64_t)sizeof(T);
+        }
+        const int q = 64 * j + lane;
+        const int kk = q / CPR;
+        int m = ((q % CPR) ^ swz_mc<T, CPR>(kk)) * EPC;
+        m = row0 + m < rmax ? m : 0;  // granules past the edge re-read the first one
+        return ((int64_t)kk * ld + m) * (int64_t)sizeof(T);
+    }
+
     // origin: operand pointer; ld: leading dimension; row0: first tile row (m or n);
     // rmax: matrix extent in that direction; k0: first k of the first slab.
     // The host guarantees that R * ld * sizeof(T) is below 2^31.
@@ -189,37 +206,29 @@ struct DirectLoader {
         rsrc[2] = 0x7fffffff;
         rsrc[3] = 0x00020000;
 #pragma unroll
-        for (int i = 0; i < PER_WAVE; ++i) {
-            const int j = wave + i * NW;
-            if (KC) {
-                const int r = ROWS_PER_LOAD * j + lane / GPR;
-                const int g = (lane % GPR) ^ swz_kc(r);
-                int row = r;
-                row = row0 + row < rmax ? row : rmax - 1 - row0;  // rows past the edge re-read the last one
-                off[i] = (uint32_t)(((int64_t)row * ld + g * EPC) * (int64_t)sizeof(T));
-            } else {
-                const int q = 64 * j + lane;
-                const int kk = q / CPR;
-                const int g = (q % CPR) ^ swz_mc<T, CPR>(kk);
-                int m = g * EPC;
-                m = row0 + m < rmax ? m : 0;  // granules past the edge re-read the first one
-                off[i] = (uint32_t)(((int64_t)kk * ld + m) * (int64_t)sizeof(T));
-            }
-        }
+        for (int i = 0; i < PER_WAVE; ++i) off[i] = (uint32_t)granule(ld, row0, rmax, i, wave, lane);
         step = (KC ? (int64_t)BK : (int64_t)BK * ld) * (int64_t)sizeof(T);
     }
 
     // end of an operand of `rmax` rows (tile direction) and `kmax` k.  The range check drops a dword that is not wholly
     // inside: an odd number of 16-bit elements is rounded up, which admits the two bytes behind the last element, in the
     // same aligned dword (the direct loads' operands are 4-byte aligned).
-    static __device__ __forceinline__ uint64_t end_of(const T *origin, int64_t ld, int rmax, int kmax)
+    static __host__ __device__ __forceinline__ uint64_t end_of(const T *origin, int64_t ld, int rmax, int kmax)
     {
         const T *e = origin + (KC ? (int64_t)(rmax - 1) * ld + kmax : (int64_t)(kmax - 1) * ld + rmax);
         return ((uint64_t)(uintptr_t)e + 3) & ~(uint64_t)3;
     }
-    // Before the loads of the operand's last slab, of which `krem` k lie inside: the descriptor's range ends with the
-    // operand, so that k-rows past K, and what a granule reaches past the operand's end, read as zeros; lanes whose whole
-    // granule of a K-contiguous row lies past K load from outside the range.
+    // Whether a granule of a slice's last slab, behind which the operand has `behind` more k (none or less: it is the
+    // operand's last slab), can reach past the operand's end: one that straddles the edge in the tile direction and has
+    // fewer elements than a granule in the k-rows behind it.  (A vector of K = 577 with ld = 1 in slices of 96 k: the last
+    // slice has one k, and the granule of k = 575 covers 575 .. 578.)
+    static __host__ __device__ __forceinline__ bool reaches_end(int64_t ld, int row0, int rmax, int behind)
+    {
+        return !KC && rmax % EPC != 0 && row0 + R > rmax && behind * ld < EPC;
+    }
+    // Before the loads of one of a slice's last two slabs, of which `krem` k lie inside the operand: the descriptor's range
+    // ends with the operand, so that k-rows past K, and what a granule reaches past the operand's end, read as zeros; lanes
+    // whose whole granule of a K-contiguous row lies past K load from outside the range.
     __device__ __forceinline__ void last_slab(uint64_t end, int krem, int wave, int lane)
     {
         const uint64_t left = end - (((uint64_t)(uint32_t)rsrc[1] << 32) | (uint32_t)rsrc[0]);
@@ -983,16 +992,17 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
         // stored).  Towards the operand's end the loads are range-checked against it (last_slab), so that
         // the last slab may be ragged and the last k-row's granules may straddle its end: a slab left to
         // guarded loads of its own would be fetched, staged and multiplied in the open, 2.3 .. 2.8 slab
-        // times.  The range is exact from two slabs before the end on, because with a leading dimension
-        // below the granule it covers up to four k-rows.
+        // times.  The range is exact from two slabs before the end on, and in the slice before the operand's last slab
+        // too if that slab is short, because with a leading dimension below the granule it covers up to four k-rows
+        // (reaches_end).
         const int n = kt1 - kt0;
-        const bool ends = kt1 == KT;                                // this slice holds the operand's last slab
-        const int krem = ends ? p.K - (kt1 - 1) * BK : BK;          // k of the slice's last slab
-        // whether its loads have to be checked
-        const bool checked = ends && (krem < BK || (!AKC && p.M % EPC_ != 0 && m0 + BM > p.M) || (!BKC && p.N % EPC_ != 0 && n0 + BN > p.N));
+        const int behind = p.K - kt1 * BK;                          // k of the operand behind this slice's slabs
+        const int krem = behind < 0 ? BK + behind : BK;             // k of the slice's last slab
         {
             DirectLoader<T, BM, NW, AKC> la;
             DirectLoader<T, BN, NW, BKC> lb;
+            // whether its loads have to be checked
+            const bool checked = krem < BK || la.reaches_end(p.lda, m0, p.M, behind) || lb.reaches_end(p.ldb, n0, p.N, behind);
             la.init(A, p.lda, m0, p.M, k_done, wave, lane);
             lb.init(B, p.ldb, n0, p.N, k_done, wave, lane);
             // The slot numbers repeat every NSLOT tiles, so the loop over tiles is unrolled

@@ -41,6 +41,20 @@ struct StageLoader {
     int64_t step;   // bytes to advance per slab
     uint64_t end;   // address of the operand's end
 
+    // byte offset from the slab's origin of the granule a lane fetches with its wave's load i
+    static __host__ __device__ __forceinline__ int64_t granule(int64_t ld, int row0, int rmax, int i, int wave, int lane)
+    {
+        const int j = wave * PER_WAVE + i;
+        if (KC) {
+            const int r = ROWS_PER_LOAD * j + lane / GPR;
+            const int g = (lane % GPR) ^ swz_kc(r);
+            return ((int64_t)(row0 + r < rmax ? r : rmax - 1 - row0) * ld + g * EPC) * (int64_t)sizeof(T);  // rows past the edge re-read the last one
+        }
+        const int q = 64 * j + lane;
+        const int kk = q / CPR;
+        const int m = ((q % CPR) ^ swz_mc<T, CPR>(kk)) * EPC;
+        return ((int64_t)kk * ld + (row0 + m < rmax ? m : 0)) * (int64_t)sizeof(T);  // granules past the edge re-read the first one
+    }
     // kmax: the operand's extent in k (of the whole operand, not of this K-slice); the rest as DirectLoader::init
     __device__ __forceinline__ void init(const T *origin, int64_t ld, int row0, int rmax, int kmax, int k0, int wave, int lane)
     {
@@ -50,26 +64,9 @@ struct StageLoader {
         rsrc[2] = 0x7fffffff;
         rsrc[3] = 0x00020000;
 #pragma unroll
-        for (int i = 0; i < PER_WAVE; ++i) {
-            const int j = wave * PER_WAVE + i;
-            int64_t at;
-            if (KC) {
-                const int r = ROWS_PER_LOAD * j + lane / GPR;
-                const int g = (lane % GPR) ^ swz_kc(r);
-                at = (int64_t)(row0 + r < rmax ? r : rmax - 1 - row0) * ld + g * EPC;  // rows past the edge re-read the last one
-            } else {
-                const int q = 64 * j + lane;
-                const int kk = q / CPR;
-                const int m = ((q % CPR) ^ swz_mc<T, CPR>(kk)) * EPC;
-                at = (int64_t)kk * ld + (row0 + m < rmax ? m : 0);  // granules past the edge re-read the first one
-            }
-            off[i] = (uint32_t)(at * (int64_t)sizeof(T)) + LEAD - i % GROUP * 1024;
-        }
+        for (int i = 0; i < PER_WAVE; ++i) off[i] = (uint32_t)granule(ld, row0, rmax, i, wave, lane) + LEAD - i % GROUP * 1024;
         step = (KC ? (int64_t)BK : (int64_t)BK * ld) * (int64_t)sizeof(T);
-        end = (uint64_t)(uintptr_t)(origin + (KC ? (int64_t)(rmax - 1) * ld + kmax : (int64_t)(kmax - 1) * ld + rmax));
-        // The check drops a dword that is not wholly inside: an odd number of 16-bit elements is rounded up, which
-        // admits the two bytes behind the last element, in the same aligned dword.
-        end = (end + 3) & ~(uint64_t)3;
+        end = DirectLoader<T, R, NW, KC>::end_of(origin, ld, rmax, kmax);
     }
     // load i of this wave to wave_dst + i KiB (LDS address); with i in order, M0 is set by the first of a group
     __device__ __forceinline__ void issue(uint32_t wave_dst, int i) const
