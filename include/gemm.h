@@ -21,8 +21,9 @@
  *   at r + c*ld (indices in elements).  ld == 0 means packed (row-major: number
  *   of columns, column-major: number of rows); otherwise ld must be at least
  *   that value.  Elements between the packed extent and ld are never written.
- *   Those of A and B may be read (nothing past an operand's last element is),
- *   but their values, NaN included, never influence C.  Pointers need only
+ *   Those of A and B may be read, but their values, NaN included, never influence
+ *   C.  Nothing past an operand's last element is read, except that the 4-byte aligned
+ *   word holding a last 16-bit element is read whole.  Pointers need only
  *   element alignment.  Bases and leading dimensions that are multiples of 4
  *   bytes (always the case for binary32) take the direct-load kernels, multiples
  *   of 16 bytes make them fastest; 16-bit operands that are only 2-byte aligned
