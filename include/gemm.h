@@ -53,12 +53,15 @@
  *   be recorded into a HIP graph only once its stream's workspace has reached
  *   the size it needs, e.g. after the same call was made once outside the
  *   capture; calls that use no K-slices only launch kernels and can always be
- *   captured.  Large products whose last round of tiles fills at most half of the
- *   chip cut those tiles into K-slices in the same workspace (64 MiB at most); without
- *   one -- a capture before it has grown, no memory left -- they run them whole, so such
- *   calls can always be captured too, with the other order of summation in the last tiles.
- *   gemm_last_config then says "tail" and the number of slices; a slice count forced by
- *   name ("t256x256:s1") is taken for all tiles.  gemm_f16f32_noalloc never allocates.
+ *   captured.  Replays of a graph that holds a K-sliced call use the workspace of the
+ *   stream it was captured on: order them with that stream's other K-sliced work and
+ *   with each other.  Large products whose last round of tiles fills at most half of the
+ *   chip cut those tiles into K-slices in the same workspace (64 MiB at most; gemm_last_config
+ *   then says "tail" and the number of slices); without one -- no memory left -- and always
+ *   while being captured they run them whole, so such a graph can be replayed on any stream,
+ *   with the other order of summation in the last tiles.  A slice count forced by name
+ *   ("t256x256:s1") is taken for all tiles.  gemm_f16f32_noalloc never allocates, and uses
+ *   its fixed array under capture as well.
  *
  * Sizes
  *   M, N, K >= 0 and each below 2^31 - 256.  M == 0 or N == 0: nothing is

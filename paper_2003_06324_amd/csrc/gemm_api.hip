@@ -558,28 +558,22 @@ int get_workspace(DeviceState &d, hipStream_t stream, size_t bytes, void **out)
     return GEMM_OK;
 }
 
-// The same for the partial tiles of a last round, which a launch can do without: nothing is allocated while the stream is
-// being captured (nor may a capture elsewhere in the process mind), and failing is no error.
+// The same for the partial tiles of a last round, which a launch can do without: failing is no error, and a stream under
+// capture has none, also where its workspace would do.  A graph that took it would share it with whatever its stream runs
+// later, and with other graphs captured on that stream, whatever streams they are replayed on.  (Nor may a capture
+// elsewhere in the process mind an allocation.)
 bool get_tail_workspace(DeviceState &d, hipStream_t stream, size_t bytes, void **out)
 {
-    const auto it = d.ws.find(stream);
-    if (it == d.ws.end() || it->second.bytes < bytes) {
-        hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
-        if (hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return false;
-        }
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
-        const int rc = get_workspace(d, stream, bytes, out);
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        return rc == GEMM_OK;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone ||
+        hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
     }
-    *out = it->second.ptr;
-    return true;
+    const int rc = get_workspace(d, stream, bytes, out);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return rc == GEMM_OK;
 }
 
 // device address of this GPU's copy of `scratch` (g_mutex held); looked up once per device

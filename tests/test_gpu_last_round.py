@@ -73,3 +73,39 @@ def test_the_fixed_array_and_streams_without_a_workspace():
             assert torch.equal(C, A.float() @ B.float())
     finally:
         g.force_config(None)
+
+
+def test_a_captured_call_leaves_its_streams_workspace_alone():
+    """Also where the workspace is large enough: the graph touches A, B and C only, so replays on another stream beside
+    sliced calls on the stream it was captured on keep their results."""
+    import torch
+    import paper_2003_06324_amd as g
+    M, N, K = 17 * 256, 16 * 256, 2048
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    A = torch.randint(-4, 5, (M, K), device="cuda", generator=gen).half()
+    B = torch.randint(-4, 5, (K, N), device="cuda", generator=gen).half()
+    A2, C2 = -A, torch.empty(M, N, device="cuda")
+    ref = A.float() @ B.float()
+    C = torch.empty(M, N, device="cuda")
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g.force_config("t256x256")
+    try:
+        g.gemm_f16f32(M, N, K, A2, 0, 0, B, 0, 0, C2, 0, 0, side.cuda_stream)   # the workspace grows
+        assert " tail" in g.last_config()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            g.gemm_f16f32(M, N, K, A, 0, 0, B, 0, 0, C, 0, 0, side.cuda_stream)
+        assert " tail" not in g.last_config(), g.last_config()
+        for _ in range(4):
+            C.zero_()
+            C2.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(other):
+                graph.replay()
+            g.gemm_f16f32(M, N, K, A2, 0, 0, B, 0, 0, C2, 0, 0, side.cuda_stream)
+            assert " tail" in g.last_config()
+            torch.cuda.synchronize()
+            assert torch.equal(C, ref) and torch.equal(C2, -ref)
+    finally:
+        g.force_config(None)
