@@ -45,9 +45,10 @@
  *   default stream) of the current device.  The call does not synchronise with
  *   the host, on any path.  Shapes that are split along K keep their partial
  *   sums in a workspace that belongs to the (device, stream) pair: calls on
- *   different streams never share one, calls on one stream are ordered by the
- *   stream, and host threads that share a stream are serialised by the library
- *   for the duration of the launches.  A workspace that is too small is
+ *   different streams never share one (hipStreamPerThread is a stream of its own
+ *   in every thread), calls on one stream are ordered by the stream, and host
+ *   threads that share a stream are serialised by the library for the duration
+ *   of the launches.  A workspace that is too small is
  *   replaced by a larger one with hipMalloc (the old one is kept until
  *   gemm_shutdown(), since earlier work may still use it), so such a call can
  *   be recorded into a HIP graph only once its stream's workspace has reached

@@ -537,7 +537,8 @@ int device_state(DeviceState **out)
 // workspace of (current device, stream), at least `bytes` long (g_mutex held)
 int get_workspace(DeviceState &d, hipStream_t stream, size_t bytes, void **out)
 {
-    Workspace &w = d.ws[stream];
+    static thread_local char own_thread;  // hipStreamPerThread names another stream in every thread
+    Workspace &w = d.ws[stream == hipStreamPerThread ? (hipStream_t)&own_thread : stream];
     if (w.bytes < bytes) {
         const size_t want = bytes > 2 * w.bytes ? bytes : 2 * w.bytes;
         void *p = nullptr;

@@ -109,3 +109,38 @@ def test_a_captured_call_leaves_its_streams_workspace_alone():
             assert torch.equal(C, ref) and torch.equal(C2, -ref)
     finally:
         g.force_config(None)
+
+
+@pytest.mark.parametrize("force", ["t256x256", "t128x128:s4"])
+def test_threads_on_their_own_per_thread_streams_do_not_share_a_workspace(force):
+    """hipStreamPerThread (the handle 2) names another stream in every thread: sliced calls of two threads overlap on the GPU."""
+    import threading
+    import torch
+    import paper_2003_06324_amd as g
+    M, N, K = (17 * 256, 16 * 256, 2048) if force == "t256x256" else (1024, 1024, 4096)
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    B = torch.randint(-4, 5, (K, N), device="cuda", generator=gen).half()
+    A = [torch.randint(-4, 5, (M, K), device="cuda", generator=gen).half() for _ in range(2)]
+    C = [torch.zeros(8, M, N, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    g.force_config(force)
+    configs = []
+
+    def work(i):
+        for c in C[i]:
+            g.gemm_f16f32(M, N, K, A[i], 0, 0, B, 0, 0, c, 0, 0, 2)
+        configs.append(g.last_config())
+        torch.cuda.synchronize()
+
+    try:
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    finally:
+        g.force_config(None)
+    assert len(configs) == 2 and all(" tail" in c or " s4" in c for c in configs), configs
+    for i in range(2):
+        ref = A[i].float() @ B.float()
+        assert all(torch.equal(c, ref) for c in C[i])
