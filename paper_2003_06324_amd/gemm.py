@@ -18,7 +18,7 @@ _lib = None
 try:
     from . import _binding   # built with the library (build.py)
 except ImportError:
-    _binding = None          # the ctypes functions below serve every call
+    _binding = None          # the ctypes functions below serve every call (also in a process that builds it on first use)
 
 EXPORTS = ("gemm_f32", "gemm_f16f32", "gemm_f16f16", "gemm_bf16f32", "gemm_f16f32_noalloc", "gemm_cost_model_scale", "gemm_set_phase_trace", "gemm_force_config", "gemm_query_config", "gemm_query_config_layouts", "gemm_tune", "gemm_tune_clear", "gemm_tune_save", "gemm_tune_load", "gemm_num_configs", "gemm_config_name",
            "gemm_last_config", "gemm_status_string", "gemm_shutdown")

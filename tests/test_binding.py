@@ -61,3 +61,19 @@ def test_whole_numbers_beyond_the_c_types_go_the_general_way():
     big = (2 ** 63, 1, 1, 16, 0, 0, 16, 0, 0, 16, 0, 0)
     assert g.gemm_f32(*big, None, False) == _general("gemm_f32")(*big, check=False)
     assert g.gemm_f32(True, 0, True, 16, False, 0, 16, 0, 0, 16, 0, 0) == 0
+
+
+@pytest.mark.parametrize("compiler", ["false", "/no/such/compiler"])
+def test_the_library_is_built_without_a_compiler_for_the_extension(monkeypatch, tmp_path, compiler):
+    from paper_2003_06324_amd import build
+    built = []
+    monkeypatch.setenv("CXX", compiler)
+    monkeypatch.setattr(build, "OBJDIR", str(tmp_path))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "BINDING", str(tmp_path / "ext.so"))
+    monkeypatch.setattr(build, "_compile", lambda src, force: built.append(src) or src)
+    monkeypatch.setattr(build, "HIPCC", "true")
+    monkeypatch.setattr(build.os, "replace", lambda a, b: open(b, "w").close())
+    with pytest.warns(UserWarning, match="extension was not built"):
+        assert build.build() == str(tmp_path / "lib.so")
+    assert built == build.sources()
