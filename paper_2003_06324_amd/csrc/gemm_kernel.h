@@ -851,10 +851,20 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args, const WorkIte
     trace_stores();
 }
 
+// How gemm_tile_kernel fetches its operands: through registers, by direct loads, by direct loads that are checked against
+// the operand's end.
+enum class Loads { STAGED, DIRECT, CHECKED };
+// Whether direct loads of this product can reach past an operand's end: a ragged last slab, or granules over the edge of an
+// M/N-contiguous operand.
+template <typename T> inline bool checks_loads(bool akc, bool bkc, int M, int N, int K)
+{
+    return K % Elem<T>::BK != 0 || (!akc && M % Elem<T>::EPC != 0) || (!bkc && N % Elem<T>::EPC != 0);
+}
+
 // ---------------------------------------------------------------------------
 // The kernel.  grid.x = work_grid() workgroups.
 // ---------------------------------------------------------------------------
-template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool ALIGNED>
+template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC, Loads LOADS>
 __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs p)
 {
     constexpr int NW = WM * WN, NT = NW * 64;
@@ -863,6 +873,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be built from 32x32 blocks");
     constexpr int A_BYTES = BM * RBK, B_BYTES = BN * RBK;
     constexpr int SLOT = A_BYTES > B_BYTES ? A_BYTES : B_BYTES;  // one operand slab
+    constexpr bool ALIGNED = LOADS != Loads::STAGED, CHECKED = LOADS == Loads::CHECKED;
     constexpr int NBUF = ALIGNED ? NSLOT : 4;  // ring of five operand slots, or two buffers of (A, B)
     typedef typename Frag<T>::type frag_t;
     constexpr int NVA = A_BYTES / 1024 / NW;  // direct loads per wave per A slab
@@ -994,15 +1005,18 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
         // guarded loads of its own would be fetched, staged and multiplied in the open, 2.3 .. 2.8 slab
         // times.  The range is exact from two slabs before the end on, and in the slice before the operand's last slab
         // too if that slab is short, because with a leading dimension below the granule it covers up to four k-rows
-        // (reaches_end).
+        // (reaches_end).  Checks and masks that find nothing to do cost a launch 0.1 .. 0.4 us all the same, in code that runs
+        // once (binary16, one round of 64x64 tiles, K = 64 .. 448, A alone K-contiguous 4.05 -> 3.74 us without; 128x128, both
+        // K-contiguous 5.54 -> 5.27; three rounds of 128x256 32.7 -> 32.2), so a product that cannot need them (checks_loads)
+        // runs a kernel of its own.
         const int n = kt1 - kt0;
         const int behind = p.K - kt1 * BK;                          // k of the operand behind this slice's slabs
-        const int krem = behind < 0 ? BK + behind : BK;             // k of the slice's last slab
+        const int krem = CHECKED && behind < 0 ? BK + behind : BK;  // k of the slice's last slab
         {
             DirectLoader<T, BM, NW, AKC> la;
             DirectLoader<T, BN, NW, BKC> lb;
             // whether its loads have to be checked
-            const bool checked = krem < BK || la.reaches_end(p.lda, m0, p.M, behind) || lb.reaches_end(p.ldb, n0, p.N, behind);
+            const bool checked = CHECKED && (krem < BK || la.reaches_end(p.lda, m0, p.M, behind) || lb.reaches_end(p.ldb, n0, p.N, behind));
             la.init(A, p.lda, m0, p.M, k_done, wave, lane);
             lb.init(B, p.ldb, n0, p.N, k_done, wave, lane);
             // The slot numbers repeat every NSLOT tiles, so the loop over tiles is unrolled
@@ -1145,7 +1159,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
             // a product whose slabs are whole)
             const int nplain = checked ? n - 5 : nbody;
             for (; t < nplain; ++t) tile_rest(std::false_type());
-            for (; t < nbody; ++t) tile_rest(std::true_type());
+            if constexpr (CHECKED)
+                for (; t < nbody; ++t) tile_rest(std::true_type());
             // the last tile, up to the k-group that holds the last k; the elements past K in the granule that
             // straddles it (of a K-contiguous operand) are masked in registers
             const bool part = krem % EPC_ != 0;
@@ -1171,7 +1186,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
                     }
                 }
                 if (__builtin_expect(kg * Elem<T>::KG < krem, 1)) kgroup(ca, cb, na, nb, cA, cB, (kg + 1) % KGS, kg + 1 < KGS, no_load, L0());
-                pin_acc();
+                if constexpr (CHECKED) pin_acc();
             };
             last_group(fa[0], fb[0], fa[1], fb[1], std::integral_constant<int, 0>());
             last_group(fa[1], fb[1], fa[0], fb[0], std::integral_constant<int, 1>());

@@ -23,11 +23,12 @@ static void walk(int extent, int64_t ld, int K, int per)
     const uint64_t allowed = (last + 3) & ~(uint64_t)3;
     const uint64_t end = Ring::end_of(origin, ld, extent, K);
     const int KT = (K + BK - 1) / BK;
+    const bool checks = checks_loads<T>(KC, true, extent, 1, K);  // else the kernel without checks runs
     for (int row0 = 0; row0 < extent; row0 += R)
         for (int kt0 = 0; kt0 < KT; kt0 += per) {
             const int kt1 = std::min(kt0 + per, KT), n = kt1 - kt0;
             const int behind = K - kt1 * BK, krem = behind < 0 ? BK + behind : BK;
-            const bool checked = STAGE || krem < BK || Ring::reaches_end(ld, row0, extent, behind);
+            const bool checked = STAGE || (checks && (krem < BK || Ring::reaches_end(ld, row0, extent, behind)));
             for (int h = 0; h < n; ++h) {
                 const int k0 = (kt0 + h) * BK;
                 const uint64_t base = (uint64_t)(uintptr_t)(KC ? origin + row0 * ld + k0 : origin + k0 * ld + row0);
