@@ -700,7 +700,10 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args, const WorkIte
 #pragma unroll
                 for (int it = 0; it < 32 / RPI; ++it) {
                     const GEMM_LDS(float) *src = stage + (it * RPI + srow) * SW + spiece * WPL;
-                    const int soff = (i * 32 + it * RPI) * ldcb;
+                    // The row offset goes into the vector offset: a store of more than 64 bits reads its data registers up to two
+                    // issue slots late, and the compiler keeps those slots free of writes to them only where the store has
+                    // no scalar offset (a next band's accumulator was moved into them at once, and got stored instead).
+                    const int off = voff + (i * 32 + it * RPI) * ldcb;
                     if constexpr (O16) {
                         const float4_t lo = *(const GEMM_LDS(float4_t) *)src;
                         const float4_t hi = *(const GEMM_LDS(float4_t) *)(src + 4);
@@ -710,10 +713,10 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args, const WorkIte
                             h[x] = (_Float16)lo[x];
                             h[4 + x] = (_Float16)hi[x];
                         }
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, h), rsrc, voff, soff, POLICY);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, h), rsrc, off, 0, POLICY);
                     } else {
                         const float4_t v = *(const GEMM_LDS(float4_t) *)src;
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), rsrc, voff, soff, POLICY);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), rsrc, off, 0, POLICY);
                     }
                 }
             }
