@@ -284,7 +284,8 @@ const char *gemm_config_name(int i);
 /*
  * Description of the configuration the last successful call on this thread
  * used, e.g. "f16 t256x256 NT aligned s1"; " small" at the end: the kernel for
- * small products ran (see gemm_query_config).  The string is thread-local storage
+ * small products ran (see gemm_query_config); " stage": the tile kernel for launches
+ * of at most one workgroup per CU.  The string is thread-local storage
  * owned by the library, valid until the thread's next gemm call.
  */
 const char *gemm_last_config(void);

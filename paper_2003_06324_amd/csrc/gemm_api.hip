@@ -268,6 +268,7 @@ struct LastCall {
     bool akc = false, bkc = false, small = false, safe = false, fixed_scratch = false;
     const char *path = nullptr;
     int splits = 0, tail = 0;  // tail: K-slices of the last tiles
+    bool stage = false;        // gemm_stage_kernel
 };
 thread_local LastCall t_last;
 thread_local char t_last_config[128];
@@ -765,6 +766,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     a.by_last_rows = divisor(tiles_m % GM > 0 ? tiles_m % GM : 1);
     a.by_sliced = divisor(tiles_m * tiles_n - a.whole_tiles);
     hipError_t launch_rc;
+    bool stage = false;
     if (small) {
         // binary32 in 16x16 blocks where those fit one round too and the sum is long enough to pay for four times the
         // workgroups (microseconds per launch, 32x32 -> 16x16 blocks: 256x256 NN K = 64 2.8 -> 3.6, 136 3.2 -> 3.3, 256 3.9 -> 3.5,
@@ -778,7 +780,8 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     } else {
         const dim3 grid((unsigned)work_grid((int)(tiles_m * tiles_n), a.whole_tiles, a.splits));
         launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
-        if (!f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, ragged || K % BK != 0, (M + N) * K * (int64_t)sizeof(T), num_cu)) fn = bf16 ? t.stage_bf16 : t.stage16;
+        stage = !f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, ragged || K % BK != 0, (M + N) * K * (int64_t)sizeof(T), num_cu);
+        if (stage) fn = bf16 ? t.stage_bf16 : t.stage16;
         launch_rc = fn(akc, bkc, aligned, grid, stream, a);
     }
     if (launch_rc != hipSuccess) {
@@ -802,7 +805,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         if (rc != hipSuccess) return GEMM_ERR_HIP;
     }
     t_last = LastCall{type_name, nullptr, t.name, akc, bkc, small, a.safe != 0, noalloc && a.splits > 1,
-                      aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, a.whole_tiles > 0 ? a.splits : 0};
+                      aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, a.whole_tiles > 0 ? a.splits : 0, stage};
     return GEMM_OK;
 }
 
@@ -1164,8 +1167,9 @@ const char *gemm_last_config(void)
     if (l.special != nullptr)
         snprintf(t_last_config, sizeof t_last_config, "%s %s", l.type, l.special);
     else
-        snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s%s", l.type, l.tile, l.akc ? 'N' : 'T', l.bkc ? 'T' : 'N', l.path,
-                 l.splits, l.small ? " small" : "", l.safe ? " safe" : "", tail, l.fixed_scratch ? " static-scratch" : "");
+        snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s%s%s", l.type, l.tile, l.akc ? 'N' : 'T', l.bkc ? 'T' : 'N', l.path,
+                 l.splits, l.small ? " small" : "", l.safe ? " safe" : "", tail, l.fixed_scratch ? " static-scratch" : "",
+                 l.stage ? " stage" : "");
     return t_last_config;
 }
 

@@ -1,5 +1,5 @@
 """Small binary32 products in 16x16 blocks: the limits of the choice (K = 192, one block per CU), every remainder of the
-blocks and of the groups of 16 k that sixteen waves share out."""
+blocks and of the groups of 8 k that sixteen waves share out."""
 import numpy as np
 import pytest
 

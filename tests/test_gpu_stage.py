@@ -28,16 +28,50 @@ def test_exact_on_whole_numbers_at_every_remainder(oracle, tile, dtype):
             pads = ((K if la == 0 else M) % 2, (N if lb == 0 else K) % 2 + 2 * (n % 2), 0)
             for slices in (1, 3):
                 C, cfg = run_gpu(dtype, A, B, la, lb, lc=0, pads=pads, force="%s:s%d" % (tile, slices), return_config=True)
-                assert "aligned" in cfg, cfg
+                assert "aligned" in cfg and (K % 64 == 0 or cfg.endswith(" stage")), cfg
                 assert np.array_equal(C.astype(np.float64), ref), (M, N, K, la, lb, slices, cfg)
+
+
+# whole slabs of operands that do not stay in the L2s: the fewest slabs it takes, and each number of them modulo its stages
+@pytest.mark.parametrize("tile", sorted(TILES))
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_exact_on_whole_slabs(oracle, tile, dtype):
+    bm, bn = TILES[tile]
+    fewest = 24 if tile == "t128x128" else 16
+    for n in range(7):
+        slices = 1 + n % 2
+        K = 64 * ((fewest + n) * slices - n % 2)   # two slices: the second one slab shorter
+        M, N = ((9 * bm, 14 * bn), (600, 744), (1000, 320), (8, 1400))[n % 4]   # (whole tiles, and whole granules over their edges)
+        assert (M + N) * K * 2 >= 5 << 19
+        A, B = gi.make_problem(2200 + K, M, N, K, "int", dtype)
+        bits = (gi.bfloat16_bits(A), gi.bfloat16_bits(B)) if dtype == "bf16" else (A, B)
+        ref = oracle.gemm(M, N, K, bits[0], 0, bits[1], 0, dtype)
+        for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+            C, cfg = run_gpu(dtype, A, B, la, lb, lc=0, pads=(8 * (n % 2), 4 * (n % 3), 0), force="%s:s%d" % (tile, slices), return_config=True)
+            assert cfg.endswith(" s%d stage" % slices), cfg
+            assert np.array_equal(C.astype(np.float64), ref), (M, N, K, la, lb, slices, cfg)
+
+
+def test_where_it_runs():
+    """The limits of the choice: workgroups, slabs, bytes of the operands; never in binary32 or on 2-byte aligned rows."""
+    def ran(M, N, K, dtype="f16", force="t64x64:s1", pad=0):
+        A, B = np.zeros((M, K), np.float32 if dtype == "f32" else np.float16), np.zeros((K, N), np.float32 if dtype == "f32" else np.float16)
+        return run_gpu(dtype, A, B, 0, 1, pads=(pad, pad, 0), force=force, return_config=True)[1].endswith(" stage")
+    assert ran(1024, 1024, 1024) and not ran(1024, 1088, 1024)           # 256 workgroups, 272
+    assert not ran(1024, 1024, 960) and ran(1024, 1024, 968)             # 15 slabs; the ragged 16th
+    assert not ran(640, 600, 1024) and ran(640, 648, 1024)               # 2.42 MiB, 2.52
+    assert ran(256, 256, 28600) and not ran(256, 256, 28736)             # 27.9 MiB, 28.1
+    assert not ran(1024, 1024, 1024, "f32") and not ran(1024, 1024, 1024, pad=1)
+    assert not ran(512, 512, 2048, force="t256x256:s1")                  # no such kernel for the tile
 
 
 @pytest.mark.parametrize("tile", sorted(TILES))
 def test_same_bits_as_the_register_staged_kernel(tile):
     bm, bn = TILES[tile]
-    for M, N, K in ((2 * bm, bn, 1000), (bm + 5, 3 * bn - 7, 1029), (3 * bm, 2 * bn, 2048)):
+    for M, N, K in ((2 * bm, bn, 1000), (bm + 5, 3 * bn - 7, 1029), (7 * bm, 9 * bn, 3072)):
         A, B = gi.make_problem(M + K, M, N, K, "normal", "f16")
         for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
             pads = ((K if la == 0 else M) % 2, (N if lb == 0 else K) % 2, 0)
-            runs = [run_gpu("f16", A, B, la, lb, pads=pads, force="%s:s2%s" % (tile, how)) for how in ("", ":safe", ":regload")]
+            runs, cfgs = zip(*(run_gpu("f16", A, B, la, lb, pads=pads, force="%s:s2%s" % (tile, how), return_config=True) for how in ("", ":safe", ":regload")))
+            assert [cfg.endswith(" stage") for cfg in cfgs] == [True, True, False], cfgs
             assert np.array_equal(runs[0], runs[1]) and np.array_equal(runs[0], runs[2]), (M, N, K, la, lb)
