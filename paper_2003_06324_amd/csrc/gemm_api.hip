@@ -195,6 +195,7 @@ struct TileConfig {
     launch_fn stage16, stage_bf16;  // gemm_stage_kernel (null: none), see runs_stage
     double stage_slab, stage_a4;    // its slab time (microseconds per 64 k, one workgroup on a CU), on 4-/8-byte aligned operands over that
     int stage_from;                 // slabs from which it is ahead on whole ones
+    int stage_most;                 // sixteenths of the CUs up to which it is ahead on whole slabs of 16-byte rows
 };
 
 #define GEMM_TILE_LAUNCHERS(BM, BN, WM, WN) \
@@ -211,24 +212,24 @@ struct TileConfig {
 // (64x128 before 128x64: the model often ties the two, and the tie goes to the first; 64x128 measures 4-8 % ahead)
 const TileConfig kTiles[] = {
     {"t256x256", 256, 256, 1, 1.02, 1.02, 6.98, 6.98, 7.2, 0.83, 1.2, 1.05, 1.67, 1.25, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0, 0},
     {"t128x128", 128, 128, 2, 0.457, 0.868, 1.99, 3.64, 1.92, 1.39, 1.23, 0.817, 1.57, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.41, 1.40, 24},
+     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.41, 1.40, 24, 15},
     {"t64x64", 64, 64, 4, 0.265, 0.855, 0.495, 1.86, 1.27, 0.78, 1.07, 0.992, 1.65, 1.35, 4,
-     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.21, 1.48, 16},
+     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.21, 1.48, 16, 16},
     {"t256x256w8", 256, 256, 1, 1.05, 1.05, 7.6, 7.6, 6.02, 0.812, 1.2, 0.915, 1.35, 1.15, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0, 0},
     {"t256x128", 256, 128, 1, 0.71, 0.71, 3.52, 3.52, 3.82, 0.637, 1.2, 1.09, 1.47, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
+     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0, 0},
     {"t128x256", 128, 256, 1, 0.661, 0.661, 4.19, 4.19, 4.17, 1.78, 1.25, 0.864, 2.03, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0},
+     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, 0.0, 0.0, 0, 0},
     {"t64x128", 64, 128, 2, 0.349, 0.512, 1.12, 1.86, 1.67, 1.11, 1.31, 0.884, 1.87, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.29, 1.45, 16},
+     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.29, 1.45, 16, 16},
     {"t128x64", 128, 64, 2, 0.371, 0.617, 1.14, 1.81, 1.33, 1.06, 1.31, 0.919, 1.84, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.31, 1.5, 16},
+     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.31, 1.5, 16, 16},
     // K split across the four waves of the workgroup (Section 5.3, small sizes); fitted on 16-byte aligned operands only
     {"k64x64", 64, 64, 4, 0.311, 0.854, 0.598, 2.02, 2.02, 0.781, 1.07, 0.992, 1.65, 1.0, 1,
-     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, 0.0, 0.0, 0},
+     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, 0.0, 0.0, 0, 0},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -281,20 +282,29 @@ int64_t ws_pitch(int64_t N) { return cdiv(N, 32) * 32; }
 size_t ws_bytes(int64_t splits, int64_t M, int64_t N) { return (size_t)splits * (size_t)M * (size_t)ws_pitch(N) * sizeof(float); }
 
 // Whether a launch on direct loads (16-bit operands, load path 0 or 3) runs gemm_stage_kernel: at most one workgroup per CU,
-// and enough slabs to pay for its longer start, 0.5 us, or a ragged last slab (which gemm_tile_kernel left to guarded loads
-// when this was measured).  Microseconds per launch back to
-// back, 96 and 240 workgroups of each tile, gemm_tile_kernel -> gemm_stage_kernel: K = 4096 26.2 -> 15.4 and 26.3 -> 16.2
-// (64x64), 26.9 -> 19.5 and 27.9 -> 22.5 (64x128), 31.2 -> 27.0 and 36.2 -> 35.0 (128x128); K = 1024 8.4 -> 6.6, 9.3 -> 8.1,
-// 10.9 -> 10.3; K = 512 4.4 -> 5.0, 5.3 -> 6.0, 7.2 -> 7.6; with a ragged K 72 .. 1544 1.03 .. 1.5 times as fast on all tiles.
+// and enough slabs to pay for its longer start, 0.5 us.  Time of gemm_tile_kernel over that of gemm_stage_kernel, geometric mean
+// of the four layouts, launches back to back on operands that change from call to call:
+//   whole slabs, 16-byte rows, K = 1536 and 4096: 64x64 1.37 and 1.59 with 256 workgroups, 64x128 1.15 and 1.23, 128x64 1.15 and
+//   1.24; 128x128 1.07 and 1.13 with 160, 1.05 and 1.07 with 192, 1.03 and 1.05 with 240, and 0.98 .. 1.02 with 256 on one card,
+//   0.90 (2048x2048x2048 20.9 -> 23.3 us) on another: a full chip of them is bound by power and by the loads of all CUs together,
+//   not by what one workgroup waits for.  4- and 8-byte rows 1.0 .. 1.26 on every tile, with 256 workgroups too.
+//   K = 512 0.88 .. 1.0, K = 768 0.9 .. 1.1 on all tiles.
+//   ragged K, 72 .. 3080: 64x64 1.0 .. 1.4, the others 0.98 .. 1.1 with 96 .. 256 workgroups, but with both operands K-contiguous
+//   1.01 at 72, 0.97 .. 0.99 from 136 to 1544 and 1.0 from 2056 on.
+//   whole K, granules over the edge of an operand: K = 256 0.975 .. 1.0 (64x64 1.02), 512 1.0 (1.04), 768 1.02 .. 1.06 (1.12),
+//   1024 and more 1.0 .. 1.5.
 // Operands of more than 28 MiB are streamed rather than held by the caches, and there loads further ahead gain nothing sure:
-// 128x8192x8192 36.0 -> 34.3 on one card and 36.5 -> 42.7 on another, 776x504x26968 38.8 -> 39.8, 4272x96x3400 (30 MB) 15.4 -> 18.9,
+// 128x8192x8192 36.0 -> 34.3 us on one card and 36.5 -> 42.7 on another, 776x504x26968 38.8 -> 39.8, 4272x96x3400 (30 MB) 15.4 -> 18.9,
 // though 6848x256x3648 (52 MB) 26.3 -> 21.1; below, 384x448x15680 (26 MB) 17.3 -> 15.7, 128x6720x1536 (21 MB) 12.0 -> 8.2.
 // Below 2.5 MiB they stay in the L2s from call to call, and the ring's one slab ahead is enough: 256x512x1024 5.8 -> 6.3,
 // 512x512x1024 5.9 -> 6.3, but 768x512x1024 8.4 -> 6.6.
-bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, bool ragged, int64_t operand_bytes, int num_cu)
+// ragged: K or granules, as measured above (operands that gemm_ksplit_kernel cannot take).
+bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, int64_t K, bool ragged, int path, int64_t operand_bytes, int num_cu)
 {
-    return t.stage16 != nullptr && workgroups <= num_cu && operand_bytes <= (28LL << 20) &&
-           (ragged || (slabs >= t.stage_from && operand_bytes >= (5LL << 19)));
+    if (t.stage16 == nullptr || workgroups > num_cu || operand_bytes > (28LL << 20)) return false;
+    if (K % 64 != 0) return true;
+    if (ragged) return slabs >= 8;
+    return slabs >= t.stage_from && operand_bytes >= (5LL << 19) && (path == 3 || 16 * workgroups <= t.stage_most * num_cu);
 }
 
 size_t tail_bytes(const TileConfig &t, int64_t sliced, int splits) { return (size_t)sliced * (size_t)splits * (size_t)(t.BM * t.BN) * sizeof(float); }
@@ -364,7 +374,7 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     if (path == 1 || path == 2) slab *= f32 ? 1.05 : (path == 2 ? t.f16_a2 * kLayA2[k_contig] : t.general);
     slab *= foot_factor;
     // (its slab time hardly depends on where the operands come from; a ragged last slab is one more)
-    const bool stage = !f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K % 64 != 0, (M + N) * K * 2, NUM_CU);
+    const bool stage = !f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K, K % 64 != 0, path, (M + N) * K * 2, NUM_CU);
     if (stage) {
         slab = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : 1.0);
         tail = 0.0;
@@ -780,7 +790,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     } else {
         const dim3 grid((unsigned)work_grid((int)(tiles_m * tiles_n), a.whole_tiles, a.splits));
         launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
-        stage = !f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, ragged || K % BK != 0, (M + N) * K * (int64_t)sizeof(T), num_cu);
+        stage = !f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, K, !ksplit_ok, path, (M + N) * K * (int64_t)sizeof(T), num_cu);
         if (stage) fn = bf16 ? t.stage_bf16 : t.stage16;
         launch_rc = fn(akc, bkc, aligned, grid, stream, a);
     }

@@ -53,16 +53,20 @@ def test_exact_on_whole_slabs(oracle, tile, dtype):
 
 
 def test_where_it_runs():
-    """The limits of the choice: workgroups, slabs, bytes of the operands; never in binary32 or on 2-byte aligned rows."""
-    def ran(M, N, K, dtype="f16", force="t64x64:s1", pad=0):
+    """The limits of the choice: workgroups, slabs, bytes of the operands, granules over an edge; never in binary32 or on
+    2-byte aligned rows."""
+    def ran(M, N, K, dtype="f16", force="t64x64:s1", pad=0, lb=1):
         A, B = np.zeros((M, K), np.float32 if dtype == "f32" else np.float16), np.zeros((K, N), np.float32 if dtype == "f32" else np.float16)
-        return run_gpu(dtype, A, B, 0, 1, pads=(pad, pad, 0), force=force, return_config=True)[1].endswith(" stage")
+        return run_gpu(dtype, A, B, 0, lb, pads=(pad, pad, 0), force=force, return_config=True)[1].endswith(" stage")
     assert ran(1024, 1024, 1024) and not ran(1024, 1088, 1024)           # 256 workgroups, 272
     assert not ran(1024, 1024, 960) and ran(1024, 1024, 968)             # 15 slabs; the ragged 16th
     assert not ran(640, 600, 1024) and ran(640, 648, 1024)               # 2.42 MiB, 2.52
     assert ran(256, 256, 28600) and not ran(256, 256, 28736)             # 27.9 MiB, 28.1
     assert not ran(1024, 1024, 1024, "f32") and not ran(1024, 1024, 1024, pad=1)
     assert not ran(512, 512, 2048, force="t256x256:s1")                  # no such kernel for the tile
+    big = dict(force="t128x128:s1")                                      # 240 workgroups, 256; the second on 8-byte rows
+    assert ran(1920, 2048, 1536, **big) and not ran(2048, 2048, 1536, **big) and ran(2048, 2048, 1536, pad=4, **big)
+    assert not ran(640, 596, 448, pad=4, lb=0) and ran(640, 596, 512, pad=4, lb=0) and not ran(640, 600, 512, pad=4, lb=0)
 
 
 @pytest.mark.parametrize("tile", sorted(TILES))
