@@ -284,11 +284,18 @@ const char *gemm_config_name(int i);
 /*
  * Description of the configuration the last successful call on this thread
  * used, e.g. "f16 t256x256 NT aligned s1"; " small" at the end: the kernel for
- * small products ran (see gemm_query_config); " stage": the tile kernel for launches
- * of at most one workgroup per CU.  The string is thread-local storage
+ * small products ran (see gemm_query_config).  The string is thread-local storage
  * owned by the library, valid until the thread's next gemm call.
  */
 const char *gemm_last_config(void);
+
+/*
+ * Name of the kernel that the last successful call on this thread launched for the product
+ * itself: "gemm_tile_kernel", "gemm_stage_kernel" (the tiles of launches of at most one workgroup
+ * per CU), "gemm_ksplit_kernel", "gemm_small_kernel", "gemm_small16_kernel"; "empty" or "zero-fill"
+ * where there was nothing to multiply, "none" before the first call.  A constant string.
+ */
+const char *gemm_last_kernel(void);
 
 /* Text for a status code (static storage). */
 const char *gemm_status_string(int status);

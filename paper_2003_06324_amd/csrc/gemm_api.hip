@@ -269,7 +269,7 @@ struct LastCall {
     bool akc = false, bkc = false, small = false, safe = false, fixed_scratch = false;
     const char *path = nullptr;
     int splits = 0, tail = 0;  // tail: K-slices of the last tiles
-    bool stage = false;        // gemm_stage_kernel
+    const char *kernel = nullptr;  // null: the special one
 };
 thread_local LastCall t_last;
 thread_local char t_last_config[128];
@@ -776,7 +776,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     a.by_last_rows = divisor(tiles_m % GM > 0 ? tiles_m % GM : 1);
     a.by_sliced = divisor(tiles_m * tiles_n - a.whole_tiles);
     hipError_t launch_rc;
-    bool stage = false;
+    const char *kernel;
     if (small) {
         // binary32 in 16x16 blocks where those fit one round too and the sum is long enough to pay for four times the
         // workgroups (microseconds per launch, 32x32 -> 16x16 blocks: 256x256 NN K = 64 2.8 -> 3.6, 136 3.2 -> 3.3, 256 3.9 -> 3.5,
@@ -786,12 +786,14 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         a.tiles_m = (int)cdiv(M, edge);
         a.tiles_n = (int)cdiv(N, edge);
         const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
+        kernel = blocks16 ? "gemm_small16_kernel" : "gemm_small_kernel";
         launch_rc = blocks16 ? launch_small16<float>(akc, bkc, grid, stream, a) : launch_small<T>(akc, bkc, grid, stream, a);
     } else {
         const dim3 grid((unsigned)work_grid((int)(tiles_m * tiles_n), a.whole_tiles, a.splits));
         launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
-        stage = !f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, K, !ksplit_ok, path, (M + N) * K * (int64_t)sizeof(T), num_cu);
+        const bool stage = !f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, K, !ksplit_ok, path, (M + N) * K * (int64_t)sizeof(T), num_cu);
         if (stage) fn = bf16 ? t.stage_bf16 : t.stage16;
+        kernel = stage ? "gemm_stage_kernel" : (t.fallback >= 0 ? "gemm_ksplit_kernel" : "gemm_tile_kernel");
         launch_rc = fn(akc, bkc, aligned, grid, stream, a);
     }
     if (launch_rc != hipSuccess) {
@@ -815,7 +817,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
         if (rc != hipSuccess) return GEMM_ERR_HIP;
     }
     t_last = LastCall{type_name, nullptr, t.name, akc, bkc, small, a.safe != 0, noalloc && a.splits > 1,
-                      aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, a.whole_tiles > 0 ? a.splits : 0, stage};
+                      aligned ? (path == 0 ? "aligned" : "aligned4") : "general", splits, a.whole_tiles > 0 ? a.splits : 0, kernel};
     return GEMM_OK;
 }
 
@@ -1177,10 +1179,16 @@ const char *gemm_last_config(void)
     if (l.special != nullptr)
         snprintf(t_last_config, sizeof t_last_config, "%s %s", l.type, l.special);
     else
-        snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s%s%s", l.type, l.tile, l.akc ? 'N' : 'T', l.bkc ? 'T' : 'N', l.path,
-                 l.splits, l.small ? " small" : "", l.safe ? " safe" : "", tail, l.fixed_scratch ? " static-scratch" : "",
-                 l.stage ? " stage" : "");
+        snprintf(t_last_config, sizeof t_last_config, "%s %s %c%c %s s%d%s%s%s%s", l.type, l.tile, l.akc ? 'N' : 'T', l.bkc ? 'T' : 'N', l.path,
+                 l.splits, l.small ? " small" : "", l.safe ? " safe" : "", tail, l.fixed_scratch ? " static-scratch" : "");
     return t_last_config;
+}
+
+const char *gemm_last_kernel(void)
+{
+    const LastCall &l = t_last;
+    if (l.type == nullptr) return "none";
+    return l.special != nullptr ? l.special : l.kernel;
 }
 
 const char *gemm_status_string(int status)

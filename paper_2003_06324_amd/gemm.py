@@ -21,7 +21,7 @@ except ImportError:
     _binding = None          # the ctypes functions below serve every call (also in a process that builds it on first use)
 
 EXPORTS = ("gemm_f32", "gemm_f16f32", "gemm_f16f16", "gemm_bf16f32", "gemm_f16f32_noalloc", "gemm_cost_model_scale", "gemm_set_phase_trace", "gemm_force_config", "gemm_query_config", "gemm_query_config_layouts", "gemm_tune", "gemm_tune_clear", "gemm_tune_save", "gemm_tune_load", "gemm_num_configs", "gemm_config_name",
-           "gemm_last_config", "gemm_status_string", "gemm_shutdown")
+           "gemm_last_config", "gemm_last_kernel", "gemm_status_string", "gemm_shutdown")
 
 
 PRODUCTS = ("gemm_f32", "gemm_f16f32", "gemm_f16f16", "gemm_bf16f32", "gemm_f16f32_noalloc")
@@ -84,6 +84,8 @@ def load_library():
     lib.gemm_config_name.restype = ctypes.c_char_p
     lib.gemm_last_config.argtypes = []
     lib.gemm_last_config.restype = ctypes.c_char_p
+    lib.gemm_last_kernel.argtypes = []
+    lib.gemm_last_kernel.restype = ctypes.c_char_p
     lib.gemm_status_string.argtypes = [i32]
     lib.gemm_status_string.restype = ctypes.c_char_p
     lib.gemm_shutdown.argtypes = []
@@ -236,6 +238,11 @@ def config_names():
 
 def last_config():
     return load_library().gemm_last_config().decode()
+
+
+def last_kernel():
+    """Name of the kernel that the thread's last product ran."""
+    return load_library().gemm_last_kernel().decode()
 
 
 def shutdown():

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import gemm_inputs as gi
+import paper_2003_06324_amd as g
 from gpu_util import run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -28,7 +29,7 @@ def test_exact_on_whole_numbers_at_every_remainder(oracle, tile, dtype):
             pads = ((K if la == 0 else M) % 2, (N if lb == 0 else K) % 2 + 2 * (n % 2), 0)
             for slices in (1, 3):
                 C, cfg = run_gpu(dtype, A, B, la, lb, lc=0, pads=pads, force="%s:s%d" % (tile, slices), return_config=True)
-                assert "aligned" in cfg and (K % 64 == 0 or cfg.endswith(" stage")), cfg
+                assert "aligned" in cfg and (K % 64 == 0 or g.last_kernel() == "gemm_stage_kernel"), (cfg, g.last_kernel())
                 assert np.array_equal(C.astype(np.float64), ref), (M, N, K, la, lb, slices, cfg)
 
 
@@ -48,7 +49,7 @@ def test_exact_on_whole_slabs(oracle, tile, dtype):
         ref = oracle.gemm(M, N, K, bits[0], 0, bits[1], 0, dtype)
         for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
             C, cfg = run_gpu(dtype, A, B, la, lb, lc=0, pads=(8 * (n % 2), 4 * (n % 3), 0), force="%s:s%d" % (tile, slices), return_config=True)
-            assert cfg.endswith(" s%d stage" % slices), cfg
+            assert cfg.endswith(" s%d" % slices) and g.last_kernel() == "gemm_stage_kernel", (cfg, g.last_kernel())
             assert np.array_equal(C.astype(np.float64), ref), (M, N, K, la, lb, slices, cfg)
 
 
@@ -57,7 +58,8 @@ def test_where_it_runs():
     2-byte aligned rows."""
     def ran(M, N, K, dtype="f16", force="t64x64:s1", pad=0, lb=1):
         A, B = np.zeros((M, K), np.float32 if dtype == "f32" else np.float16), np.zeros((K, N), np.float32 if dtype == "f32" else np.float16)
-        return run_gpu(dtype, A, B, 0, lb, pads=(pad, pad, 0), force=force, return_config=True)[1].endswith(" stage")
+        run_gpu(dtype, A, B, 0, lb, pads=(pad, pad, 0), force=force)
+        return g.last_kernel() == "gemm_stage_kernel"
     assert ran(1024, 1024, 1024) and not ran(1024, 1088, 1024)           # 256 workgroups, 272
     assert not ran(1024, 1024, 960) and ran(1024, 1024, 968)             # 15 slabs; the ragged 16th
     assert not ran(640, 600, 1024) and ran(640, 648, 1024)               # 2.42 MiB, 2.52
@@ -76,6 +78,6 @@ def test_same_bits_as_the_register_staged_kernel(tile):
         A, B = gi.make_problem(M + K, M, N, K, "normal", "f16")
         for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
             pads = ((K if la == 0 else M) % 2, (N if lb == 0 else K) % 2, 0)
-            runs, cfgs = zip(*(run_gpu("f16", A, B, la, lb, pads=pads, force="%s:s2%s" % (tile, how), return_config=True) for how in ("", ":safe", ":regload")))
-            assert [cfg.endswith(" stage") for cfg in cfgs] == [True, True, False], cfgs
+            runs, ran = zip(*((run_gpu("f16", A, B, la, lb, pads=pads, force="%s:s2%s" % (tile, how)), g.last_kernel()) for how in ("", ":safe", ":regload")))
+            assert ran == ("gemm_stage_kernel", "gemm_stage_kernel", "gemm_tile_kernel")
             assert np.array_equal(runs[0], runs[1]) and np.array_equal(runs[0], runs[2]), (M, N, K, la, lb)
