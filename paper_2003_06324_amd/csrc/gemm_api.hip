@@ -344,8 +344,9 @@ int tail_slices(const TileConfig &t, int64_t tiles, int64_t KT, bool f32, int nu
 // 3 = direct-load kernels on operands that are 4- or 8-byte aligned (row pieces straddle cache lines)
 // k_contig: how many of A and B have K as their contiguous dimension (0..2); the misaligned
 // classes depend on it (a K-contiguous row is what straddles lines or gets its loads split)
+// ksplit_ok: as for choose_uncached
 double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64_t KT, int splits, bool f32,
-                     int path, int k_contig, int NUM_CU, size_t max_ws_bytes)
+                     int path, int k_contig, int NUM_CU, size_t max_ws_bytes, bool ksplit_ok)
 {
     static const double kLayA4[3] = {0.867, 1.0, 0.986};  // 16-bit, path 3, by k_contig
     static const double kLayA2[3] = {1.14, 1.0, 1.19};   // 16-bit, path 2
@@ -368,15 +369,18 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     const double foot = ((double)M * K + (double)K * N) * esz;
     const double foot_factor = foot <= kFootLo ? kFootFactor
                                : (foot >= kFootHi ? 1.0 : exp(log(kFootFactor) * (log(kFootHi) - log(foot)) / (log(kFootHi) - log(kFootLo))));
-    // slabs' worth of extra time for the guarded last slab of a ragged K
+    // slabs' worth of extra time for a ragged K beside its last slab's own: a guarded loop on path 1 and 2; on direct loads, which
+    // have none, a fitted term all the same (with zero in binary32 the picks of 39 calls were 2 .. 4 % slower, with zero or one
+    // in 16 bits those of 367 and 375 calls 0.6 % slower and the same)
     double tail = f32 ? (path == 3 ? 3.23 : 1.27) : (path == 3 ? 2.8 : 2.32);
     if (path == 3) slab *= f32 ? t.f32_a4 : t.f16_a4 * kLayA4[k_contig];
     if (path == 1 || path == 2) slab *= f32 ? 1.05 : (path == 2 ? t.f16_a2 * kLayA2[k_contig] : t.general);
     slab *= foot_factor;
-    // (its slab time hardly depends on where the operands come from; a ragged last slab is one more)
-    const bool stage = !f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K, K % 64 != 0, path, (M + N) * K * 2, NUM_CU);
-    if (stage) {
-        slab = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : 1.0);
+    // (its slab time hardly depends on where the operands come from; where it runs it is not behind the other kernel, whose
+    // time for small operands is the lower one; a ragged last slab is one more)
+    if (!f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K, !ksplit_ok, path, (M + N) * K * 2, NUM_CU)) {
+        const double stage = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : 1.0);
+        if (stage < slab) slab = stage;
         tail = 0.0;
     }
     if (path == 1 || path == 2) {
@@ -453,7 +457,7 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
             const int cand = forced > 0 ? forced : s;
             if (cand > 1 && cand > KT) break;
             if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
-            const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu, max_ws_bytes);
+            const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu, max_ws_bytes, ksplit_ok);
             if (c < best) { best = c; tile = t; splits = cand; }
             if (forced > 0) break;
         }
@@ -849,7 +853,7 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
             if (kTiles[t].fallback >= 0 && !key.ksplit_ok) continue;
             for (int s = 1; s <= 32 && (s == 1 || s <= KT); s *= 2)
                 cand.emplace_back(estimate_cost(kTiles[t], key.M, key.N, key.K, KT, s, key.f32 != 0, key.path, key.k_contig,
-                                                key.num_cu, 0), t, s);
+                                                key.num_cu, 0, key.ksplit_ok != 0), t, s);
         }
     }
     std::sort(cand.begin(), cand.end());
