@@ -44,6 +44,11 @@ CASES = [
      (4097 * 1025 + 1025 * 3073) * 2 + 4097 * 3073 * 4),
     ("f16_1000x1500x2000_NN", "--dtype f16 --size 1000 1500 2000 --layout NN --dist uniform",
      (1000 * 2000 + 2000 * 1500) * 2 + 1000 * 1500 * 4),
+    ("f16_1536x1024x2048_NT", "--dtype f16 --size 1536 1024 2048 --layout NT --dist normal",
+     (1536 * 2048 + 2048 * 1024) * 2 + 1536 * 1024 * 4),
+    # a last round of tiles cut into K-slices
+    ("f16_4224x7840x6824_NT", "--dtype f16 --size 4224 7840 6824 --layout NT --dist normal",
+     (4224 * 6824 + 6824 * 7840) * 2 + 4224 * 7840 * 4),
 ]
 SQ = "SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES GRBM_GUI_ACTIVE"
 ITERS = 12
@@ -81,10 +86,10 @@ def find(raw, sub, suffix):
 
 def short(name):
     """Readable kernel name (the profiler leaves names with a _Float16 argument mangled)."""
-    m = re.search(r"gemm_(tile|ksplit)_kernel<([^>]*)>", name)
+    m = re.search(r"gemm_(tile|ksplit|stage|small)_kernel<([^>]*)>", name)
     if m:
         return "gemm_%s_kernel<%s>" % (m.group(1), m.group(2).replace("_Float16", "f16").replace(" ", ""))
-    m = re.search(r"gemm_(tile|ksplit)_kernelI(DF16_|DF16b|f)((?:L[ib]\d+E)+)E", name)
+    m = re.search(r"gemm_(tile|ksplit|stage|small)_kernelI(DF16_|DF16b|f)((?:L[ib]\d+E)+)E", name)
     if m:
         elem = {"DF16_": "f16", "DF16b": "bf16", "f": "float"}[m.group(2)]
         # Lb0E / Lb1E are booleans, Li<n>E integers
@@ -94,10 +99,10 @@ def short(name):
 
 
 def counters(raw, sub, pattern):
-    """Mean per dispatch of every counter over the dispatches whose kernel name contains pattern."""
+    """Mean per dispatch of every counter over the dispatches whose kernel name matches pattern."""
     acc = collections.defaultdict(list)
     for r in csv.DictReader(open(find(raw, sub, "counter_collection.csv"))):
-        if pattern in r["Kernel_Name"]:
+        if re.search(pattern, r["Kernel_Name"]):
             acc[r["Counter_Name"]].append(float(r["Counter_Value"]))
     return {k: sum(v[SKIP:]) / len(v[SKIP:]) for k, v in acc.items()}
 
@@ -128,7 +133,8 @@ def summarise(raw, out):
     for r in rows:
         txt.append("%-92s %6d %12.1f %8.4g" % (short(r["Name"]), int(r["Calls"]), float(r["AverageNs"]) / 1e3,
                                                float(r["Percentage"])))
-    txt += ["", "Template arguments: element type, BM, BN, waves in M, waves in N, A K-contiguous, B K-contiguous, direct-load path.",
+    txt += ["", "Template arguments: element type, BM, BN, waves in M, waves in N, (stage kernel: stages,) A K-contiguous, B K-contiguous, (tile",
+            "kernel: loads: 0 through registers, 1 direct, 2 direct and checked against the operand's end).",
             "Per-kernel averages include the warm-up steps.  --no-context leaves out bench.py's zero-data, binary16-output and",
             "bfloat16 runs, which launch the headline kernels on other data and would mix into these averages.",
             "bench.py's JSON line of this same run:", line, ""]
@@ -140,10 +146,10 @@ def summarise(raw, out):
     ff, wf = 1048576.0 / cf, 1048576.0 / cw   # the copy moves 1 GiB = 1048576 KiB each way
     table, js = [], {}
     for name, _, algo in CASES:
-        kernels = ["gemm_tile_kernel", "gemm_ksplit_kernel", "splitk_reduce_kernel"]
+        kernels = ["gemm_tile_kernel", "gemm_stage_kernel", "gemm_ksplit_kernel", "splitk_reduce_kernel", "tail_reduce_kernel"]
         f = summed(raw, "fetch_" + name, kernels)["FETCH_SIZE"]
         w = summed(raw, "write_" + name, kernels)["WRITE_SIZE"]
-        sq = counters(raw, "sq_" + name, "gemm_")
+        sq = counters(raw, "sq_" + name, "gemm_(tile|stage|ksplit|small)")
         util = sq["SQ_VALU_MFMA_BUSY_CYCLES"] / (sq["GRBM_GUI_ACTIVE"] / 8 * 1024)
         conflict = sq["SQ_LDS_BANK_CONFLICT"] / max(sq["SQ_LDS_IDX_ACTIVE"], 1.0)
         fb, wb = f * ff * 1024, w * wf * 1024
@@ -157,8 +163,8 @@ def summarise(raw, out):
                      "%.3f + WRITE_SIZE x %.3f KiB per library call; mfma_util = SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE / 8 x 1024)"
                      % (ff, wf))
     json.dump(js, open(os.path.join(out, "counters.json"), "w"), indent=1)
-    txt = ["HBM traffic and SQ counters per library call, rocprofv3 --pmc, one counter set per run (the K-sliced shapes include their",
-           "reduce pass in the traffic columns; MfmaUtil and LDS counters are those of the gemm kernel)",
+    txt = ["HBM traffic and SQ counters per library call, rocprofv3 --pmc, one counter set per run (the shapes with K-slices, of all or of",
+           "the last tiles, include their reduce pass in the traffic columns; MfmaUtil and LDS counters are those of the gemm kernel)",
            "run and summarised by: python3 -m paper_2003_06324_amd.collect_profiles; per case it runs",
            "  rocprofv3 --pmc FETCH_SIZE --output-format csv -d <raw>/fetch_<case> -o p -- python3 -m paper_2003_06324_amd.profile_workload <case args> --iters 12 --copy-mib 1024",
            "  rocprofv3 --pmc WRITE_SIZE --output-format csv -d <raw>/write_<case> -o p -- (same)",

@@ -856,7 +856,7 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args, const WorkIte
 
 // How gemm_tile_kernel fetches its operands: through registers, by direct loads, by direct loads that are checked against
 // the operand's end.
-enum class Loads { STAGED, DIRECT, CHECKED };
+constexpr int LOADS_STAGED = 0, LOADS_DIRECT = 1, LOADS_CHECKED = 2;
 // Whether direct loads of this product can reach past an operand's end: a ragged last slab, or granules over the edge of an
 // M/N-contiguous operand.
 template <typename T> inline bool checks_loads(bool akc, bool bkc, int M, int N, int K)
@@ -867,7 +867,7 @@ template <typename T> inline bool checks_loads(bool akc, bool bkc, int M, int N,
 // ---------------------------------------------------------------------------
 // The kernel.  grid.x = work_grid() workgroups.
 // ---------------------------------------------------------------------------
-template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC, Loads LOADS>
+template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC, int LOADS>
 __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs p)
 {
     constexpr int NW = WM * WN, NT = NW * 64;
@@ -876,7 +876,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_tile_kernel(const KernelArgs
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be built from 32x32 blocks");
     constexpr int A_BYTES = BM * RBK, B_BYTES = BN * RBK;
     constexpr int SLOT = A_BYTES > B_BYTES ? A_BYTES : B_BYTES;  // one operand slab
-    constexpr bool ALIGNED = LOADS != Loads::STAGED, CHECKED = LOADS == Loads::CHECKED;
+    constexpr bool ALIGNED = LOADS != LOADS_STAGED, CHECKED = LOADS == LOADS_CHECKED;
     constexpr int NBUF = ALIGNED ? NSLOT : 4;  // ring of five operand slots, or two buffers of (A, B)
     typedef typename Frag<T>::type frag_t;
     constexpr int NVA = A_BYTES / 1024 / NW;  // direct loads per wave per A slab

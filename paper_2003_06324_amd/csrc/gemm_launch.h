@@ -33,9 +33,9 @@ template <typename T, int BM, int BN, int WM, int WN, bool AKC, bool BKC>
 static hipError_t launch_aligned(bool aligned, dim3 grid, hipStream_t s, const KernelArgs &a)
 {
     const dim3 block(WM * WN * 64);
-    if (!aligned) return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, Loads::STAGED>, grid, block, s, a);
-    if (checks_loads<T>(AKC, BKC, a.M, a.N, a.K)) return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, Loads::CHECKED>, grid, block, s, a);
-    return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, Loads::DIRECT>, grid, block, s, a);
+    if (!aligned) return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, LOADS_STAGED>, grid, block, s, a);
+    if (checks_loads<T>(AKC, BKC, a.M, a.N, a.K)) return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, LOADS_CHECKED>, grid, block, s, a);
+    return launch_kernel(gemm_tile_kernel<T, BM, BN, WM, WN, AKC, BKC, LOADS_DIRECT>, grid, block, s, a);
 }
 
 // akc: A is K-contiguous (row-major); bkc: B is K-contiguous (column-major)

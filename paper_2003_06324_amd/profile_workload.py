@@ -71,7 +71,7 @@ def main():
     for _ in range(args.iters):
         fn(M, N, K, A, la, 0, B, lb, 0, C, gi.ROW_MAJOR, 0, stream)
     torch.cuda.synchronize()
-    print("gemm:", g.last_config(), "x", args.iters)
+    print("gemm:", g.last_config(), g.last_kernel(), "x", args.iters)
     if args.copy_mib:
         n = args.copy_mib * (1 << 20) // 4
         src = torch.ones(n, dtype=torch.float32, device="cuda")
@@ -100,7 +100,7 @@ def phases(launch, iters, what):
     rec = buf.cpu().numpy().reshape(cap, 8)
     rec = rec[rec[:, 0] != 0]
     ts = (rec[:, :6] - rec[:, 0].min()) * 0.01          # microseconds (100 MHz clock)
-    print("%s [%s]: %d workgroups, span of the launch %.1f us" % (what, g.last_config(), len(rec), ts[:, 5].max()))
+    print("%s [%s, %s]: %d workgroups, span of the launch %.1f us" % (what, g.last_config(), g.last_kernel(), len(rec), ts[:, 5].max()))
     have_first = bool((rec[:, 1] != 0).all())     # only the direct-load kernels record it
     spans = ([("start -> first operands landed", 0, 1), ("K loop", 1, 2)] if have_first
              else [("start -> K loop done", 0, 2)])
