@@ -50,11 +50,12 @@
  *   threads that share a stream are serialised by the library for the duration
  *   of the launches.  A workspace that is too small is
  *   replaced by a larger one with hipMalloc (the old one is kept until
- *   gemm_shutdown(), since earlier work may still use it), so such a call can
- *   be recorded into a HIP graph only once its stream's workspace has reached
- *   the size it needs, e.g. after the same call was made once outside the
- *   capture; calls that use no K-slices only launch kernels and can always be
- *   captured.  Replays of a graph that holds a K-sliced call use the workspace of the
+ *   gemm_shutdown(), since earlier work may still use it).  That cannot be done while
+ *   the stream is being captured: a call whose automatic choice needs more than the
+ *   workspace has then runs in one slice (with another order of summation than outside
+ *   the capture), and only a slice count forced by name is refused.  Make the call once
+ *   outside the capture to have its slices recorded.  Replays of a graph that holds a
+ *   K-sliced call use the workspace of the
  *   stream it was captured on: order them with that stream's other K-sliced work and
  *   with each other.  Large products whose last round of tiles fills at most half of the
  *   chip cut those tiles into K-slices in the same workspace (64 MiB at most; gemm_last_config

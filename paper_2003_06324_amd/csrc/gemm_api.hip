@@ -549,11 +549,17 @@ int device_state(DeviceState **out)
     return GEMM_OK;
 }
 
-// workspace of (current device, stream), at least `bytes` long (g_mutex held)
-int get_workspace(DeviceState &d, hipStream_t stream, size_t bytes, void **out)
+// workspace of (device, stream) as it is (g_mutex held)
+Workspace &stream_workspace(DeviceState &d, hipStream_t stream)
 {
     static thread_local char own_thread;  // hipStreamPerThread names another stream in every thread
-    Workspace &w = d.ws[stream == hipStreamPerThread ? (hipStream_t)&own_thread : stream];
+    return d.ws[stream == hipStreamPerThread ? (hipStream_t)&own_thread : stream];
+}
+
+// The same, made at least `bytes` long
+int get_workspace(DeviceState &d, hipStream_t stream, size_t bytes, void **out)
+{
+    Workspace &w = stream_workspace(d, stream);
     if (w.bytes < bytes) {
         const size_t want = bytes > 2 * w.bytes ? bytes : 2 * w.bytes;
         void *p = nullptr;
@@ -698,6 +704,15 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     } else {
         choose(M, N, K, KT, f32, path, (int)akc + (int)bkc, num_cu, noalloc ? (size_t)GEMM_NOALLOC_SCRATCH_BYTES : 0,
                ksplit_ok, tile, splits);
+        // A stream under capture cannot be given a larger workspace: a pick in K-slices that needs one gives way to the best in
+        // one slice, so that which calls can be captured does not depend on the model's constants.
+        if (splits > 1 && !noalloc && tune == nullptr && g_forced_splits == 0 &&
+            stream_workspace(*dev, stream).bytes < ws_bytes(cdiv(KT, cdiv(KT, splits)), M, N)) {
+            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+            else if (status == hipStreamCaptureStatusActive)
+                choose(M, N, K, KT, f32, path, (int)akc + (int)bkc, num_cu, 1, ksplit_ok, tile, splits);
+        }
     }
     const bool small = tile == kSmall;
     if (tile_of(tile).fallback >= 0 && !ksplit_ok) tile = kTiles[tile].fallback;  // forced, but not served by that kernel

@@ -294,3 +294,37 @@ def test_k_slices_with_every_residue_of_n(oracle, entry):
                     assert np.array_equal(C.view(np.uint16), oracle.round_to_half(exact).view(np.uint16)), (N, force, pads, cfg)
                 else:
                     assert np.array_equal(C, exact.astype(np.float32)), (entry, N, force, pads, offs, cfg)
+
+
+def test_a_sliced_choice_is_captured_in_one_slice_on_a_stream_without_a_workspace():
+    """The workspace of a stream cannot grow while the stream is being captured; once it has grown, the slices are recorded."""
+    import torch
+    import paper_2003_06324_amd as g
+    M, N, K = 256, 256, 16384
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    A = torch.randint(-4, 5, (M, K), device="cuda", generator=gen).half()
+    B = torch.randint(-4, 5, (N, K), device="cuda", generator=gen).half()
+    C = torch.zeros(M, N, device="cuda")
+    assert int(g.query_config(2, M, N, K, 16, gi.ROW_MAJOR, gi.COL_MAJOR).split(":s")[1]) > 1
+    stream = torch.cuda.Stream()
+
+    def captured():
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            g.gemm_f16f32(M, N, K, A, gi.ROW_MAJOR, 0, B, gi.COL_MAJOR, 0, C, gi.ROW_MAJOR, 0, stream.cuda_stream)
+        slices = int(g.last_config().split()[4][1:])
+        for _ in range(3):
+            A.copy_(torch.randint(-4, 5, (M, K), device="cuda", generator=gen))
+            C.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(C, A.float() @ B.float().t())
+        return slices
+
+    torch.cuda.synchronize()
+    g.shutdown()   # (the stream may have served an earlier test)
+    g.force_config(None)
+    assert captured() == 1
+    g.gemm_f16f32(M, N, K, A, gi.ROW_MAJOR, 0, B, gi.COL_MAJOR, 0, C, gi.ROW_MAJOR, 0, stream.cuda_stream)
+    assert captured() > 1
