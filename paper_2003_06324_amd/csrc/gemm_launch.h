@@ -88,10 +88,21 @@ hipError_t launch_stage(bool akc, bool bkc, bool aligned, dim3 grid, hipStream_t
 {
     (void)aligned;
     const dim3 block(256);
-    if (akc && bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, true>, grid, block, s, a);
-    if (akc && !bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, false>, grid, block, s, a);
-    if (!akc && bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, false, true>, grid, block, s, a);
-    return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, false, false>, grid, block, s, a);
+    if (akc && bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, true, false>, grid, block, s, a);
+    if (akc && !bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, false, false>, grid, block, s, a);
+    if (!akc && bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, false, true, false>, grid, block, s, a);
+    return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, false, false, false>, grid, block, s, a);
+}
+
+// the same for a K-contiguous operand whose rows begin off the cache lines, one stage more
+template <typename T, int BM, int BN, int NST>
+hipError_t launch_skew(bool akc, bool bkc, bool aligned, dim3 grid, hipStream_t s, const KernelArgs &a)
+{
+    (void)aligned;
+    const dim3 block(256);
+    if (akc && bkc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, true, true>, grid, block, s, a);
+    if (akc) return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, true, false, true>, grid, block, s, a);
+    return launch_kernel(gemm_stage_kernel<T, BM, BN, 2, 2, NST, false, true, true>, grid, block, s, a);
 }
 
 typedef hipError_t (*launch_fn)(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
@@ -108,6 +119,10 @@ typedef hipError_t (*launch_fn)(bool, bool, bool, dim3, hipStream_t, const Kerne
     extern template hipError_t launch_stage<T, BM, BN, NST>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
 #define GEMM_INSTANTIATE_STAGE(T, BM, BN, NST) \
     template hipError_t launch_stage<T, BM, BN, NST>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
+#define GEMM_DECLARE_SKEW(T, BM, BN, NST) \
+    extern template hipError_t launch_skew<T, BM, BN, NST>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
+#define GEMM_INSTANTIATE_SKEW(T, BM, BN, NST) \
+    template hipError_t launch_skew<T, BM, BN, NST>(bool, bool, bool, dim3, hipStream_t, const KernelArgs &);
 #define GEMM_DECLARE_SMALL(T) \
     extern template hipError_t launch_small<T>(bool, bool, dim3, hipStream_t, const KernelArgs &);
 #define GEMM_INSTANTIATE_SMALL(T) template hipError_t launch_small<T>(bool, bool, dim3, hipStream_t, const KernelArgs &);

@@ -20,13 +20,31 @@
 // operand: k-rows past K, and the part of a granule past the operand's last row, read as zeros.  A ragged last slab
 // therefore runs through the same loop: lanes whose whole granule of a K-contiguous operand lies past K load from outside
 // the range, the granule that straddles K is masked in registers, and the k-groups past K are skipped.
+//
+// SKEW: rows of a K-contiguous operand that begin off a 128-byte line.  A row's 128 bytes of a slab then lie in two lines,
+// and the second one is fetched again with the next slab (the L1 has long lost it), so the loads cost up to twice the
+// lines.  Instead, image s of such an operand holds for every row the s-th whole line from the one on that the row begins
+// in; granule j of slab t is then granule (j + d) % 8 of image t + (j + d) / 8, with d = 0 .. 7 the row's place in its
+// first line.  That is an address per lane, nothing more, but a slab takes two images, so there is one image more than
+// slabs, and one stage more for loads as far ahead.  The loads alone of a 64x128 tile (operands in the memory-side cache)
+// take 0.23 us a slab on rows that begin on lines, 0.36 with rows 16 bytes off them; the product 1536x1024x2048, both
+// operands K-contiguous and their rows padded by 16 bytes, 17.4 us before and 14.4 with this.
 #pragma once
 #include "gemm_kernel.h"
 
 namespace gemm_gfx950 {
 
+// Place of row r of a K-contiguous operand in its first line, in granules, counted from the operand's beginning (on a line, where
+// it is to pay).  With rows that begin on 16 bytes, eight rows further it is the same again, so it is one number for all rows a
+// lane deals with.  Zero where rows do not begin on 16 bytes, and where there are less than the eight rows that the granules in
+// front of a row are sure to lie in.
+__host__ __device__ __forceinline__ int line_skew(int64_t ld, int esz, int rows, int r)
+{
+    return ld * esz % 16 != 0 || rows < GPR ? 0 : (int)((uint32_t)r * (uint32_t)(ld * esz / 16) & (GPR - 1));
+}
+
 // Direct loads of one operand: the same LDS image as DirectLoader's, wave w filling PER_WAVE consecutive pieces of 1 KiB.
-template <typename T, int R, int NW, bool KC>
+template <typename T, int R, int NW, bool KC, bool SKEW = false>
 struct StageLoader {
     static constexpr int EPC = Elem<T>::EPC, BK = Elem<T>::BK;
     static constexpr int PER_WAVE = R * RBK / 1024 / NW;
@@ -34,12 +52,13 @@ struct StageLoader {
     static constexpr int CPR = R / EPC;             // granules per k-row (M/N-contiguous image)
     static constexpr int ROWS_PER_LOAD = 1024 / RBK;
     static constexpr int GROUP = 4;                 // loads per M0 value: the instruction offset is below 4096
-    static constexpr int LEAD = (GROUP - 1) * 1024; // the descriptor's base lies this far before the slab, so that the lane
-                                                    // offsets, from which the instruction offset is taken off, stay positive
+    static constexpr int LEAD = (GROUP - 1) * 1024 + (SKEW ? RBK : 0);  // the descriptor's base lies this far before the slab, so
+                                                    // that the lane offsets, from which the instruction offset is taken off, stay positive
     int4_t rsrc;
     uint32_t off[PER_WAVE];
     int64_t step;   // bytes to advance per slab
     uint64_t end;   // address of the operand's end
+    int skew;       // line_skew of the lane's rows
 
     // byte offset from the slab's origin of the granule a lane fetches with its wave's load i
     static __host__ __device__ __forceinline__ int64_t granule(int64_t ld, int row0, int rmax, int i, int wave, int lane)
@@ -65,6 +84,12 @@ struct StageLoader {
         rsrc[3] = 0x00020000;
 #pragma unroll
         for (int i = 0; i < PER_WAVE; ++i) off[i] = (uint32_t)granule(ld, row0, rmax, i, wave, lane) + LEAD - i % GROUP * 1024;
+        skew = 0;
+        if constexpr (SKEW && KC) {
+            skew = line_skew(ld, sizeof(T), rmax, lane / GPR);
+#pragma unroll
+            for (int i = 0; i < PER_WAVE; ++i) off[i] -= 16 * skew;
+        }
         step = (KC ? (int64_t)BK : (int64_t)BK * ld) * (int64_t)sizeof(T);
         end = DirectLoader<T, R, NW, KC>::end_of(origin, ld, rmax, kmax);
     }
@@ -91,14 +116,17 @@ struct StageLoader {
         const int range = (left >> 31) != 0 ? 0x7fffffff : (int)(uint32_t)left;
         rsrc[2] = __builtin_amdgcn_readfirstlane(range);  // (uniform anyway, which the compiler does not see through the loop)
     }
-    // before the loads of a slab of which only `krem` k lie inside the operand
+    // the present image lies past the slice: nothing is loaded
+    __device__ __forceinline__ void no_range() { rsrc[2] = 0; }
+    // before the loads of a slab (or image) of which only `krem` k (skewed: from the row's beginning in it on, none or less if the
+    // image is past the slice's last slab) lie inside the operand
     __device__ __forceinline__ void ragged_slab(int krem, int wave, int lane)
     {
         if (!KC) return;  // k-rows past K lie past the operand's end
 #pragma unroll
         for (int i = 0; i < PER_WAVE; ++i) {
             const int r = ROWS_PER_LOAD * (wave * PER_WAVE + i) + lane / GPR;
-            const int g = (lane % GPR) ^ swz_kc(r);
+            const int g = ((lane % GPR) ^ swz_kc(r)) - skew;
             if (g * EPC >= krem) off[i] = 0x80000000u;
         }
     }
@@ -107,19 +135,28 @@ struct StageLoader {
 // LDS addresses of a wave's fragments of one operand (NF blocks of 32 tile rows from r0 on; see Fetch), as registers that
 // move with the slot.  K-contiguous image: one per k-group, the blocks 32 rows apart; M/N-contiguous: one per block, the
 // k-groups 16 k-rows apart.
-template <typename T, int R, bool KC, int NF>
+template <typename T, int R, bool KC, int NF, bool SKEW>
 struct StageFragments {
     typedef typename Frag<T>::type frag_t;
     static constexpr int NA = KC ? KGS : NF;
     uint32_t at[NA];
+    bool next[NA];  // skewed: the granule is in the image behind the slab's own
 
-    __device__ __forceinline__ void init(uint32_t img, int r0, int lane)
+    // stage: bytes from an image to the one behind it
+    __device__ __forceinline__ void init(uint32_t img, int r0, int lane, int64_t ld, int rows, int stage)
     {
 #pragma unroll
         for (int x = 0; x < NA; ++x) {
+            next[x] = false;
             if (KC) {
                 const int r = r0 + (lane & 31);
-                at[x] = img + r * RBK + (((2 * x + (lane >> 5)) ^ swz_kc(r)) << 4);
+                int g = 2 * x + (lane >> 5);
+                if constexpr (SKEW) {
+                    g += line_skew(ld, sizeof(T), rows, lane & 31);
+                    next[x] = g >= GPR;
+                    g &= GPR - 1;
+                }
+                at[x] = img + (next[x] ? stage : 0) + r * RBK + ((g ^ swz_kc(r)) << 4);
             } else {
                 const int s = lane & 15;
                 const int col = r0 + x * 32 + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
@@ -128,10 +165,11 @@ struct StageFragments {
             }
         }
     }
-    __device__ __forceinline__ void move(int delta)
+    // to the next slab: its own image lies `delta` bytes further, the one behind it `delta_next`
+    __device__ __forceinline__ void move(int delta, int delta_next)
     {
 #pragma unroll
-        for (int x = 0; x < NA; ++x) at[x] += delta;
+        for (int x = 0; x < NA; ++x) at[x] += SKEW && KC && next[x] ? delta_next : delta;
     }
     __device__ __forceinline__ frag_t read(int f, int kg) const
     {
@@ -158,7 +196,7 @@ template <int MOST, int NL> __device__ __forceinline__ void wait_slabs_left(int 
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(MOST * NL));
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int NST, bool AKC, bool BKC>
+template <typename T, int BM, int BN, int WM, int WN, int NST, bool AKC, bool BKC, bool SKEW>
 __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArgs p)
 {
     static_assert(sizeof(T) == 2, "16-bit operands");
@@ -166,10 +204,10 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
     constexpr int BK = Elem<T>::BK, KG = Elem<T>::KG, EPC = Elem<T>::EPC;
     constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
     constexpr int A_BYTES = BM * RBK, B_BYTES = BN * RBK, STAGE = A_BYTES + B_BYTES;
-    typedef StageLoader<T, BM, NW, AKC> LoaderA;
-    typedef StageLoader<T, BN, NW, BKC> LoaderB;
+    typedef StageLoader<T, BM, NW, AKC, SKEW> LoaderA;
+    typedef StageLoader<T, BN, NW, BKC, SKEW> LoaderB;
     constexpr int NVA = LoaderA::PER_WAVE, NVB = LoaderB::PER_WAVE, NL = NVA + NVB;  // loads per wave and slab
-    static_assert(NST >= 3 && (NST - 1) * NL <= 63, "the counted waits go up to 63 loads");
+    static_assert(NST >= 3 + SKEW && (NST - 1) * NL <= 63, "the counted waits go up to 63 loads");
     constexpr int NB = FM * FN, NM = KGS * NB;  // MFMA blocks of a k-group and of a slab
     typedef typename Frag<T>::type frag_t;
 
@@ -190,6 +228,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
     // slabs of this slice; only the operand's last one can be ragged
     const int kt0 = item.kt0, n = item.kt1 - kt0;
     const int krem = p.K - (kt0 + n - 1) * BK < BK ? p.K - (kt0 + n - 1) * BK : BK;  // k of the last slab
+    const int images = n + SKEW;
     const bool safe = p.safe != 0;
 
     LoaderA la;
@@ -201,15 +240,19 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
         if (q < NVA) la.issue(dst_a + slot, q);
         else lb.issue(dst_b + slot, q - NVA);
     };
-    int h = 0;  // slab the loaders point at
+    int h = 0;  // slab (image) the loaders point at
     // Exact ranges from two slabs before the end on, because a granule of an M/N-contiguous operand with a leading
     // dimension below the granule covers up to four k-rows.
     auto prepare = [&]() {
         la.exact_range();
         lb.exact_range();
-        if (h == n - 1 && krem < BK) {
-            la.ragged_slab(krem, wave, lane);
-            lb.ragged_slab(krem, wave, lane);
+        if ((h == n - 1 && krem < BK) || (SKEW && h == n)) {
+            la.ragged_slab(krem - (h - (n - 1)) * BK, wave, lane);
+            lb.ragged_slab(krem - (h - (n - 1)) * BK, wave, lane);
+        }
+        if constexpr (SKEW) {  // the image behind the last slab is one of skewed rows only
+            if (!AKC && h >= n) la.no_range();
+            if (!BKC && h >= n) lb.no_range();
         }
     };
     auto advance = [&]() {
@@ -227,7 +270,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
         }
     };
     typedef std::integral_constant<int, 1> One;
-    typedef std::integral_constant<int, NST - 3> Ahead;
+    typedef std::integral_constant<int, NST - 3 - SKEW> Ahead;
     auto load_first = [&](int slab) {
 #pragma unroll
         for (int q = 0; q < NL; ++q) load1(slab * STAGE, q);
@@ -235,7 +278,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
     };
     if (n <= 2) prepare();
     load_first(0);
-    if (n > 1) load_first(1);
+    if constexpr (SKEW) load_first(1);
+    if (n > 1) load_first(1 + SKEW);
 
     float16_t acc[FM][FN];
 #pragma unroll
@@ -244,10 +288,10 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
         for (int j = 0; j < FN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    StageFragments<T, BM, AKC, FM> ra;
-    StageFragments<T, BN, BKC, FN> rb;
-    ra.init(lds0, wm * TM, lane);
-    rb.init(lds0 + A_BYTES, wn * TN, lane);
+    StageFragments<T, BM, AKC, FM, SKEW> ra;
+    StageFragments<T, BN, BKC, FN, SKEW> rb;
+    ra.init(lds0, wm * TM, lane, p.lda, p.M, STAGE);
+    rb.init(lds0 + A_BYTES, wn * TN, lane, p.ldb, p.N, STAGE);
     frag_t fa[KGS][FM], fb[KGS][FN];
     auto read_group = [&](int kg) {
 #pragma unroll
@@ -255,7 +299,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
 #pragma unroll
         for (int j = 0; j < FN; ++j) fb[kg][j] = rb.read(j, kg);
     };
-    hand_over(One(), n - 1);  // slab 0
+    hand_over(One(), n - 1);  // slab 0 (and the image behind it: everything below speaks of slabs with theirs)
     trace_mark(p, 1);
 #pragma unroll
     for (int kg = 0; kg < KGS; ++kg) {
@@ -263,7 +307,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
         __builtin_amdgcn_sched_barrier(0);  // the loop's waits count on this order
     }
 #pragma unroll 1
-    for (int i = 2; i < NST - 1 && i < n; ++i) load_first(i);
+    for (int i = 2 + SKEW; i < NST - 1 && i < images; ++i) load_first(i);
     hand_over(Ahead(), n - 2);  // slab 1
 
     // block m of a slab, k-group by k-group; blocks of a k-group in boustrophedon order, as in gemm_tile_kernel
@@ -274,12 +318,13 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
         asm volatile("" : "+a"(acc[mi][mj]));  // keeps the MFMA at this place in the stream
     };
     int read_at = 0, free = (NST - 1) * STAGE;  // LDS offsets: of the slab in the fragment addresses, of the free slot
-    // slab t, not the last one: multiply it, read slab t+1, load (if LOAD) slab t+NST-1 into the free slot
+    // slab t, not the last one: multiply it, read slab t+1, load (if LOAD) slab (image) t+NST-1 into the free slot
     auto body = [&](auto load_tag, int left) {
         constexpr bool LOAD = decltype(load_tag)::value;
         const int delta = read_at == (NST - 1) * STAGE ? -(NST - 1) * STAGE : STAGE;
-        ra.move(delta);
-        rb.move(delta);
+        const int delta_next = SKEW && read_at == (NST - 2) * STAGE ? -(NST - 1) * STAGE : STAGE;
+        ra.move(delta, delta_next);
+        rb.move(delta, delta_next);
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
             multiply1(m);
@@ -297,7 +342,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
         hand_over(Ahead(), left);  // slab t+2
     };
     int t = 0;
-    for (; t + NST - 1 < n; ++t) body(std::true_type(), NST);
+    for (; t + NST - 1 < images; ++t) body(std::true_type(), NST);
     for (; t < n - 1; ++t) body(std::false_type(), n - 3 - t);
     // the last slab
     if ((AKC || BKC) && krem % EPC != 0) {
