@@ -202,7 +202,8 @@ struct TileConfig {
                                 // binary32 operands; 0: only when forced
     launch_fn stage16, stage_bf16;  // gemm_stage_kernel (null: none), see runs_stage
     launch_fn skew16, skew_bf16;    // the same for rows off the cache lines, see runs_skew
-    double stage_slab, stage_a4;    // its slab time (microseconds per 64 k, one workgroup on a CU), on 4-/8-byte aligned operands over that
+    double stage_slab, stage_a4;    // its slab time (microseconds per 64 k, one workgroup on a CU), on 4-/8-byte aligned operands over that,
+    double stage_off;               // and on 16-byte aligned rows off the cache lines
     int stage_from;                 // slabs from which it is ahead on whole ones
     int stage_most;                 // sixteenths of the CUs up to which it is ahead on whole slabs of 16-byte rows
     int skew_from;                  // slabs from which it straightens rows off the cache lines
@@ -223,24 +224,24 @@ struct TileConfig {
 // (64x128 before 128x64: the model often ties the two, and the tie goes to the first; 64x128 measures 4-8 % ahead)
 const TileConfig kTiles[] = {
     {"t256x256", 256, 256, 1, 1.02, 1.02, 6.98, 6.98, 7.2, 0.83, 1.2, 1.05, 1.67, 1.25, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
     {"t128x128", 128, 128, 2, 0.457, 0.868, 1.99, 3.64, 1.92, 1.39, 1.23, 0.817, 1.57, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.41, 1.40, 24, 15, 24},
+     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.40, 1.435, 1.03, 24, 15, 24},
     {"t64x64", 64, 64, 4, 0.265, 0.855, 0.495, 1.86, 1.27, 0.78, 1.07, 0.992, 1.65, 1.35, 4,
-     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.21, 1.48, 16, 16, 32},
+     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.20, 1.55, 1.10, 16, 16, 32},
     {"t256x256w8", 256, 256, 1, 1.05, 1.05, 7.6, 7.6, 6.02, 0.812, 1.2, 0.915, 1.35, 1.15, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
     {"t256x128", 256, 128, 1, 0.71, 0.71, 3.52, 3.52, 3.82, 0.637, 1.2, 1.09, 1.47, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
     {"t128x256", 128, 256, 1, 0.661, 0.661, 4.19, 4.19, 4.17, 1.78, 1.25, 0.864, 2.03, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
     {"t64x128", 64, 128, 2, 0.349, 0.512, 1.12, 1.86, 1.67, 1.11, 1.31, 0.884, 1.87, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.29, 1.45, 16, 16, 24},
+     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.265, 1.585, 1.12, 16, 16, 24},
     {"t128x64", 128, 64, 2, 0.371, 0.617, 1.14, 1.81, 1.33, 1.06, 1.31, 0.919, 1.84, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.31, 1.5, 16, 16, 24},
+     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.285, 1.63, 1.12, 16, 16, 24},
     // K split across the four waves of the workgroup (Section 5.3, small sizes); fitted on 16-byte aligned operands only
     {"k64x64", 64, 64, 4, 0.311, 0.854, 0.598, 2.02, 2.02, 0.781, 1.07, 0.992, 1.65, 1.0, 1,
-     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
+     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -310,9 +311,10 @@ bool rows_off_lines(const void *p, int64_t ld, int64_t rows) { return (uintptr_t
 //   1.01 at 72, 0.97 .. 0.99 from 136 to 1544 and 1.0 from 2056 on.
 //   whole K, granules over the edge of an operand: K = 256 0.975 .. 1.0 (64x64 1.02), 512 1.0 (1.04), 768 1.02 .. 1.06 (1.12),
 //   1024 and more 1.0 .. 1.5.
-// Operands of more than 28 MiB are streamed rather than held by the caches, and there loads further ahead gain nothing sure:
-// 128x8192x8192 36.0 -> 34.3 us on one card and 36.5 -> 42.7 on another, 776x504x26968 38.8 -> 39.8, 4272x96x3400 (30 MB) 15.4 -> 18.9,
-// though 6848x256x3648 (52 MB) 26.3 -> 21.1; below, 384x448x15680 (26 MB) 17.3 -> 15.7, 128x6720x1536 (21 MB) 12.0 -> 8.2.
+// Operands of more than 28 MiB are streamed rather than held by the caches.  A few workgroups do not keep enough loads in flight
+// for that either way, and launches shorter than stage_from lose (128x3520x5120, eight slices of ten slabs, 128x128 15.8 -> 19.8);
+// the others gain, over 420 products of 28 .. 300 MB with 100 .. 256 workgroups 1.49 on 64x64, 1.17 on 128x64, 1.14 on 64x128, 1.06 on
+// 128x128, the last with a full chip too (8192x128x8192 40.6 -> 38.0, on another card 36.4 -> 34.3; 1024x1024x43264 141 -> 110).
 // Below 2.5 MiB they stay in the L2s from call to call, and the ring's one slab ahead is enough: 256x512x1024 5.8 -> 6.3,
 // 512x512x1024 5.9 -> 6.3, but 768x512x1024 8.4 -> 6.6.
 // ragged: K or granules, as measured above (operands that gemm_ksplit_kernel cannot take).
@@ -320,7 +322,8 @@ bool rows_off_lines(const void *p, int64_t ld, int64_t rows) { return (uintptr_t
 // a full chip of 128x128 tiles 1.03 .. 1.10 at K = 2048, 1.07 .. 1.16 at 4096 (2048x2048x2048 with rows padded by 16 bytes 26.1 -> 23.7).
 bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, int64_t K, bool ragged, int path, int64_t operand_bytes, int off_lines, int num_cu)
 {
-    if (t.stage16 == nullptr || workgroups > num_cu || operand_bytes > (28LL << 20)) return false;
+    if (t.stage16 == nullptr || workgroups > num_cu) return false;
+    if (operand_bytes > (28LL << 20)) return slabs >= t.stage_from && 8 * workgroups >= 3 * num_cu;
     if (K % 64 != 0) return true;
     if (ragged) return slabs >= 8;
     return slabs >= t.stage_from && operand_bytes >= (5LL << 19) &&
@@ -385,6 +388,7 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     // from the memory side: the slab time falls, log-linearly in the bytes of A and B, from 1 x at kFootHi bytes to
     // kFootFactor x at kFootLo bytes and below (fitted on the paper's power-of-two sizes, where it decides between
     // one slice and several for the sizes up to 1024).
+    static const double kStreamed = 60e6;  // bytes of operands from which the stage kernel's slabs come later, the more the longer
     static const double kFootLo = 2.23e+05, kFootHi = 1.52e+07, kFootFactor = 0.29;
     const double foot = ((double)M * K + (double)K * N) * esz;
     const double foot_factor = foot <= kFootLo ? kFootFactor
@@ -399,7 +403,8 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     // (its slab time hardly depends on where the operands come from; where it runs it is not behind the other kernel, whose
     // time for small operands is the lower one; a ragged last slab is one more)
     if (!f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K, !ksplit_ok, path, (M + N) * K * 2, off_lines, NUM_CU)) {
-        const double stage = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : 1.0);
+        double stage = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : (off_lines ? t.stage_off : 1.0));
+        if (foot > kStreamed) stage *= 1.0 + (t.BM + t.BN < 256 ? 0.35 : 0.1) * log2(foot / kStreamed);
         if (stage < slab) slab = stage;
         tail = 0.0;
     }
