@@ -99,7 +99,7 @@ def main():
         call = g.gemm_f16f32 if dt == "f16" else g.gemm_f32
         pA, pB = A.data_ptr() + off, B.data_ptr() + off
         fn = lambda: call(M, N, K, pA, la, 0, pB, lb, 0, C, gi.ROW_MAJOR, 0, stream)
-        configs = ["%s:s%d" % (tile, s) for tile in g.config_names() for s in (1, 2, 4, 8, 16, 32)]
+        configs = ["%s:s%d" % (tile, s) for tile in g.config_names() for s in (1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32)]
         takes = [timed(fn, configs, 10), timed(fn, configs, 10)]   # two takes: clock noise only adds time
         results = sorted((min(a, b),) + tuple(c.split(":s")) for c, a, b in zip(configs, *takes))
         results = [(us, tile, int(s)) for us, tile, s in results]
