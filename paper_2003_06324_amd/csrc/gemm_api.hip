@@ -442,14 +442,15 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
 // binary32 K = 136 6.3 -> 3.6, 256 6.9 -> 4.2, 512 7.5 .. 9.6 -> 5.7 .. 6.4, 768 6.8 .. 10.8 -> 7.3 .. 8.7;
 // 16 bits K = 136 4.3 -> 3.5, 512 4.4 .. 6.2 -> 3.5 .. 4.1, 768 5.2 .. 7.2 -> 3.9 .. 5.0, 1024 with both operands K-contiguous
 // 5.8 .. 5.9 -> 5.7 .. 5.8, 2048 6.4 .. 9.0 -> 6.8 .. 10.2;
-// K-contiguous rows on 2-byte boundaries, whose loads are split up, K = 136 5.2 -> 3.6, 512 5.9 -> 8.2.
+// K-contiguous rows on 2-byte boundaries, whose loads are split up, K = 136 5.2 -> 3.6, 512 5.9 -> 8.2, where the bases are not on
+// words; where they are (words), K = 257 5.3 .. 6.2 -> 2.7 .. 3.7, 511 6.3 .. 7.3 -> 3.5 .. 4.8, 767 7.1 .. 8.6 -> 4.5 .. 6.4.
 // Twice the blocks lose 10 % and more at any K.  Over 1202 calls inside the rule (all layouts, alignments and types, extents from
 // 1, from 1x8192 to 8192x32) the time is 0.70 of the tile kernels' in the geometric mean; the slowest are K <= 32, where most of
 // the waves have nothing to do (3.2 -> 3.4).
-bool serves_small(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_contig, int num_cu)
+bool serves_small(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_contig, bool words, int num_cu)
 {
     if (cdiv(M, 32) * cdiv(N, 32) > num_cu) return false;
-    return K <= (f32 ? 512 : (path == 2 && k_contig > 0 ? 256 : 768));
+    return K <= (f32 ? 512 : (path == 2 && k_contig > 0 && !words ? 256 : 768));
 }
 
 // What can be forced, or traced, are the tile kernels: with any such setting the small kernel stays out, whether the
@@ -477,7 +478,7 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
     double best = 1e300;
     tile = g_forced_tile >= 0 ? g_forced_tile : 0;
     splits = 1;
-    if (small_allowed() && serves_small(M, N, K, f32, path, k_contig, num_cu)) {
+    if (small_allowed() && serves_small(M, N, K, f32, path, k_contig, off_lines == 3, num_cu)) {
         tile = kSmall;
         return;
     }
@@ -730,8 +731,9 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     const int64_t KT = cdiv(K, BK);
     int tile, splits;
     const bool ksplit_ok = aligned && !ragged && K % BK == 0;
-    // 1: rows of an operand begin off the cache lines, 2: and gemm_stage_kernel can straighten them
-    const int off_lines = f32 || !aligned ? 0
+    // 1: rows of an operand begin off the cache lines, 2: and gemm_stage_kernel can straighten them; 3: rows begin in the middle of a
+    // word, and gemm_small_kernel can read them word by word
+    const int off_lines = f32 ? 0 : !aligned ? (path == 2 && (((uintptr_t)A | (uintptr_t)B) & 3) == 0 ? 3 : 0)
                           : ((akc && rows_off_lines(A, lda, M)) || (bkc && rows_off_lines(B, ldb, N)) ? 2 : ((lda | ldb) * 2 % 128 != 0 ? 1 : 0));
     if (tune) {
         tune->key = ShapeKey{M, N, K, (int)f32, path, (int)akc + (int)bkc, num_cu, (int)ksplit_ok};
@@ -905,7 +907,7 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     std::vector<std::tuple<double, int, int>> cand;
     {
         std::lock_guard<std::mutex> lock(g_mutex);
-        if (small_allowed() && serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
+        if (small_allowed() && serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, req.off_lines == 3, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
         for (int t = 0; t < kNumTiles; ++t) {
             if (kTiles[t].fallback >= 0 && !key.ksplit_ok) continue;
             for (const int s : kSlices) {
@@ -1108,7 +1110,7 @@ int gemm_tune_load(const char *path)
         const int words = sscanf(line + end, "%7s %1s", kernel, more);
         if (words > 0 && kernel[0] != '#') {
             const bool ok = strcmp(kernel, "small") == 0 && (words == 1 || more[0] == '#') && tile == kSmallAs && slices == 1 &&
-                            serves_small(M, N, K, esz == 4, path_, kc, cus);
+                            serves_small(M, N, K, esz == 4, path_, kc, true, cus);
             tile = ok ? kSmall : -1;
         }
         // a tile this build does not have, or one that does not serve the class, makes the file invalid as a whole

@@ -72,3 +72,18 @@ def test_a_recorded_pick_of_the_kernel_gives_way_to_the_tile_kernels(oracle, tmp
     finally:
         g.set_phase_trace(None)
         g.tune_clear()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K", [17, 255, 257, 513, 767])
+def test_rows_that_begin_in_the_middle_of_a_word(oracle, dtype, K):
+    """Odd leading dimensions of one operand or both, bases on words: read word by word, and up to K = 768."""
+    M, N = 95, 130
+    A, B = gi.make_problem(5000 + K, M, N, K, "int", dtype)
+    ref = _ref(oracle, A, B, dtype)
+    for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        for odd in ((1, 1), (1, 0), (0, 1)):
+            minor = (K if la == 0 else M, N if lb == 0 else K)
+            pads = tuple((minor[i] + odd[i]) % 2 for i in (0, 1)) + (0,)
+            C, cfg = run_gpu(dtype, A, B, la, lb, pads=pads, return_config=True)
+            assert cfg.endswith(" small") and np.array_equal(C.astype(np.float64), ref), (la, lb, odd, cfg)
