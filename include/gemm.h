@@ -249,7 +249,7 @@ int gemm_tune_load(const char *path);
  * leading dimension too long for 32-bit tile offsets, a forced ":regload").  Writes "<tile>:s<splits>"
  * into buf (NUL-terminated, truncated to buflen).  Products of at most one 32x32 block of C per CU and a short K
  * (512 for binary32, 768 for 16-bit operands, 256 for K-contiguous 16-bit rows on 2-byte boundaries, which is
- * assumed here for alignment 2; with both bases on 4-byte boundaries such calls run it up to 768 too) run a kernel
+ * assumed here for alignment 2; with both bases on 4-byte boundaries, rows on 2-byte ones of either kind run it up to 1152) run a kernel
  * of their own in one slice, which has no name: it answers "t64x64:s1", gemm_last_config says "small", and it
  * runs only while nothing is forced or traced (forcing "t64x64:s1" runs the tile kernel of that name).
  * This is the host side of the per-size tuning of Section 5.3, exposed so that it can be

@@ -443,14 +443,15 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
 // 16 bits K = 136 4.3 -> 3.5, 512 4.4 .. 6.2 -> 3.5 .. 4.1, 768 5.2 .. 7.2 -> 3.9 .. 5.0, 1024 with both operands K-contiguous
 // 5.8 .. 5.9 -> 5.7 .. 5.8, 2048 6.4 .. 9.0 -> 6.8 .. 10.2;
 // K-contiguous rows on 2-byte boundaries, whose loads are split up, K = 136 5.2 -> 3.6, 512 5.9 -> 8.2, where the bases are not on
-// words; where they are (words), K = 257 5.3 .. 6.2 -> 2.7 .. 3.7, 511 6.3 .. 7.3 -> 3.5 .. 4.8, 767 7.1 .. 8.6 -> 4.5 .. 6.4.
+// words; where they are (words), K = 257 5.3 .. 6.2 -> 2.7 .. 3.7, 511 6.3 .. 7.3 -> 3.5 .. 4.8, 767 7.1 .. 8.6 -> 4.5 .. 6.4, 1151
+// 7.8 .. 11.1 -> 5.6 .. 8.1 (neither operand K-contiguous 8.2 .. 10.5 -> 4.5 .. 7.4), 1279 8.0 .. 10.6 -> 6.3 .. 9.3, the nearest 9.0 -> 8.7.
 // Twice the blocks lose 10 % and more at any K.  Over 1202 calls inside the rule (all layouts, alignments and types, extents from
 // 1, from 1x8192 to 8192x32) the time is 0.70 of the tile kernels' in the geometric mean; the slowest are K <= 32, where most of
 // the waves have nothing to do (3.2 -> 3.4).
 bool serves_small(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_contig, bool words, int num_cu)
 {
     if (cdiv(M, 32) * cdiv(N, 32) > num_cu) return false;
-    return K <= (f32 ? 512 : (path == 2 && k_contig > 0 && !words ? 256 : 768));
+    return K <= (f32 ? 512 : path == 2 ? (words ? 1152 : (k_contig > 0 ? 256 : 768)) : 768);
 }
 
 // What can be forced, or traced, are the tile kernels: with any such setting the small kernel stays out, whether the

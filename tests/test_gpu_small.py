@@ -75,9 +75,9 @@ def test_a_recorded_pick_of_the_kernel_gives_way_to_the_tile_kernels(oracle, tmp
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("K", [17, 255, 257, 513, 767])
+@pytest.mark.parametrize("K", [17, 255, 257, 767, 1151])
 def test_rows_that_begin_in_the_middle_of_a_word(oracle, dtype, K):
-    """Odd leading dimensions of one operand or both, bases on words: read word by word, and up to K = 768."""
+    """Odd leading dimensions of one operand or both, bases on words: read word by word, and up to K = 1152."""
     M, N = 95, 130
     A, B = gi.make_problem(5000 + K, M, N, K, "int", dtype)
     ref = _ref(oracle, A, B, dtype)
