@@ -988,7 +988,10 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         const int64_t per = cdiv(KT, best_splits);
-        g_tuned[key] = std::make_pair(best_tile, (int)cdiv(KT, per));
+        // (a class does not tell whether rows can be read word by word: where it is that which brings the kernel for small products
+        // in, nothing is recorded and the rule goes on choosing it)
+        if (best_tile == kSmall && !serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, false, key.num_cu)) g_tuned.erase(key);
+        else g_tuned[key] = std::make_pair(best_tile, (int)cdiv(KT, per));
         ++g_epoch;
     }
     // the product, by the configuration just recorded (unless one is forced)
@@ -1111,7 +1114,7 @@ int gemm_tune_load(const char *path)
         const int words = sscanf(line + end, "%7s %1s", kernel, more);
         if (words > 0 && kernel[0] != '#') {
             const bool ok = strcmp(kernel, "small") == 0 && (words == 1 || more[0] == '#') && tile == kSmallAs && slices == 1 &&
-                            serves_small(M, N, K, esz == 4, path_, kc, true, cus);
+                            serves_small(M, N, K, esz == 4, path_, kc, false, cus);
             tile = ok ? kSmall : -1;
         }
         // a tile this build does not have, or one that does not serve the class, makes the file invalid as a whole

@@ -87,3 +87,28 @@ def test_rows_that_begin_in_the_middle_of_a_word(oracle, dtype, K):
             pads = tuple((minor[i] + odd[i]) % 2 for i in (0, 1)) + (0,)
             C, cfg = run_gpu(dtype, A, B, la, lb, pads=pads, return_config=True)
             assert cfg.endswith(" small") and np.array_equal(C.astype(np.float64), ref), (la, lb, odd, cfg)
+
+
+def test_tuning_leaves_the_choice_on_such_rows_to_the_rule(oracle, tmp_path):
+    """A search that finds the kernel fastest there records no pick that a file could not hold; later calls run it all the same."""
+    import torch
+    import paper_2003_06324_amd as g
+    M, N, K = 95, 131, 511
+    A, B = gi.make_problem(5600, M, N, K, "int", "f16")
+    from gpu_util import to_device
+    dA, dB = to_device(gi.store(A, gi.ROW_MAJOR)), to_device(gi.store(B, gi.COL_MAJOR))
+    dC = torch.empty(M * N, dtype=torch.float32, device="cuda")
+    g.force_config(None)
+    g.tune_clear()
+    try:
+        pick = g.tune(g.KIND_F16F32, M, N, K, dA, gi.ROW_MAJOR, 0, dB, gi.COL_MAJOR, 0, dC, gi.ROW_MAJOR, 0, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert np.array_equal(dC.cpu().numpy().reshape(M, N).astype(np.float64), _ref(oracle, A, B, "f16"))
+        picks = str(tmp_path / "picks.txt")
+        g.tune_save(picks)
+        g.tune_clear()
+        g.tune_load(picks)
+        cfg = run_gpu("f16", A, B, 0, 1, return_config=True)[1].split()
+        assert cfg[1] + ":" + cfg[4] == pick, (pick, cfg)
+    finally:
+        g.tune_clear()
