@@ -314,16 +314,17 @@ bool rows_off_lines(const void *p, int64_t ld, int64_t rows) { return (uintptr_t
 // Operands of more than 28 MiB are streamed rather than held by the caches.  A few workgroups do not keep enough loads in flight
 // for that either way, and launches shorter than stage_from lose (128x3520x5120, eight slices of ten slabs, 128x128 15.8 -> 19.8);
 // the others gain, over 420 products of 28 .. 300 MB with 100 .. 256 workgroups 1.49 on 64x64, 1.17 on 128x64, 1.14 on 64x128, 1.06 on
-// 128x128, the last with a full chip too (8192x128x8192 40.6 -> 38.0, on another card 36.4 -> 34.3; 1024x1024x43264 141 -> 110).
+// 128x128, the last with a full chip too (8192x128x8192 40.6 -> 38.0, on another card 36.4 -> 34.3; 1024x1024x43264 141 -> 110).  One row
+// of 128x128 tiles does not run it: 128x8192x8192 35.6 -> 34.1 on three cards, but 35.9 -> 38.1 and 36.1 -> 40.6 on two others.
 // Below 2.5 MiB they stay in the L2s from call to call, and the ring's one slab ahead is enough: 256x512x1024 5.8 -> 6.3,
 // 512x512x1024 5.9 -> 6.3, but 768x512x1024 8.4 -> 6.6.
 // ragged: K or granules, as measured above (operands that gemm_ksplit_kernel cannot take).
 // Rows off the cache lines that are straightened (off_lines 2, from skew_from slabs on) cost nothing more there, in the ring they do:
 // a full chip of 128x128 tiles 1.03 .. 1.10 at K = 2048, 1.07 .. 1.16 at 4096 (2048x2048x2048 with rows padded by 16 bytes 26.1 -> 23.7).
-bool runs_stage(const TileConfig &t, int64_t workgroups, int64_t slabs, int64_t K, bool ragged, int path, int64_t operand_bytes, int off_lines, int num_cu)
+bool runs_stage(const TileConfig &t, int64_t M, int64_t workgroups, int64_t slabs, int64_t K, bool ragged, int path, int64_t operand_bytes, int off_lines, int num_cu)
 {
     if (t.stage16 == nullptr || workgroups > num_cu) return false;
-    if (operand_bytes > (28LL << 20)) return slabs >= t.stage_from && 8 * workgroups >= 3 * num_cu;
+    if (operand_bytes > (28LL << 20)) return slabs >= t.stage_from && 8 * workgroups >= 3 * num_cu && (M > t.BM || t.BM * t.BN < 128 * 128);
     if (K % 64 != 0) return true;
     if (ragged) return slabs >= 8;
     return slabs >= t.stage_from && operand_bytes >= (5LL << 19) &&
@@ -402,7 +403,7 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     slab *= foot_factor;
     // (its slab time hardly depends on where the operands come from; where it runs it is not behind the other kernel, whose
     // time for small operands is the lower one; a ragged last slab is one more)
-    if (!f32 && (path == 0 || path == 3) && runs_stage(t, W, per, K, !ksplit_ok, path, (M + N) * K * 2, off_lines, NUM_CU)) {
+    if (!f32 && (path == 0 || path == 3) && runs_stage(t, M, W, per, K, !ksplit_ok, path, (M + N) * K * 2, off_lines, NUM_CU)) {
         double stage = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : (off_lines ? t.stage_off : 1.0));
         if (foot > kStreamed) stage *= 1.0 + (t.BM + t.BN < 256 ? 0.35 : 0.1) * log2(foot / kStreamed);
         if (stage < slab) slab = stage;
@@ -853,7 +854,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     } else {
         const dim3 grid((unsigned)work_grid((int)(tiles_m * tiles_n), a.whole_tiles, a.splits));
         launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
-        const bool stage = !f32 && aligned && runs_stage(t, tiles_m * tiles_n * splits, kt_per_split, K, !ksplit_ok, path, (M + N) * K * (int64_t)sizeof(T), off_lines, num_cu);
+        const bool stage = !f32 && aligned && runs_stage(t, M, tiles_m * tiles_n * splits, kt_per_split, K, !ksplit_ok, path, (M + N) * K * (int64_t)sizeof(T), off_lines, num_cu);
         const bool skew = stage && off_lines == 2 && kt_per_split >= t.skew_from;
         if (skew) fn = bf16 ? t.skew_bf16 : t.skew16;
         else if (stage) fn = bf16 ? t.stage_bf16 : t.stage16;
