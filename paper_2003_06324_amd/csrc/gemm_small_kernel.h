@@ -14,10 +14,38 @@ namespace gemm_gfx950 {
 
 constexpr int SMALL_WAVES = 16;
 
+__host__ __device__ __forceinline__ uint32_t two_words_shifted(uint32_t hi, uint32_t lo, int bits)
+{
+#if defined(__HIP_DEVICE_COMPILE__)  // (of the 64-bit shift the compiler makes two instructions, one of them a slow one)
+    return __builtin_amdgcn_alignbit(hi, lo, bits);
+#else
+    return (uint32_t)((((uint64_t)hi << 32) | lo) >> bits);
+#endif
+}
+
+// Eight 16-bit elements that may begin in the middle of a word, read as the words they begin in and the last element by itself
+// (nothing behind it, which may be nobody's), and shifted into place.  What makes the reads is handed in.
+template <typename Read>
+__host__ __device__ __forceinline__ uint4_t words_of(const uint16_t *p, const Read &read)
+{
+    const int late = (int)((uintptr_t)p >> 1) & 1;
+    const uint4_t w = read.words(p - late);
+    const uint32_t last = read.element(p + 7);
+    uint4_t o;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) o[x] = two_words_shifted(x < 3 ? w[x + 1] : last, w[x], 16 * late);
+    return o;
+}
+struct GlobalRead {
+    typedef uint4_t words_t __attribute__((aligned(4)));
+    __host__ __device__ __forceinline__ uint4_t words(const uint16_t *p) const { return *(const words_t *)p; }
+    __host__ __device__ __forceinline__ uint32_t element(const uint16_t *p) const { return *p; }
+};
+
 // The fragment of one k-group: EPL consecutive k of one row, zero from kend on (full: the group lies below kend).
-// words: 16-bit rows of which every second one begins in the middle of a word are read from the word on that holds the fragment's
-// first element, and shifted: 16 bytes from such an address are split up by the memory pipeline, which a product of one round of
-// loads waits for (255x255x255 NT 5.1 us, with this 3.4; 109x451x137 3.22, 2.95).
+// words: 16-bit rows of which every second one begins in the middle of a word are read word by word: 16 bytes from such an
+// address are split up by the memory pipeline, which a product of one round of loads waits for (255x255x255 NT 5.1 us, with
+// this 3.4; 109x451x137 3.22, 2.95).
 template <typename T, bool KC>
 __device__ __forceinline__ typename Frag<T>::type small_fragment(const T *base, int64_t ld, int64_t row, int k, int kend, bool full, bool words)
 {
@@ -28,14 +56,7 @@ __device__ __forceinline__ typename Frag<T>::type small_fragment(const T *base, 
         typedef frag_t loose_t __attribute__((aligned(sizeof(T))));
         const T *p = base + row * ld + k;
         if (full && sizeof(T) == 2 && words) {
-            typedef uint4_t words_t __attribute__((aligned(4)));
-            const int late = (int)((uintptr_t)p >> 1) & 1;
-            const uint4_t w = *(const words_t *)(p - late);
-            const uint32_t behind = *(const uint32_t *)(p + 6 + late);  // (not late: the last word again)
-            uint4_t o;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) o[x] = __builtin_amdgcn_alignbit(x < 3 ? w[x + 1] : behind, w[x], 16 * late);
-            f = __builtin_bit_cast(frag_t, o);
+            f = __builtin_bit_cast(frag_t, words_of((const uint16_t *)p, GlobalRead()));
         } else if (full) {
             f = *(const loose_t *)p;
         } else {

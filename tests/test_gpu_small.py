@@ -112,3 +112,16 @@ def test_tuning_leaves_the_choice_on_such_rows_to_the_rule(oracle, tmp_path):
         assert cfg[1] + ":" + cfg[4] == pick, (pick, cfg)
     finally:
         g.tune_clear()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K", [16, 256, 768, 1152])
+def test_whole_k_groups_on_such_rows(oracle, dtype, K):
+    """The last fragment of the last row ends with the operand, in the upper half of a word or the lower one."""
+    for M, N in ((96, 130), (95, 33)):
+        A, B = gi.make_problem(5100 + K, M, N, K, "int", dtype)
+        ref = _ref(oracle, A, B, dtype)
+        for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+            minor = (K if la == 0 else M, N if lb == 0 else K)
+            C, cfg = run_gpu(dtype, A, B, la, lb, pads=(1 + minor[0] % 2, 1 + minor[1] % 2, 0), return_config=True)
+            assert cfg.endswith(" small") and np.array_equal(C.astype(np.float64), ref), (M, la, lb, cfg)
