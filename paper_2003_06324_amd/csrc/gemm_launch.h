@@ -61,14 +61,34 @@ hipError_t launch_ksplit(bool akc, bool bkc, bool aligned, dim3 grid, hipStream_
     return launch_kernel(gemm_ksplit_kernel<T, BM, BN, false, false>, grid, block, s, a);
 }
 
+// AW: false where small_by_words has no form for it (binary32, operands that are not K-contiguous)
+template <typename T, bool AKC, bool BKC, bool AW>
+static hipError_t launch_small_b(bool words_b, dim3 grid, hipStream_t s, const KernelArgs &a)
+{
+    const dim3 block(SMALL_WAVES * 64);
+    if constexpr (BKC && sizeof(T) == 2) {
+        if (words_b) return launch_kernel(gemm_small_kernel<T, AKC, BKC, AW, true>, grid, block, s, a);
+    }
+    return launch_kernel(gemm_small_kernel<T, AKC, BKC, AW, false>, grid, block, s, a);
+}
+
+template <typename T, bool AKC, bool BKC>
+static hipError_t launch_small_ab(dim3 grid, hipStream_t s, const KernelArgs &a)
+{
+    const bool words_b = small_by_words<T>(a.B, a.ldb);
+    if constexpr (AKC && sizeof(T) == 2) {
+        if (small_by_words<T>(a.A, a.lda)) return launch_small_b<T, AKC, BKC, true>(words_b, grid, s, a);
+    }
+    return launch_small_b<T, AKC, BKC, false>(words_b, grid, s, a);
+}
+
 template <typename T>
 hipError_t launch_small(bool akc, bool bkc, dim3 grid, hipStream_t s, const KernelArgs &a)
 {
-    const dim3 block(SMALL_WAVES * 64);
-    if (akc && bkc) return launch_kernel(gemm_small_kernel<T, true, true>, grid, block, s, a);
-    if (akc && !bkc) return launch_kernel(gemm_small_kernel<T, true, false>, grid, block, s, a);
-    if (!akc && bkc) return launch_kernel(gemm_small_kernel<T, false, true>, grid, block, s, a);
-    return launch_kernel(gemm_small_kernel<T, false, false>, grid, block, s, a);
+    if (akc && bkc) return launch_small_ab<T, true, true>(grid, s, a);
+    if (akc && !bkc) return launch_small_ab<T, true, false>(grid, s, a);
+    if (!akc && bkc) return launch_small_ab<T, false, true>(grid, s, a);
+    return launch_small_ab<T, false, false>(grid, s, a);
 }
 
 // binary32, 16x16 blocks; a function template so that only its instantiation file compiles the kernel

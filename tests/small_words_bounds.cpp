@@ -47,7 +47,9 @@ int main()
                     for (int g = 0; g < K / KG; ++g)  // whole k-groups; what is left of K is read element by element
                         for (int half = 0; half < 2; ++half) {
                             const uint16_t *p = base + r * ld + g * KG + half * KG / 2;
-                            const uint4_t f = words_of(p, read);
+                            WordFragment words;
+                            words.read(p, read);
+                            const uint4_t f = words.shifted();
                             if (memcmp(&f, p, 16) != 0) ++g_wrong;
                         }
             }
