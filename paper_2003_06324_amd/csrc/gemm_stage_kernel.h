@@ -246,13 +246,18 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
     auto prepare = [&]() {
         la.exact_range();
         lb.exact_range();
-        if ((h == n - 1 && krem < BK) || (SKEW && h == n)) {
-            la.ragged_slab(krem - (h - (n - 1)) * BK, wave, lane);
-            lb.ragged_slab(krem - (h - (n - 1)) * BK, wave, lane);
-        }
-        if constexpr (SKEW) {  // the image behind the last slab is one of skewed rows only
+        if constexpr (SKEW) {
+            const int left = krem - (h - (n - 1)) * BK;  // k from the image's beginning to the end of the last slab, none or less behind it
+            if ((h == n - 1 && krem < BK) || h == n) {
+                la.ragged_slab(left, wave, lane);
+                lb.ragged_slab(left, wave, lane);
+            }
+            // the image behind the last slab is one of skewed rows only
             if (!AKC && h >= n) la.no_range();
             if (!BKC && h >= n) lb.no_range();
+        } else if (h == n - 1 && krem < BK) {  // (apart from the above: the code that runs once costs by its length)
+            la.ragged_slab(krem, wave, lane);
+            lb.ragged_slab(krem, wave, lane);
         }
     };
     auto advance = [&]() {
