@@ -315,20 +315,24 @@ bool rows_off_lines(const void *p, int64_t ld, int64_t rows) { return (uintptr_t
 // for that either way, and launches shorter than stage_from lose (128x3520x5120, eight slices of ten slabs, 128x128 15.8 -> 19.8);
 // the others gain, over 420 products of 28 .. 300 MB with 100 .. 256 workgroups 1.49 on 64x64, 1.17 on 128x64, 1.14 on 64x128, 1.06 on
 // 128x128, the last with a full chip too (8192x128x8192 40.6 -> 38.0, on another card 36.4 -> 34.3; 1024x1024x43264 141 -> 110).  One row
-// of 128x128 tiles does not run it: 128x8192x8192 35.6 -> 34.1 on three cards, but 35.9 -> 38.1 and 36.1 -> 40.6 on two others.
+// of 128x128 tiles 1.10 at up to 15/16 of the CUs, over 249 products of up to 128 rows (all layouts, N and K from 1024 to 16384), but
+// a full chip of them is behind, as it is on operands that the caches hold (stage_most), whatever the leading dimension: TN 128x8192x8192
+// 35.6 -> 38.4 us, 128x8192x6144 29.3 -> 33.9, with rows of B 9216 elements apart 36.5 -> 38.5 and 29.7 -> 33.5; NT 128x4096x16384
+// 42.9 -> 46.5.  A column of tiles is not: TN 8192x128x8192 40.4 -> 38.3, 8192x128x6144 35.6 -> 34.0.
 // Below 2.5 MiB they stay in the L2s from call to call, and the ring's one slab ahead is enough: 256x512x1024 5.8 -> 6.3,
 // 512x512x1024 5.9 -> 6.3, but 768x512x1024 8.4 -> 6.6.
 // ragged: K or granules, as measured above (operands that gemm_ksplit_kernel cannot take).
-// Rows off the cache lines that are straightened (off_lines 2, from skew_from slabs on) cost nothing more there, in the ring they do:
-// a full chip of 128x128 tiles 1.03 .. 1.10 at K = 2048, 1.07 .. 1.16 at 4096 (2048x2048x2048 with rows padded by 16 bytes 26.1 -> 23.7).
+// Rows off the cache lines that are straightened (off_lines 2, from skew_from slabs on) cost nothing more on a full chip, in the ring they do:
+// a full chip of 128x128 tiles 1.03 .. 1.10 at K = 2048, 1.07 .. 1.16 at 4096 (2048x2048x2048 with rows padded by 16 bytes
+// 26.1 -> 23.7; 128x8192x8192 NT 45.3 -> 35.7).
 bool runs_stage(const TileConfig &t, int64_t M, int64_t workgroups, int64_t slabs, int64_t K, bool ragged, int path, int64_t operand_bytes, int off_lines, int num_cu)
 {
     if (t.stage16 == nullptr || workgroups > num_cu) return false;
-    if (operand_bytes > (28LL << 20)) return slabs >= t.stage_from && 8 * workgroups >= 3 * num_cu && (M > t.BM || t.BM * t.BN < 128 * 128);
+    const bool pays = 16 * workgroups <= t.stage_most * num_cu || (off_lines == 2 && slabs >= t.skew_from);
+    if (operand_bytes > (28LL << 20)) return slabs >= t.stage_from && 8 * workgroups >= 3 * num_cu && (M > t.BM || pays);
     if (K % 64 != 0) return true;
     if (ragged) return slabs >= 8;
-    return slabs >= t.stage_from && operand_bytes >= (5LL << 19) &&
-           (path == 3 || 16 * workgroups <= t.stage_most * num_cu || (off_lines == 2 && slabs >= t.skew_from));
+    return slabs >= t.stage_from && operand_bytes >= (5LL << 19) && (path == 3 || pays);
 }
 
 size_t tail_bytes(const TileConfig &t, int64_t sliced, int splits) { return (size_t)sliced * (size_t)splits * (size_t)(t.BM * t.BN) * sizeof(float); }

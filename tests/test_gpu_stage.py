@@ -81,3 +81,19 @@ def test_same_bits_as_the_register_staged_kernel(tile):
             runs, ran = zip(*((run_gpu("f16", A, B, la, lb, pads=pads, force="%s:s2%s" % (tile, how)), g.last_kernel()) for how in ("", ":safe", ":regload")))
             assert ran == ("gemm_stage_kernel", "gemm_stage_kernel", "gemm_tile_kernel")
             assert np.array_equal(runs[0], runs[1]) and np.array_equal(runs[0], runs[2]), (M, N, K, la, lb)
+
+
+@pytest.mark.parametrize("M,N,K", [(120, 3064, 6144), (3072, 128, 6176)])
+def test_one_row_or_column_of_tiles_on_streamed_operands(M, N, K):
+    """Operands of more than 28 MiB, 96 workgroups, 24 slabs or 25 each."""
+    A, B = gi.make_problem(M + K, M, N, K, "normal", "f16")
+    assert (M + N) * K * 2 > 28 << 20
+    for la, lb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        runs, ran = zip(*((run_gpu("f16", A, B, la, lb, force="t128x128:s4" + how), g.last_kernel()) for how in ("", ":regload")))
+        assert ran == ("gemm_stage_kernel", "gemm_tile_kernel")
+        assert np.array_equal(runs[0], runs[1]), (la, lb)
+    zeros = np.zeros((128, 8192), np.float16), np.zeros((8192, 8192), np.float16)
+    run_gpu("f16", *zeros, 0, 1, force="t128x128:s4")                    # a full chip of one row; its rows straightened
+    assert g.last_kernel() == "gemm_tile_kernel"
+    run_gpu("f16", *zeros, 0, 1, pads=(8, 8, 0), force="t128x128:s4")
+    assert g.last_kernel() == "gemm_stage_kernel"
