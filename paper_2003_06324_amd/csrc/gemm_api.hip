@@ -201,9 +201,8 @@ struct TileConfig {
                                 // which the automatic selection considers this configuration, for 16-bit and for
                                 // binary32 operands; 0: only when forced
     launch_fn stage16, stage_bf16;  // gemm_stage_kernel (null: none), see runs_stage
-    launch_fn skew16, skew_bf16;    // the same for rows off the cache lines, see runs_skew
-    double stage_slab, stage_a4;    // its slab time (microseconds per 64 k, one workgroup on a CU), on 4-/8-byte aligned operands over that,
-    double stage_off;               // and on 16-byte aligned rows off the cache lines
+    launch_fn skew16, skew_bf16;    // the same for rows off the cache lines, see rows_off_lines
+    double stage_slab, stage_a4;    // its slab time (microseconds per 64 k, one workgroup on a CU), on 4-/8-byte aligned operands over that
     int stage_from;                 // slabs from which it is ahead on whole ones
     int stage_most;                 // sixteenths of the CUs up to which it is ahead on whole slabs of 16-byte rows
     int skew_from;                  // slabs from which it straightens rows off the cache lines
@@ -224,24 +223,24 @@ struct TileConfig {
 // (64x128 before 128x64: the model often ties the two, and the tie goes to the first; 64x128 measures 4-8 % ahead)
 const TileConfig kTiles[] = {
     {"t256x256", 256, 256, 1, 1.02, 1.02, 6.98, 6.98, 7.2, 0.83, 1.2, 1.05, 1.67, 1.25, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
     {"t128x128", 128, 128, 2, 0.457, 0.868, 1.99, 3.64, 1.92, 1.39, 1.23, 0.817, 1.57, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.40, 1.435, 1.03, 24, 15, 24},
+     GEMM_TILE_LAUNCHERS(128, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 128, 4), 0.40, 1.435, 24, 15, 24},
     {"t64x64", 64, 64, 4, 0.265, 0.855, 0.495, 1.86, 1.27, 0.78, 1.07, 0.992, 1.65, 1.35, 4,
-     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.20, 1.55, 1.10, 16, 16, 32},
+     GEMM_TILE_LAUNCHERS(64, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 64, 6), 0.20, 1.55, 16, 16, 32},
     {"t256x256w8", 256, 256, 1, 1.05, 1.05, 7.6, 7.6, 6.02, 0.812, 1.2, 0.915, 1.35, 1.15, 1,
-     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(256, 256, 2, 4), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
     {"t256x128", 256, 128, 1, 0.71, 0.71, 3.52, 3.52, 3.82, 0.637, 1.2, 1.09, 1.47, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(256, 128, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
     {"t128x256", 128, 256, 1, 0.661, 0.661, 4.19, 4.19, 4.17, 1.78, 1.25, 0.864, 2.03, 1.3, 1,
-     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
+     GEMM_TILE_LAUNCHERS(128, 256, 2, 2), -1, 15, 15, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
     {"t64x128", 64, 128, 2, 0.349, 0.512, 1.12, 1.86, 1.67, 1.11, 1.31, 0.884, 1.87, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.265, 1.585, 1.12, 16, 16, 24},
+     GEMM_TILE_LAUNCHERS(64, 128, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(64, 128, 5), 0.265, 1.585, 16, 16, 24},
     {"t128x64", 128, 64, 2, 0.371, 0.617, 1.14, 1.81, 1.33, 1.06, 1.31, 0.919, 1.84, 1.3, 3,
-     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.285, 1.63, 1.12, 16, 16, 24},
+     GEMM_TILE_LAUNCHERS(128, 64, 2, 2), -1, 15, 15, GEMM_STAGE_LAUNCHERS(128, 64, 5), 0.285, 1.63, 16, 16, 24},
     // K split across the four waves of the workgroup (Section 5.3, small sizes); fitted on 16-byte aligned operands only
     {"k64x64", 64, 64, 4, 0.311, 0.854, 0.598, 2.02, 2.02, 0.781, 1.07, 0.992, 1.65, 1.0, 1,
-     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, 0, 0},
+     launch_ksplit<_Float16, 64, 64>, launch_ksplit<float, 64, 64>, launch_ksplit<__bf16, 64, 64>, 2, 1, 1, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, 0, 0, 0},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -322,13 +321,13 @@ bool rows_off_lines(const void *p, int64_t ld, int64_t rows) { return (uintptr_t
 // Below 2.5 MiB they stay in the L2s from call to call, and the ring's one slab ahead is enough: 256x512x1024 5.8 -> 6.3,
 // 512x512x1024 5.9 -> 6.3, but 768x512x1024 8.4 -> 6.6.
 // ragged: K or granules, as measured above (operands that gemm_ksplit_kernel cannot take).
-// Rows off the cache lines that are straightened (off_lines 2, from skew_from slabs on) cost nothing more on a full chip, in the ring they do:
+// Rows off the cache lines that are straightened (off_lines, from skew_from slabs on) cost nothing more on a full chip, in the ring they do:
 // a full chip of 128x128 tiles 1.03 .. 1.10 at K = 2048, 1.07 .. 1.16 at 4096 (2048x2048x2048 with rows padded by 16 bytes
 // 26.1 -> 23.7; 128x8192x8192 NT 45.3 -> 35.7).
-bool runs_stage(const TileConfig &t, int64_t M, int64_t workgroups, int64_t slabs, int64_t K, bool ragged, int path, int64_t operand_bytes, int off_lines, int num_cu)
+bool runs_stage(const TileConfig &t, int64_t M, int64_t workgroups, int64_t slabs, int64_t K, bool ragged, int path, int64_t operand_bytes, bool off_lines, int num_cu)
 {
     if (t.stage16 == nullptr || workgroups > num_cu) return false;
-    const bool pays = 16 * workgroups <= t.stage_most * num_cu || (off_lines == 2 && slabs >= t.skew_from);
+    const bool pays = 16 * workgroups <= t.stage_most * num_cu || (off_lines && slabs >= t.skew_from);
     if (operand_bytes > (28LL << 20)) return slabs >= t.stage_from && 8 * workgroups >= 3 * num_cu && (M > t.BM || pays);
     if (K % 64 != 0) return true;
     if (ragged) return slabs >= 8;
@@ -374,7 +373,7 @@ int tail_slices(const TileConfig &t, int64_t tiles, int64_t KT, bool f32, int nu
 // classes depend on it (a K-contiguous row is what straddles lines or gets its loads split)
 // ksplit_ok: as for choose_uncached
 double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64_t KT, int splits, bool f32,
-                     int path, int k_contig, int NUM_CU, size_t max_ws_bytes, bool ksplit_ok, int off_lines)
+                     int path, int k_contig, int NUM_CU, size_t max_ws_bytes, bool ksplit_ok)
 {
     static const double kLayA4[3] = {0.867, 1.0, 0.986};  // 16-bit, path 3, by k_contig
     static const double kLayA2[3] = {1.14, 1.0, 1.19};   // 16-bit, path 2
@@ -406,9 +405,12 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     if (path == 1 || path == 2) slab *= f32 ? 1.05 : (path == 2 ? t.f16_a2 * kLayA2[k_contig] : t.general);
     slab *= foot_factor;
     // (its slab time hardly depends on where the operands come from; where it runs it is not behind the other kernel, whose
-    // time for small operands is the lower one; a ragged last slab is one more)
-    if (!f32 && (path == 0 || path == 3) && runs_stage(t, M, W, per, K, !ksplit_ok, path, (M + N) * K * 2, off_lines, NUM_CU)) {
-        double stage = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : (off_lines ? t.stage_off : 1.0));
+    // time for small operands is the lower one; a ragged last slab is one more.  16-byte rows are priced alike wherever they begin, on
+    // the cache lines or off them, so a shape has one pick, which gemm_query_config can tell: with a price of their own for rows off the
+    // lines the 240 of 3176 drawn products with such rows that had another pick took 1.015 times as long; where an operand is
+    // K-contiguous, and straightened or not, 1.026, where neither is, 0.97)
+    if (!f32 && (path == 0 || path == 3) && runs_stage(t, M, W, per, K, !ksplit_ok, path, (M + N) * K * 2, false, NUM_CU)) {
+        double stage = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : 1.0);
         if (foot > kStreamed) stage *= 1.0 + (t.BM + t.BN < 256 ? 0.35 : 0.1) * log2(foot / kStreamed);
         if (stage < slab) slab = stage;
         tail = 0.0;
@@ -478,13 +480,14 @@ double between_margin(int slices, bool f32) { return (slices & (slices - 1)) == 
 // max_ws_bytes: largest K-slice workspace the caller can provide (0 = no limit); automatic
 // picks that would need more are not considered.
 // ksplit_ok: the operands qualify for the kernels that split K across the waves of a workgroup
+// words: rows begin in the middle of a word, and gemm_small_kernel can read them word by word
 void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int path, int k_contig, int num_cu,
-                     size_t max_ws_bytes, bool ksplit_ok, int off_lines, int &tile, int &splits)
+                     size_t max_ws_bytes, bool ksplit_ok, bool words, int &tile, int &splits)
 {
     double best = 1e300;
     tile = g_forced_tile >= 0 ? g_forced_tile : 0;
     splits = 1;
-    if (small_allowed() && serves_small(M, N, K, f32, path, k_contig, off_lines == 3, num_cu)) {
+    if (small_allowed() && serves_small(M, N, K, f32, path, k_contig, words, num_cu)) {
         tile = kSmall;
         return;
     }
@@ -498,7 +501,7 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
             const int cand = forced > 0 ? forced : s;
             if (cand > 1 && cand > KT) break;
             if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
-            const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu, max_ws_bytes, ksplit_ok, off_lines) *
+            const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu, max_ws_bytes, ksplit_ok) *
                              (forced > 0 ? 1.0 : between_margin(s, f32));
             if (c < best) { best = c; tile = t; splits = cand; }
             if (forced > 0) break;
@@ -513,7 +516,7 @@ struct Pick {
     int64_t M = -1, N = 0, K = 0;
     size_t max_ws = 0;
     uint64_t epoch = 0;
-    int f32 = 0, path = 0, k_contig = 0, num_cu = 0, ksplit_ok = 0, off_lines = 0, tile = 0, splits = 0;
+    int f32 = 0, path = 0, k_contig = 0, num_cu = 0, ksplit_ok = 0, words = 0, tile = 0, splits = 0;
 };
 Pick g_picks[64];
 uint64_t g_epoch = 1;
@@ -537,14 +540,14 @@ struct TuneRequest {
     int tile = -1, splits = 1;
     ShapeKey key{};
     bool filled = false;
-    int off_lines = 0;  // as in gemm_impl
+    bool words = false;  // as for choose_uncached
 };
 
 void choose(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int path, int k_contig, int num_cu,
-            size_t max_ws_bytes, bool ksplit_ok, int off_lines, int &tile, int &splits)
+            size_t max_ws_bytes, bool ksplit_ok, bool words, int &tile, int &splits)
 {
     const uint64_t h = (uint64_t)M * 0x9E3779B97F4A7C15ull ^ (uint64_t)N * 0xC2B2AE3D27D4EB4Full ^
-                       (uint64_t)K * 0x165667B19E3779F9ull ^ (uint64_t)((uint64_t)off_lines * 64 + k_contig * 16 + path * 4 + f32 * 2 + ksplit_ok);
+                       (uint64_t)K * 0x165667B19E3779F9ull ^ (uint64_t)(words * 64 + k_contig * 16 + path * 4 + f32 * 2 + ksplit_ok);
     if (g_forced_tile < 0 && g_forced_splits == 0 && !g_tuned.empty()) {
         const auto it = g_tuned.find(ShapeKey{M, N, K, (int)f32, path, k_contig, num_cu, (int)ksplit_ok});
         if (it != g_tuned.end() && (it->second.first != kSmall || small_allowed()) && (max_ws_bytes == 0 || it->second.second == 1 ||
@@ -556,14 +559,14 @@ void choose(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int path, int
     }
     Pick &e = g_picks[(h >> 32) & 63];
     if (e.M == M && e.N == N && e.K == K && e.max_ws == max_ws_bytes && e.epoch == g_epoch && e.f32 == (int)f32 &&
-        e.path == path && e.k_contig == k_contig && e.num_cu == num_cu && e.ksplit_ok == (int)ksplit_ok && e.off_lines == off_lines) {
+        e.path == path && e.k_contig == k_contig && e.num_cu == num_cu && e.ksplit_ok == (int)ksplit_ok && e.words == (int)words) {
         tile = e.tile;
         splits = e.splits;
         return;
     }
-    choose_uncached(M, N, K, KT, f32, path, k_contig, num_cu, max_ws_bytes, ksplit_ok, off_lines, tile, splits);
+    choose_uncached(M, N, K, KT, f32, path, k_contig, num_cu, max_ws_bytes, ksplit_ok, words, tile, splits);
     e.M = M; e.N = N; e.K = K; e.max_ws = max_ws_bytes; e.epoch = g_epoch; e.f32 = f32; e.path = path; e.k_contig = k_contig;
-    e.num_cu = num_cu; e.ksplit_ok = ksplit_ok; e.off_lines = off_lines; e.tile = tile; e.splits = splits;
+    e.num_cu = num_cu; e.ksplit_ok = ksplit_ok; e.words = words; e.tile = tile; e.splits = splits;
 }
 
 bool bad_matrix(const void *p, int layout, int64_t &ld, int64_t rows, int64_t cols)
@@ -737,21 +740,19 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     const int64_t KT = cdiv(K, BK);
     int tile, splits;
     const bool ksplit_ok = aligned && !ragged && K % BK == 0;
-    // 1: rows of an operand begin off the cache lines, 2: and gemm_stage_kernel can straighten them; 3: rows begin in the middle of a
-    // word, and gemm_small_kernel can read them word by word
-    const int off_lines = f32 ? 0 : !aligned ? (path == 2 && (((uintptr_t)A | (uintptr_t)B) & 3) == 0 ? 3 : 0)
-                          : ((akc && rows_off_lines(A, lda, M)) || (bkc && rows_off_lines(B, ldb, N)) ? 2 : ((lda | ldb) * 2 % 128 != 0 ? 1 : 0));
+    // rows begin in the middle of a word, and gemm_small_kernel can read them word by word
+    const bool words = !f32 && path == 2 && (((uintptr_t)A | (uintptr_t)B) & 3) == 0;
     if (tune) {
         tune->key = ShapeKey{M, N, K, (int)f32, path, (int)akc + (int)bkc, num_cu, (int)ksplit_ok};
         tune->filled = true;
-        tune->off_lines = off_lines;
+        tune->words = words;
     }
     if (tune && tune->tile >= 0) {
         tile = tune->tile;
         splits = (int)(tune->splits < KT ? tune->splits : KT);
     } else {
         choose(M, N, K, KT, f32, path, (int)akc + (int)bkc, num_cu, noalloc ? (size_t)GEMM_NOALLOC_SCRATCH_BYTES : 0,
-               ksplit_ok, off_lines, tile, splits);
+               ksplit_ok, words, tile, splits);
         // A stream under capture cannot be given a larger workspace: a pick in K-slices that needs one gives way to the best in
         // one slice, so that which calls can be captured does not depend on the model's constants.
         if (splits > 1 && !noalloc && tune == nullptr && g_forced_splits == 0 &&
@@ -759,7 +760,7 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
             hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
             if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
             else if (status == hipStreamCaptureStatusActive)
-                choose(M, N, K, KT, f32, path, (int)akc + (int)bkc, num_cu, 1, ksplit_ok, off_lines, tile, splits);
+                choose(M, N, K, KT, f32, path, (int)akc + (int)bkc, num_cu, 1, ksplit_ok, words, tile, splits);
         }
     }
     const bool small = tile == kSmall;
@@ -858,8 +859,9 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     } else {
         const dim3 grid((unsigned)work_grid((int)(tiles_m * tiles_n), a.whole_tiles, a.splits));
         launch_fn fn = f32 ? t.f32 : (bf16 ? t.bf16 : t.f16);
+        const bool off_lines = (akc && rows_off_lines(A, lda, M)) || (bkc && rows_off_lines(B, ldb, N));
         const bool stage = !f32 && aligned && runs_stage(t, M, tiles_m * tiles_n * splits, kt_per_split, K, !ksplit_ok, path, (M + N) * K * (int64_t)sizeof(T), off_lines, num_cu);
-        const bool skew = stage && off_lines == 2 && kt_per_split >= t.skew_from;
+        const bool skew = stage && off_lines && kt_per_split >= t.skew_from;
         if (skew) fn = bf16 ? t.skew_bf16 : t.skew16;
         else if (stage) fn = bf16 ? t.stage_bf16 : t.stage16;
         kernel = stage ? "gemm_stage_kernel" : (t.fallback >= 0 ? "gemm_ksplit_kernel" : "gemm_tile_kernel");
@@ -913,13 +915,13 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     std::vector<std::tuple<double, int, int>> cand;
     {
         std::lock_guard<std::mutex> lock(g_mutex);
-        if (small_allowed() && serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, req.off_lines == 3, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
+        if (small_allowed() && serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, req.words, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
         for (int t = 0; t < kNumTiles; ++t) {
             if (kTiles[t].fallback >= 0 && !key.ksplit_ok) continue;
             for (const int s : kSlices) {
                 if (s > 1 && s > KT) break;
                 cand.emplace_back(estimate_cost(kTiles[t], key.M, key.N, key.K, KT, s, key.f32 != 0, key.path, key.k_contig,
-                                                key.num_cu, 0, key.ksplit_ok != 0, req.off_lines) * between_margin(s, key.f32 != 0), t, s);
+                                                key.num_cu, 0, key.ksplit_ok != 0) * between_margin(s, key.f32 != 0), t, s);
             }
         }
     }
@@ -1155,7 +1157,7 @@ int gemm_query_config_layouts(int elem_bytes, int64_t M, int64_t N, int64_t K, i
         // 16 or more (or 1): direct loads, aligned; 8 or 4: direct loads on misaligned rows; 0: register-staged
         // (operand extents that are not multiples of the granule); 2: register-staged, 2-byte aligned
         const int path = (aligned == 1 || aligned >= 16) ? 0 : (aligned == 2 ? 2 : (aligned >= 4 ? 3 : 1));
-        choose(M, N, K, KT, f32, path, k_contig, kDefaultNumCU, 0, (path == 0 || path == 3) && K % BK == 0, 0, tile, splits);
+        choose(M, N, K, KT, f32, path, k_contig, kDefaultNumCU, 0, (path == 0 || path == 3) && K % BK == 0, false, tile, splits);
     }
     const int64_t per = cdiv(KT, splits);
     splits = (int)cdiv(KT, per);  // no empty slices, as in the launch path
