@@ -361,57 +361,94 @@ int tail_slices(const TileConfig &t, int64_t tiles, int64_t KT, bool f32, int nu
     return tail_gain(t, sliced, KT, (int)s, f32) > 0.0 ? (int)s : 1;
 }
 
+// What estimate_cost prices, and what is the same for every configuration.
+struct Problem {
+    int64_t M, N, K, KT;
+    bool f32;
+    int path, k_contig, num_cu;  // path: 0 = direct-load kernels, 1 = register-staged loads, 2 = register-staged loads of operands
+                                 // that are only 2-byte aligned (each 16-byte load is then split up by the memory pipeline),
+                                 // 3 = direct-load kernels on operands that are 4- or 8-byte aligned (row pieces straddle cache lines)
+                                 // k_contig: how many of A and B have K as their contiguous dimension (0..2); the misaligned
+                                 // classes depend on it (a K-contiguous row is what straddles lines or gets its loads split)
+    size_t max_ws_bytes;         // see choose_uncached, ksplit_ok too
+    bool ksplit_ok;
+    double bytes;        // of A and B
+    double foot_factor;  // on the slab time, of operands that the XCDs' L2s hold
+    double streamed;     // doublings of bytes beyond those from which the stage kernel's slabs come later, or 0
+
+    Problem(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int path, int k_contig, int num_cu, size_t max_ws_bytes, bool ksplit_ok)
+        : M(M), N(N), K(K), KT(KT), f32(f32), path(path), k_contig(k_contig), num_cu(num_cu), max_ws_bytes(max_ws_bytes), ksplit_ok(ksplit_ok)
+    {
+        // Operands small enough to stay in the XCDs' L2s between and within calls are served faster than ones that come
+        // from the memory side: the slab time falls, log-linearly in the bytes of A and B, from 1 x at kFootHi bytes to
+        // kFootFactor x at kFootLo bytes and below (fitted on the paper's power-of-two sizes, where it decides between
+        // one slice and several for the sizes up to 1024).
+        static const double kStreamed = 60e6;
+        static const double kFootLo = 2.23e+05, kFootHi = 1.52e+07, kFootFactor = 0.29;
+        bytes = ((double)M * K + (double)K * N) * (f32 ? 4.0 : 2.0);
+        foot_factor = bytes <= kFootLo ? kFootFactor
+                      : (bytes >= kFootHi ? 1.0 : exp(log(kFootFactor) * (log(kFootHi) - log(bytes)) / (log(kFootHi) - log(kFootLo))));
+        streamed = bytes > kStreamed ? log2(bytes / kStreamed) : 0.0;
+    }
+};
+
+// K cut into at most `wanted` slices of `per` slabs: `count` of them are not empty
+struct Slicing {
+    int wanted = 1;
+    int64_t per = 0, count = 0;
+    Slicing() {}
+    Slicing(int64_t KT, int wanted) : wanted(wanted), per(cdiv(KT, wanted)), count(cdiv(KT, per)) {}
+};
+
+// the pass that sums S slices
+double reduce_cost(const Problem &p, int64_t S)
+{
+    if (S <= 1) return 0.0;
+    return (1.51 + 0.0868 * (double)S) * g_cost_scale[GEMM_COST_FIXED] +
+           (double)p.M * p.N * 4.0 * (double)(S + 1) / (3.8e+06 * g_cost_scale[GEMM_COST_HBM]);
+}
+
+// What estimate_cost cannot fall below for this tile in any number of slices, without the pass that sums them
+double least_cost(const TileConfig &t, const Problem &p, int64_t tiles)
+{
+    const double t_hbm = (p.bytes + (double)p.M * p.N * 4.0) / (4.79e+06 * t.hbm_eff * g_cost_scale[GEMM_COST_HBM]);
+    const double t_l2 = (double)tiles * (double)p.KT * (t.BM + t.BN) * 128.0 / (2.18e+07 * g_cost_scale[GEMM_COST_L2]);
+    return 0.999999 * (2.68 * g_cost_scale[GEMM_COST_FIXED] + (t_hbm > t_l2 ? t_hbm : t_l2));  // (less what rounding may make of it)
+}
+
 // Estimated run time in microseconds of (tile, splits) on this shape.  Three floors: the
 // MFMA work as scheduled on 256 CUs (rounds of resident workgroups, slab time depending on
 // how many workgroups share a CU), HBM traffic for the unique bytes (limited by how many
 // bytes the resident workgroups keep in flight), and L2->CU traffic for all the bytes the
 // workgroups pull; plus launch/fill/drain and, with K slices, the reduce pass.
-// path: 0 = direct-load kernels, 1 = register-staged loads, 2 = register-staged loads of operands
-// that are only 2-byte aligned (each 16-byte load is then split up by the memory pipeline),
-// 3 = direct-load kernels on operands that are 4- or 8-byte aligned (row pieces straddle cache lines)
-// k_contig: how many of A and B have K as their contiguous dimension (0..2); the misaligned
-// classes depend on it (a K-contiguous row is what straddles lines or gets its loads split)
-// ksplit_ok: as for choose_uncached
-double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64_t KT, int splits, bool f32,
-                     int path, int k_contig, int NUM_CU, size_t max_ws_bytes, bool ksplit_ok)
+double estimate_cost(const TileConfig &t, const Problem &p, int64_t tiles, const Slicing &slices)
 {
     static const double kLayA4[3] = {0.867, 1.0, 0.986};  // 16-bit, path 3, by k_contig
     static const double kLayA2[3] = {1.14, 1.0, 1.19};   // 16-bit, path 2
     const double *const scale = g_cost_scale;
-    const int64_t tiles = cdiv(M, t.BM) * cdiv(N, t.BN);
-    const int64_t per = cdiv(KT, splits);
-    const int64_t S = cdiv(KT, per);
-    const int64_t W = tiles * S;
-    const double slots = (double)NUM_CU * t.wg_per_cu;
-    const double rounds = (double)cdiv(W, (int64_t)slots);
-    const int64_t share = cdiv(W, NUM_CU) < t.wg_per_cu ? cdiv(W, NUM_CU) : t.wg_per_cu;
+    const bool f32 = p.f32;
+    const int path = p.path, k_contig = p.k_contig;
+    const int64_t per = slices.per, S = slices.count, W = tiles * S;
+    const double slots = (double)p.num_cu * t.wg_per_cu;
+    const double rounds = (double)cdiv(W, (int64_t)p.num_cu * t.wg_per_cu);
+    const int64_t share = cdiv(W, p.num_cu) < t.wg_per_cu ? cdiv(W, p.num_cu) : t.wg_per_cu;
     const double alone = f32 ? t.f32_alone : t.f16_alone, full = f32 ? t.f32_full : t.f16_full;
     double slab = alone + (t.wg_per_cu > 1 ? (full - alone) * (double)(share - 1) / (t.wg_per_cu - 1) : 0.0);
-    const double esz = f32 ? 4.0 : 2.0;
-    // Operands small enough to stay in the XCDs' L2s between and within calls are served faster than ones that come
-    // from the memory side: the slab time falls, log-linearly in the bytes of A and B, from 1 x at kFootHi bytes to
-    // kFootFactor x at kFootLo bytes and below (fitted on the paper's power-of-two sizes, where it decides between
-    // one slice and several for the sizes up to 1024).
-    static const double kStreamed = 60e6;  // bytes of operands from which the stage kernel's slabs come later, the more the longer
-    static const double kFootLo = 2.23e+05, kFootHi = 1.52e+07, kFootFactor = 0.29;
-    const double foot = ((double)M * K + (double)K * N) * esz;
-    const double foot_factor = foot <= kFootLo ? kFootFactor
-                               : (foot >= kFootHi ? 1.0 : exp(log(kFootFactor) * (log(kFootHi) - log(foot)) / (log(kFootHi) - log(kFootLo))));
     // slabs' worth of extra time for a ragged K beside its last slab's own: a guarded loop on path 1 and 2; on direct loads, which
     // have none, a fitted term all the same (with zero in binary32 the picks of 39 calls were 2 .. 4 % slower, with zero or one
     // in 16 bits those of 367 and 375 calls 0.6 % slower and the same)
     double tail = f32 ? (path == 3 ? 3.23 : 1.27) : (path == 3 ? 2.8 : 2.32);
     if (path == 3) slab *= f32 ? t.f32_a4 : t.f16_a4 * kLayA4[k_contig];
     if (path == 1 || path == 2) slab *= f32 ? 1.05 : (path == 2 ? t.f16_a2 * kLayA2[k_contig] : t.general);
-    slab *= foot_factor;
+    slab *= p.foot_factor;
     // (its slab time hardly depends on where the operands come from; where it runs it is not behind the other kernel, whose
     // time for small operands is the lower one; a ragged last slab is one more.  16-byte rows are priced alike wherever they begin, on
     // the cache lines or off them, so a shape has one pick, which gemm_query_config can tell: with a price of their own for rows off the
     // lines the 240 of 3176 drawn products with such rows that had another pick took 1.015 times as long; where an operand is
     // K-contiguous, and straightened or not, 1.026, where neither is, 0.97)
-    if (!f32 && (path == 0 || path == 3) && runs_stage(t, M, W, per, K, !ksplit_ok, path, (M + N) * K * 2, false, NUM_CU)) {
+    if (!f32 && (path == 0 || path == 3) && runs_stage(t, p.M, W, per, p.K, !p.ksplit_ok, path, (p.M + p.N) * p.K * 2, false, p.num_cu)) {
         double stage = t.stage_slab * (path == 3 ? t.stage_a4 * kLayA4[k_contig] : 1.0);
-        if (foot > kStreamed) stage *= 1.0 + (t.BM + t.BN < 256 ? 0.35 : 0.1) * log2(foot / kStreamed);
+        stage *= 1.0 + (t.BM + t.BN < 256 ? 0.35 : 0.1) * p.streamed;
         if (stage < slab) slab = stage;
         tail = 0.0;
     }
@@ -425,23 +462,19 @@ double estimate_cost(const TileConfig &t, int64_t M, int64_t N, int64_t K, int64
     }
     slab *= scale[GEMM_COST_SLAB];
     double t_mfma = rounds * ((double)per * slab + t.fixed);
-    if (splits == 1) {
-        const int ts = tail_slices(t, tiles, KT, f32, NUM_CU, max_ws_bytes);
-        if (ts > 1) t_mfma -= tail_gain(t, tiles % NUM_CU, KT, ts, f32);
+    if (slices.wanted == 1) {
+        const int ts = tail_slices(t, tiles, p.KT, f32, p.num_cu, p.max_ws_bytes);
+        if (ts > 1) t_mfma -= tail_gain(t, tiles % p.num_cu, p.KT, ts, f32);
     }
-    if (K % (f32 ? 32 : 64) != 0) t_mfma += tail * slab;
-    const double unique = ((double)M * K + (double)K * N) * esz + (double)M * N * 4.0;
+    if (p.K % (f32 ? 32 : 64) != 0) t_mfma += tail * slab;
+    const double unique = p.bytes + (double)p.M * p.N * 4.0;
     const double resident = (double)W < slots ? (double)W : slots;
     double hbm_rate = resident * 1.5 * (t.BM + t.BN) * 128.0 / 0.848;  // bytes/us the workgroups keep in flight
     if (hbm_rate > 4.79e+06) hbm_rate = 4.79e+06;
     hbm_rate *= t.hbm_eff;
     const double t_hbm = unique / (hbm_rate * scale[GEMM_COST_HBM]);
     const double t_l2 = (double)W * (double)per * (t.BM + t.BN) * 128.0 / (2.18e+07 * scale[GEMM_COST_L2]);
-    double cost = 2.68 * scale[GEMM_COST_FIXED] + (t_mfma > t_hbm ? (t_mfma > t_l2 ? t_mfma : t_l2) : (t_hbm > t_l2 ? t_hbm : t_l2));
-    if (S > 1)
-        cost += (1.51 + 0.0868 * (double)S) * scale[GEMM_COST_FIXED] +
-                (double)M * N * 4.0 * (double)(S + 1) / (3.8e+06 * scale[GEMM_COST_HBM]);
-    return cost;
+    return 2.68 * scale[GEMM_COST_FIXED] + (t_mfma > t_hbm ? (t_mfma > t_l2 ? t_mfma : t_l2) : (t_hbm > t_l2 ? t_hbm : t_l2)) + reduce_cost(p, S);
 }
 
 // Products gemm_small_kernel is the fastest for: blocks for one round of CUs, and a K that sixteen waves request in a
@@ -475,6 +508,7 @@ bool small_allowed()
 // 1.065 (146, 22 of them 2.5 % and more slower), 3 % 1.070 (135, 19), 6 % 1.075 (118, 11), 10 % 1.091 (89, 7); over all products 1.015
 // with any of them.  Binary32, whose slab times are steadier, 3 %.
 const int kSlices[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
+constexpr int kNumSlices = sizeof(kSlices) / sizeof(kSlices[0]);
 double between_margin(int slices, bool f32) { return (slices & (slices - 1)) == 0 ? 1.0 : (f32 ? 1.03 : 1.10); }
 
 // max_ws_bytes: largest K-slice workspace the caller can provide (0 = no limit); automatic
@@ -493,23 +527,32 @@ void choose_uncached(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int 
     }
     // a forced slice count beyond the number of slabs means one slab per slice
     const int forced = g_forced_splits > 0 ? (int)(g_forced_splits < KT ? g_forced_splits : KT) : 0;
+    const Problem problem(M, N, K, KT, f32, path, k_contig, num_cu, max_ws_bytes, ksplit_ok);
+    Slicing slicings[kNumSlices];
+    int n = 0;
+    for (const int s : kSlices) {
+        const int cand = forced > 0 ? forced : s;
+        if (cand > 1 && cand > KT) break;
+        if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
+        slicings[n++] = Slicing(KT, cand);
+        if (forced > 0) break;
+    }
     for (int t = 0; t < kNumTiles; ++t) {
         if (g_forced_tile >= 0 && t != g_forced_tile) continue;
         if (g_forced_tile < 0 && kTiles[t].fallback >= 0 && !ksplit_ok) continue;
         if (g_forced_tile < 0 && !(((f32 ? kTiles[t].auto32 : kTiles[t].auto16) >> path) & 1)) continue;
-        for (const int s : kSlices) {
-            const int cand = forced > 0 ? forced : s;
-            if (cand > 1 && cand > KT) break;
-            if (forced == 0 && cand > 1 && max_ws_bytes > 0 && ws_bytes(cand, M, N) > max_ws_bytes) break;
-            const double c = estimate_cost(kTiles[t], M, N, K, KT, cand, f32, path, k_contig, num_cu, max_ws_bytes, ksplit_ok) *
-                             (forced > 0 ? 1.0 : between_margin(s, f32));
-            if (c < best) { best = c; tile = t; splits = cand; }
-            if (forced > 0) break;
+        const int64_t tiles = cdiv(M, kTiles[t].BM) * cdiv(N, kTiles[t].BN);
+        const double least = least_cost(kTiles[t], problem, tiles);
+        for (int i = 0; i < n; ++i) {
+            if (least + 0.999999 * reduce_cost(problem, slicings[i].count) >= best) break;  // (and more slices cost no less)
+            const double c = estimate_cost(kTiles[t], problem, tiles, slicings[i]) * (forced > 0 ? 1.0 : between_margin(slicings[i].wanted, f32));
+            if (c < best) { best = c; tile = t; splits = slicings[i].wanted; }
         }
     }
 }
 
-// The selection costs about a hundred evaluations of the model; calls repeat shapes, so the last picks
+// The selection costs up to a hundred evaluations of the model (1 .. 2 us; of 16-bit products that fill the chip 0.4, for what cannot
+// be the fastest any more is left out: 3.3 with every tile and count evaluated); calls repeat shapes, so the last picks
 // are kept (g_mutex held; any change of the forced configuration or of the model's scales
 // starts a new epoch and thereby empties the table).
 struct Pick {
@@ -916,12 +959,13 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         if (small_allowed() && serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, req.words, key.num_cu)) cand.emplace_back(0.0, kSmall, 1);
+        const Problem problem(key.M, key.N, key.K, KT, key.f32 != 0, key.path, key.k_contig, key.num_cu, 0, key.ksplit_ok != 0);
         for (int t = 0; t < kNumTiles; ++t) {
             if (kTiles[t].fallback >= 0 && !key.ksplit_ok) continue;
+            const int64_t tiles = cdiv(key.M, kTiles[t].BM) * cdiv(key.N, kTiles[t].BN);
             for (const int s : kSlices) {
                 if (s > 1 && s > KT) break;
-                cand.emplace_back(estimate_cost(kTiles[t], key.M, key.N, key.K, KT, s, key.f32 != 0, key.path, key.k_contig,
-                                                key.num_cu, 0, key.ksplit_ok != 0) * between_margin(s, key.f32 != 0), t, s);
+                cand.emplace_back(estimate_cost(kTiles[t], problem, tiles, Slicing(KT, s)) * between_margin(s, problem.f32), t, s);
             }
         }
     }
