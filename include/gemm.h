@@ -207,8 +207,8 @@ int gemm_cost_model_scale(int term, double factor);
  * enqueued back to back; then the four fastest and the cost model's own pick again, twice in turn with 24 timed
  * launches each, the better take of each kept), records the fastest in a process-wide table, computes C
  * once more with it and writes "<tile>:s<slices>" into buf.  Later calls with the same M, N, K,
- * operand width (16-bit or binary32), layouts and alignment class on a device with as many CUs use
- * the recorded pair (so do gemm_query_config*); a forced configuration still overrides it, and
+ * operand width (16-bit or binary32), layouts and alignment class (16, 4 or 2 bytes; rows on the cache lines and off them are
+ * one class) on a device with as many CUs use the recorded pair (so do gemm_query_config*); a forced configuration still overrides it, and
  * gemm_f16f32_noalloc ignores an entry whose partial sums do not fit its array.  The call blocks the
  * host until hip_stream has drained, allocates (events, K-slice workspace), and cannot be captured into a
  * HIP graph.  Errors as the entry point's, plus GEMM_ERR_INVALID_ARG for an unknown kind, a negative
@@ -229,12 +229,13 @@ int gemm_tune_clear(void);
  * The recorded pairs as a text file, so that a service tunes once and later processes start with the picks:
  * gemm_tune_save writes every pair gemm_tune has recorded (one line each: bytes per operand element, M, N,
  * K, alignment class, number of K-contiguous operands, CU count, whether the operands are whole slabs and
- * granules, tile name, K slices, and "small" where the kernel for small products runs; '#' starts a comment
+ * granules, tile name, K slices, "small" where the kernel for small products runs, and "words" where only bases on
+ * 4-byte boundaries let it (see gemm_query_config; a class of its own); '#' starts a comment
  * line); gemm_tune_load adds the pairs of such a file to the table, replacing entries for the same class.  Host only.  GEMM_ERR_INVALID_ARG if the file cannot be
  * opened or written, or (load) if any line does not parse, names a tile this build does not have or one
  * that cannot serve the line's class (the kernel for small products included), a K-slice count outside 1 .. 32
- * (what gemm_tune records), or has another word than "small" or a '#' comment behind it: then
- * nothing of the file is taken over.
+ * (what gemm_tune records), or has other words behind it than "small", "words", both in this order, or a '#' comment, or
+ * "words" on a class that these do not tell apart: then nothing of the file is taken over.
  */
 int gemm_tune_save(const char *path);
 int gemm_tune_load(const char *path);

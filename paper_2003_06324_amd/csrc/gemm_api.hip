@@ -494,6 +494,13 @@ bool serves_small(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_con
     return K <= (f32 ? 512 : path == 2 ? (words ? 1152 : (k_contig > 0 ? 256 : 768)) : 768);
 }
 
+// Whether it is bases on words that bring the small kernel in: a class of their own for recorded picks, because bases off the words
+// leave the tile kernels to choose from, and a pick of either kind is none for the other.
+bool by_words_only(int64_t M, int64_t N, int64_t K, bool f32, int path, int k_contig, bool words, int num_cu)
+{
+    return words && serves_small(M, N, K, f32, path, k_contig, true, num_cu) && !serves_small(M, N, K, f32, path, k_contig, false, num_cu);
+}
+
 // What can be forced, or traced, are the tile kernels: with any such setting the small kernel stays out, whether the
 // rule above, a recorded pick or gemm_tune would run it (g_mutex held).
 bool small_allowed()
@@ -569,10 +576,11 @@ uint64_t g_epoch = 1;
 struct ShapeKey {
     int64_t M, N, K;
     int f32, path, k_contig, num_cu, ksplit_ok;
+    int words;  // by_words_only
     bool operator<(const ShapeKey &o) const
     {
-        return std::tie(M, N, K, f32, path, k_contig, num_cu, ksplit_ok) <
-               std::tie(o.M, o.N, o.K, o.f32, o.path, o.k_contig, o.num_cu, o.ksplit_ok);
+        return std::tie(M, N, K, f32, path, k_contig, num_cu, ksplit_ok, words) <
+               std::tie(o.M, o.N, o.K, o.f32, o.path, o.k_contig, o.num_cu, o.ksplit_ok, o.words);
     }
 };
 std::map<ShapeKey, std::pair<int, int>> g_tuned;
@@ -592,7 +600,8 @@ void choose(int64_t M, int64_t N, int64_t K, int64_t KT, bool f32, int path, int
     const uint64_t h = (uint64_t)M * 0x9E3779B97F4A7C15ull ^ (uint64_t)N * 0xC2B2AE3D27D4EB4Full ^
                        (uint64_t)K * 0x165667B19E3779F9ull ^ (uint64_t)(words * 64 + k_contig * 16 + path * 4 + f32 * 2 + ksplit_ok);
     if (g_forced_tile < 0 && g_forced_splits == 0 && !g_tuned.empty()) {
-        const auto it = g_tuned.find(ShapeKey{M, N, K, (int)f32, path, k_contig, num_cu, (int)ksplit_ok});
+        const auto it = g_tuned.find(ShapeKey{M, N, K, (int)f32, path, k_contig, num_cu, (int)ksplit_ok,
+                                              (int)by_words_only(M, N, K, f32, path, k_contig, words, num_cu)});
         if (it != g_tuned.end() && (it->second.first != kSmall || small_allowed()) && (max_ws_bytes == 0 || it->second.second == 1 ||
                                     ws_bytes(it->second.second, M, N) <= max_ws_bytes)) {
             tile = it->second.first;
@@ -786,7 +795,8 @@ int gemm_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     // rows begin in the middle of a word, and gemm_small_kernel can read them word by word
     const bool words = !f32 && path == 2 && (((uintptr_t)A | (uintptr_t)B) & 3) == 0;
     if (tune) {
-        tune->key = ShapeKey{M, N, K, (int)f32, path, (int)akc + (int)bkc, num_cu, (int)ksplit_ok};
+        tune->key = ShapeKey{M, N, K, (int)f32, path, (int)akc + (int)bkc, num_cu, (int)ksplit_ok,
+                             (int)by_words_only(M, N, K, f32, path, (int)akc + (int)bkc, words, num_cu)};
         tune->filled = true;
         tune->words = words;
     }
@@ -1039,10 +1049,7 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         const int64_t per = cdiv(KT, best_splits);
-        // (a class does not tell whether rows can be read word by word: where it is that which brings the kernel for small products
-        // in, nothing is recorded and the rule goes on choosing it)
-        if (best_tile == kSmall && !serves_small(key.M, key.N, key.K, key.f32 != 0, key.path, key.k_contig, false, key.num_cu)) g_tuned.erase(key);
-        else g_tuned[key] = std::make_pair(best_tile, (int)cdiv(KT, per));
+        g_tuned[key] = std::make_pair(best_tile, (int)cdiv(KT, per));
         ++g_epoch;
     }
     // the product, by the configuration just recorded (unless one is forced)
@@ -1121,8 +1128,8 @@ int gemm_tune_clear(void)
 }
 
 // One recorded pick per line: "<bytes per operand element> M N K <alignment class> <K-contiguous operands> <CUs>
-// <whole slabs and granules> <tile> <K slices>", and "small" if the small kernel runs as that tile; lines starting
-// with '#' are comments.
+// <whole slabs and granules> <tile> <K slices>", "small" if the small kernel runs as that tile, and "words" for the class that
+// by_words_only tells; lines starting with '#' are comments.
 int gemm_tune_save(const char *path)
 {
     if (path == nullptr) return GEMM_ERR_INVALID_ARG;
@@ -1132,8 +1139,8 @@ int gemm_tune_save(const char *path)
     fprintf(f, "# gemm_tune picks: elem_bytes M N K class k_contig cus whole tile slices\n");
     for (const auto &e : g_tuned) {
         const ShapeKey &k = e.first;
-        fprintf(f, "%d %lld %lld %lld %d %d %d %d %s %d%s\n", k.f32 ? 4 : 2, (long long)k.M, (long long)k.N, (long long)k.K, k.path,
-                k.k_contig, k.num_cu, k.ksplit_ok, tile_of(e.second.first).name, e.second.second, e.second.first == kSmall ? " small" : "");
+        fprintf(f, "%d %lld %lld %lld %d %d %d %d %s %d%s%s\n", k.f32 ? 4 : 2, (long long)k.M, (long long)k.N, (long long)k.K, k.path,
+                k.k_contig, k.num_cu, k.ksplit_ok, tile_of(e.second.first).name, e.second.second, e.second.first == kSmall ? " small" : "", k.words ? " words" : "");
     }
     return fclose(f) == 0 ? GEMM_OK : GEMM_ERR_INVALID_ARG;
 }
@@ -1151,7 +1158,7 @@ int gemm_tune_load(const char *path)
         long long M, N, K;
         int esz, path_, kc, cus, whole, slices;
         int end = 0;
-        char name[32], kernel[8] = "", more[2] = "";
+        char name[32];
         if (sscanf(line, "%d %lld %lld %lld %d %d %d %d %31s %d%n", &esz, &M, &N, &K, &path_, &kc, &cus, &whole, name, &slices, &end) != 10 ||
             (esz != 2 && esz != 4) || M <= 0 || N <= 0 || K <= 0 || path_ < 0 || path_ > 3 || kc < 0 || kc > 2 || cus <= 0 ||
             (whole != 0 && whole != 1) || slices < 1 || slices > 32) {   // gemm_tune records 1 .. 32 slices
@@ -1161,19 +1168,25 @@ int gemm_tune_load(const char *path)
         int tile = -1;
         for (int i = 0; i < kNumTiles; ++i)
             if (strcmp(name, kTiles[i].name) == 0) tile = i;
-        // behind the slices: nothing, a comment, or the word for the small kernel, which then has to serve the class
-        const int words = sscanf(line + end, "%7s %1s", kernel, more);
-        if (words > 0 && kernel[0] != '#') {
-            const bool ok = strcmp(kernel, "small") == 0 && (words == 1 || more[0] == '#') && tile == kSmallAs && slices == 1 &&
-                            serves_small(M, N, K, esz == 4, path_, kc, false, cus);
-            tile = ok ? kSmall : -1;
+        // behind the slices: "small", which then has to serve the class, "words", both in this order, or nothing; then a comment
+        bool small = false, by_words = false, known = true;
+        const char *rest = line + end;
+        char word[8];
+        for (int used = 0; known && sscanf(rest, "%7s%n", word, &used) == 1 && word[0] != '#'; rest += used) {
+            known = (strcmp(word, "small") == 0 && !small && !by_words) || (strcmp(word, "words") == 0 && !by_words);
+            small = small || strcmp(word, "small") == 0;
+            by_words = by_words || strcmp(word, "words") == 0;
         }
+        if (by_words && !by_words_only(M, N, K, esz == 4, path_, kc, path_ == 2, cus)) known = false;
+        if (small && !(tile == kSmallAs && slices == 1 && serves_small(M, N, K, esz == 4, path_, kc, by_words, cus))) known = false;
+        if (!known) tile = -1;
+        else if (small) tile = kSmall;
         // a tile this build does not have, or one that does not serve the class, makes the file invalid as a whole
         if (tile < 0 || (tile_of(tile).fallback >= 0 && !whole)) {
             rc = GEMM_ERR_INVALID_ARG;
             break;
         }
-        read[ShapeKey{M, N, K, esz == 4, path_, kc, cus, whole}] = std::make_pair(tile, slices);
+        read[ShapeKey{M, N, K, esz == 4, path_, kc, cus, whole, (int)by_words}] = std::make_pair(tile, slices);
     }
     fclose(f);
     if (rc != GEMM_OK) return rc;   // nothing of a bad file is taken over
