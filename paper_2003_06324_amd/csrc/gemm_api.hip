@@ -516,7 +516,8 @@ bool small_allowed()
 // with any of them.  Binary32, whose slab times are steadier, 3 %.
 const int kSlices[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
 constexpr int kNumSlices = sizeof(kSlices) / sizeof(kSlices[0]);
-double between_margin(int slices, bool f32) { return (slices & (slices - 1)) == 0 ? 1.0 : (f32 ? 1.03 : 1.10); }
+bool power_of_two(int slices) { return (slices & (slices - 1)) == 0; }
+double between_margin(int slices, bool f32) { return power_of_two(slices) ? 1.0 : (f32 ? 1.03 : 1.10); }
 
 // max_ws_bytes: largest K-slice workspace the caller can provide (0 = no limit); automatic
 // picks that would need more are not considered.
@@ -1014,14 +1015,31 @@ int tune_impl(int64_t M, int64_t N, int64_t K, const void *A, int layA, int64_t 
             if (e) (void)hipEventDestroy(e);
         (void)hipGetLastError();   // e.g. a candidate with no memory for its slices, or a stream under capture
     };
+    // Without a limit every tile is timed in 1, 2, 4 .. 32 slices, and behind the model's favourite, which may have another count;
+    // the counts between are timed around the four fastest only (all of them everywhere: 48 ms instead of 21 at 1536x1024x2048,
+    // 3.3 s instead of 1.3 at 8192^3).
     timing_list all, first, finalists, second;
-    for (const auto &c : cand) all.emplace_back(0.0f, std::get<1>(c), std::get<2>(c));
+    for (const auto &c : cand)
+        if (max_candidates > 0 || all.empty() || power_of_two(std::get<2>(c))) all.emplace_back(0.0f, std::get<1>(c), std::get<2>(c));
     // Six timed launches per candidate, behind 40 untimed ones of the model's favourite.  Then the four fastest and
     // the model's favourite again, twice in turn with 24 launches each, the better take of each kept: short kernels
     // time +-20 % on six launches, and a pick that is not measurably faster than the model's should not replace it.
     pass(all, 40, 2, 6, first);
     std::sort(first.begin(), first.end());
     if (first.size() > 4) first.resize(4);
+    if (max_candidates == 0) {
+        timing_list between;
+        for (const auto &c : cand) {
+            const int s = std::get<2>(c);
+            bool near = false;
+            for (const auto &f : first) near = near || (std::get<1>(f) == std::get<1>(c) && s < 2 * std::get<2>(f) && 2 * s > std::get<2>(f));
+            if (near && !power_of_two(s) && !(std::get<1>(c) == std::get<1>(all[0]) && s == std::get<2>(all[0])))
+                between.emplace_back(0.0f, std::get<1>(c), s);
+        }
+        if (!between.empty()) pass(between, 40, 2, 6, first);
+        std::sort(first.begin(), first.end());
+        if (first.size() > 4) first.resize(4);
+    }
     finalists = first;
     bool has_model = false;
     for (const auto &f : first) has_model = has_model || (std::get<1>(f) == std::get<1>(all[0]) && std::get<2>(f) == std::get<2>(all[0]));
