@@ -116,6 +116,7 @@ def test_a_full_search_does_not_time_every_slice_count_of_every_tile():
     pairs that the model holds for the cheapest; 4.2 times with all of them."""
     import time
     import torch
+    import paper_2003_06324_amd as g
     M = N = K = 4096
     A, B = (torch.randn(M * K, device="cuda").half() for _ in range(2))
     C = torch.empty(M * N, dtype=torch.float32, device="cuda")
