@@ -274,7 +274,7 @@ int gemm_query_config_layouts(int elem_bytes, int64_t M, int64_t N, int64_t K, i
  * clock at the phase boundaries of its tile: word 0 start, 1 first operands landed (direct-load
  * kernels only), 2 K loop done, 3 shared memory free for the epilogue, 4 stores issued,
  * 5 stores complete; word 7 says where it ran (XCC id in the upper half, the hardware id
- * register in the lower).  Workgroups numbered beyond the buffer record nothing; a later
+ * register in the lower), and word 6 is set to 1 by kernels that straighten rows of A or B to the cache lines.  Workgroups numbered beyond the buffer record nothing; a later
  * launch overwrites an earlier one's records.  NULL switches it off (the default).  The
  * caller owns the buffer and keeps it alive while set.  Process-wide.
  */

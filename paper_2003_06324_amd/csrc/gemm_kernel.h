@@ -96,18 +96,20 @@ struct KernelArgs {
 // Profiling aid: with a trace buffer set, thread 0 of every workgroup records the constant-rate
 // (100 MHz) clock at the phase boundaries of its tile - 0 start, 1 first slab landed, 2 K loop
 // done, 3 LDS free for the epilogue, 4 stores issued, 5 stores complete - and in word 7 where it
-// ran (XCC id above bit 32, the hardware id register below).  Costs a scalar branch per mark.
+// ran (XCC id above bit 32, the hardware id register below); kernels that straighten rows to the
+// cache lines put a one into word 6.  Costs a scalar branch per mark.
 __device__ __forceinline__ void trace_mark(const KernelArgs &p, int slot)
 {
     if (p.trace != nullptr && threadIdx.x == 0 && (int)blockIdx.x < p.trace_records)
         p.trace[(size_t)blockIdx.x * 8 + slot] = wall_clock64();
 }
-__device__ __forceinline__ void trace_place(const KernelArgs &p)
+template <bool STRAIGHTENED = false> __device__ __forceinline__ void trace_place(const KernelArgs &p)
 {
     if (p.trace != nullptr && threadIdx.x == 0 && (int)blockIdx.x < p.trace_records) {
         const unsigned hw = __builtin_amdgcn_s_getreg((31 << 11) | 4);    // HW_ID: wave, SIMD, CU, SH, SE ...
         const unsigned xcc = __builtin_amdgcn_s_getreg((31 << 11) | 20);  // XCC_ID
         p.trace[(size_t)blockIdx.x * 8 + 7] = ((unsigned long long)xcc << 32) | hw;
+        if constexpr (STRAIGHTENED) p.trace[(size_t)blockIdx.x * 8 + 6] = 1;
     }
 }
 

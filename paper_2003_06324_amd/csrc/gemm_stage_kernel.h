@@ -222,7 +222,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_stage_kernel(const KernelArg
     WorkItem item;
     if (!work_item(p, KT, item)) return;
     trace_mark(p, 0);
-    trace_place(p);
+    trace_place<SKEW>(p);
     const int m0 = item.tile_m * BM, n0 = item.tile_n * BN;
 
     // slabs of this slice; only the operand's last one can be ragged

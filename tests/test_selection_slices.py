@@ -9,7 +9,7 @@ import paper_2003_06324_amd as g
 def test_slices_fill_the_chip():
     g.force_config(None)
     g.cost_model_scale(-1)
-    # 40, 48 and 24 tiles of 128x128 or twice as many of half the size: powers of two would fill 160, 192 and 192 of 256 CUs
+    # 40, 42 and 24 tiles of 128x128 or twice as many of half the size: powers of two would fill 160, 168 and 192 of 256 CUs
     for M, N, K in ((600, 912, 16608), (786, 669, 8937 // 64 * 64), (744, 488, 48576)):
         tile, slices = g.query_config(2, M, N, K, 16, g.ROW_MAJOR, g.COL_MAJOR).split(":s")
         bm, bn = (int(x) for x in tile[1:].split("x"))
