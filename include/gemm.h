@@ -208,7 +208,9 @@ int gemm_cost_model_scale(int term, double factor);
  * launches each, the better take of each kept), records the fastest in a process-wide table, computes C
  * once more with it and writes "<tile>:s<slices>" into buf.  Later calls with the same M, N, K,
  * operand width (16-bit or binary32), layouts and alignment class (16, 4 or 2 bytes; rows on the cache lines and off them are
- * one class) on a device with as many CUs use the recorded pair (so do gemm_query_config*); a forced configuration still overrides it, and
+ * one class, and of 2 bytes the products that only bases on 4-byte boundaries bring to the kernel for small ones, see
+ * gemm_query_config, are another) on a device with as many CUs use the recorded pair (so do gemm_query_config*, which know
+ * nothing of that last class); a forced configuration still overrides it, and
  * gemm_f16f32_noalloc ignores an entry whose partial sums do not fit its array.  The call blocks the
  * host until hip_stream has drained, allocates (events, K-slice workspace), and cannot be captured into a
  * HIP graph.  Errors as the entry point's, plus GEMM_ERR_INVALID_ARG for an unknown kind, a negative
